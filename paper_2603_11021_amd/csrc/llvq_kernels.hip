@@ -1482,6 +1482,7 @@ __global__ void __launch_bounds__(kThreads, 8) encode_kernel(const unsigned char
 }  // namespace
 
 #include "llvq_search_kernel.h"
+#include "llvq_group_kernel.h"
 
 namespace {
 
@@ -2429,7 +2430,7 @@ int llvq_gptq_quantize_levels(llvq_ctx* ctx, float* d_W, int N, int KB, size_t l
     return LLVQ_OK;
 }
 
-// rows of a chunk of llvq_gptq_group_scales (one KB x KB system per row is held in the workspace)
+// rows whose KB x KB systems the workspace of llvq_gptq_group_scales has room for at least
 static int group_chunk_rows(int N) { return N < 128 ? N : 128; }
 
 size_t llvq_gptq_group_scales_workspace_bytes(int N, int KB) {
@@ -2446,37 +2447,33 @@ int llvq_gptq_group_scales(llvq_ctx* ctx, float* d_Wq, const float* d_W0, int N,
     if (ws_bytes < llvq_gptq_group_scales_workspace_bytes(N, KB)) return LLVQ_EINVAL;
     if (!aligned(d_Wq, 4) || !aligned(d_W0, 4) || !aligned(d_H, 4) || !aligned(d_gain, 2) || !aligned(d_s, 4) || !aligned(d_ws, 16)) return LLVQ_EALIGN;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (!ctx->blas && rocblas_create_handle(&ctx->blas) != rocblas_status_success) { ctx->set_error("rocblas_create_handle failed"); return LLVQ_EHIP; }
-    if (rocblas_set_stream(ctx->blas, st) != rocblas_status_success) { ctx->set_error("rocblas_set_stream failed"); return LLVQ_EHIP; }
-    const size_t K = (size_t)24 * KB;
-    const int C = group_chunk_rows(N);
-    auto up = [](size_t v) { return (v + 63) & ~(size_t)63; };
-    float* d_T = reinterpret_cast<float*>(d_ws);                       // [N][K]  = W0 H
-    float* d_Z = d_T + up((size_t)N * K);                              // [C][K]  = Wq[rows, block p] H[block p, :]
-    float* d_M = d_Z + up((size_t)C * K);                              // [C][KB][KB]
-    float* d_r = d_M + up((size_t)C * KB * KB);                        // [N][KB]
-    const float one = 1.0f, zero = 0.0f;
-    // T = W0 H.  Row-major arrays seen column-major: T^T (K x N) = H (K x K, symmetric) * W0^T (K x N, leading dimension ldw)
-    rocblas_status bs = rocblas_sgemm(ctx->blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)K, N, (rocblas_int)K, &one,
-                                      d_H, (rocblas_int)K, d_W0, (rocblas_int)ldw, &zero, d_T, (rocblas_int)K);
-    if (bs != rocblas_status_success) { ctx->set_error(std::string("rocblas: ") + rocblas_status_to_string(bs)); return LLVQ_EHIP; }
-    {
-        const size_t n = (size_t)N * KB;
-        hipLaunchKernelGGL(group_rhs_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d_Wq, ldw, d_T, K, N, KB, d_r);
-    }
-    for (int row0 = 0; row0 < N; row0 += C) {
-        const int c = std::min(C, N - row0);
-        for (int p = 0; p < KB; p++) {
-            // Z^T (K x c) = H[block p, :]^T (K x 24) * Wq[rows, block p]^T (24 x c)
-            bs = rocblas_sgemm(ctx->blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)K, c, 24, &one,
-                               d_H + (size_t)24 * p * K, (rocblas_int)K, d_Wq + (size_t)row0 * ldw + (size_t)24 * p, (rocblas_int)ldw, &zero,
-                               d_Z, (rocblas_int)K);
-            if (bs != rocblas_status_success) { ctx->set_error(std::string("rocblas: ") + rocblas_status_to_string(bs)); return LLVQ_EHIP; }
-            const size_t n = (size_t)c * KB;
-            hipLaunchKernelGGL(group_gram_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d_Wq, ldw, d_Z, K, row0, c, KB, p, d_M);
+    // As many rows at a time as the workspace holds systems for (lower triangles and right-hand sides), whole groups of rows
+    // of the first kernel where there are several chunks.  Few rows and columns: the walk over H is cut into parts, until
+    // there are about four workgroups per compute unit.
+    const size_t n_sys = group_system(KB);
+    const size_t floats = llvq_gptq_group_scales_workspace_bytes(N, KB) / sizeof(float) - 64;
+    const int units = (KB + 3) / 4, p_groups = (KB + kGroupP - 1) / kGroupP, group_rows = 32 * kGroupRowWaves;
+    const int row_groups = (N + group_rows - 1) / group_rows;
+    const int splits = std::max(1, std::min(std::min(kGroupMaxSplits, units), 4 * ctx->num_cu / std::max(1, row_groups * p_groups)));
+    size_t chunk = std::min<size_t>((size_t)N, (floats - (size_t)splits * N * KB) / n_sys);
+    if (chunk < (size_t)N && chunk > (size_t)group_rows) chunk -= chunk % group_rows;
+    float* d_sys = reinterpret_cast<float*>(d_ws);                     // [chunk] systems
+    float* d_r = d_sys + chunk * n_sys;                                // [splits][chunk][KB]
+    const size_t lds_head = (2 * (size_t)((KB + 3) & ~3) + 4) * sizeof(float), lds_full = lds_head + n_sys * sizeof(float);
+    const bool in_lds = lds_full <= kGroupLdsMax;
+    for (size_t row0 = 0; row0 < (size_t)N; row0 += chunk) {
+        const int c = (int)std::min(chunk, (size_t)N - row0);
+        hipLaunchKernelGGL(group_gram_kernel, dim3((unsigned)((c + group_rows - 1) / group_rows), (unsigned)p_groups, (unsigned)splits), dim3(64 * kGroupRowWaves), 0, st,
+                           d_Wq, d_W0, ldw, d_H, (int)row0, c, KB, d_sys, d_r);
+        if (in_lds) {
+            if (int rc = set_lds<group_solve_kernel<true>>(ctx, kGroupLdsMax)) return rc;
+            hipLaunchKernelGGL(group_solve_kernel<true>, dim3(c), dim3(64 * kGroupSolveWaves), lds_full, st, d_sys, d_r, splits, lambda, (int)row0, c, KB, d_Wq, ldw,
+                               reinterpret_cast<uint16_t*>(d_gain), d_s);
+        } else {
+            if (int rc = set_lds<group_solve_kernel<false>>(ctx, kGroupLdsMax)) return rc;
+            hipLaunchKernelGGL(group_solve_kernel<false>, dim3(c), dim3(64 * kGroupSolveWaves), lds_head, st, d_sys, d_r, splits, lambda, (int)row0, c, KB, d_Wq, ldw,
+                               reinterpret_cast<uint16_t*>(d_gain), d_s);
         }
-        hipLaunchKernelGGL(group_solve_kernel, dim3(c), dim3(kGroupSolveThreads), 0, st, d_M, d_r, lambda, row0, c, KB, d_Wq, ldw,
-                           reinterpret_cast<uint16_t*>(d_gain), d_s);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(ctx, e, "group scales launch");
     }
