@@ -1837,13 +1837,18 @@ static int launch_encode(llvq_ctx* ctx, const int8_t* d_x, size_t n, void* d_idx
 
 // nearest-direction search of n blocks whose rows start ldw floats apart
 static int launch_search(llvq_ctx* ctx, int metric, const float* d_w, size_t ldw, size_t n, int8_t* d_points, float* d_score, hipStream_t st) {
-    const int grid = (int)std::min<size_t>(n, (size_t)2 * ctx->num_cu);
-    if (metric == LLVQ_ANGULAR)
-        hipLaunchKernelGGL(search_mfma_kernel<LLVQ_ANGULAR>, dim3(grid), dim3(kMfmaSearchThreads), 0, st, ctx->d_search, ctx->search_lay,
-                           ctx->d_tile_a, ctx->d_tile_scale, ctx->d_words, d_w, ldw, n, d_points, d_score);
-    else
-        hipLaunchKernelGGL(search_mfma_kernel<LLVQ_EUCLIDEAN>, dim3(grid), dim3(kMfmaSearchThreads), 0, st, ctx->d_search, ctx->search_lay,
-                           ctx->d_tile_a, ctx->d_tile_scale, ctx->d_words, d_w, ldw, n, d_points, d_score);
+    // two workgroups of four waves per compute unit (two waves per SIMD: the bounds of 8192 pairs fill the registers)
+    const int grid = (int)std::min<size_t>((n + kSearchWaves - 1) / kSearchWaves, (size_t)2 * ctx->num_cu);
+    const size_t lds = (kSearchTabDwords + kSearchWaves * kSearchScratch) * sizeof(uint32_t);
+#define LLVQ_LAUNCH_SEARCH(METRIC)                                                                                                          \
+    do {                                                                                                                                    \
+        if (int rc = set_lds<search_kernel<METRIC>>(ctx, lds)) return rc;                                                                   \
+        hipLaunchKernelGGL(search_kernel<METRIC>, dim3(grid), dim3(64 * kSearchWaves), lds, st, ctx->d_search, ctx->search_lay,             \
+                           (uint32_t)ctx->m_max, ctx->d_tile_a, ctx->d_tile_scale, d_w, ldw, n, d_points, d_score);                         \
+    } while (0)
+    if (metric == LLVQ_ANGULAR) LLVQ_LAUNCH_SEARCH(LLVQ_ANGULAR);
+    else LLVQ_LAUNCH_SEARCH(LLVQ_EUCLIDEAN);
+#undef LLVQ_LAUNCH_SEARCH
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "search launch");
 }
