@@ -13,6 +13,7 @@
 #include <type_traits>
 
 #include "llvq_tables.h"
+#include "llvq_wide.h"
 
 #if defined(__HIPCC__)
 #define LLVQ_HD __host__ __device__ __forceinline__
@@ -33,15 +34,19 @@ namespace llvq {
 #endif
 typedef const LLVQ_LDS unsigned char* TabBase;
 
-struct TabPtrs {
+// LAY: where the tables lie inside the blob (Lay13, or Lay19 for the larger unions)
+template <class LAY>
+struct TabPtrsOf {
     TabBase base;                  // LDS-resident part of the blob
     const unsigned char* gbase;    // the whole blob in global memory (for kernels that keep only its first part in LDS)
     uint32_t ncls;
     uint64_t npoints;
 };
+typedef TabPtrsOf<Lay13> TabPtrs;
 
-LLVQ_HD TabPtrs make_tab_ptrs(TabBase base, const unsigned char* gbase, const TableLayout& L) {
-    TabPtrs T;
+template <class LAY = Lay13>
+LLVQ_HD TabPtrsOf<LAY> make_tab_ptrs(TabBase base, const unsigned char* gbase, const TableLayout& L) {
+    TabPtrsOf<LAY> T;
     T.base = base;
     T.gbase = gbase;
     T.ncls = L.ncls;
@@ -78,14 +83,14 @@ LLVQ_HD V tab_load(TabBase p) {
 }
 
 // element `byte_off` bytes into the table at constant offset OFF
-template <typename V, uint32_t OFF>
-LLVQ_HD V tab_at(const TabPtrs& T, uint32_t byte_off) {
+template <typename V, uint32_t OFF, class LAY>
+LLVQ_HD V tab_at(const TabPtrsOf<LAY>& T, uint32_t byte_off) {
     return tab_load<V>(T.base + OFF + byte_off);
 }
 
 // the same for the tables that stay in global memory
-template <typename V, uint32_t OFF>
-LLVQ_HD V gtab_at(const TabPtrs& T, uint32_t byte_off) {
+template <typename V, uint32_t OFF, class LAY>
+LLVQ_HD V gtab_at(const TabPtrsOf<LAY>& T, uint32_t byte_off) {
     return *reinterpret_cast<const V*>(T.gbase + OFF + byte_off);
 }
 
@@ -119,8 +124,9 @@ LLVQ_HD uint32_t bfe6(uint32_t v, uint32_t off) {
 // Entry (F, m) of spread6 is dword F * kSpreadPitch + m (the odd pitch spreads equal m of different masks over
 // the LDS banks).  Fx = F * 4 * kSpreadPitch; the source is bits o..o+5 of plane (bits past the mask's
 // popcount do not change the entry's value).
-LLVQ_HD uint32_t spread6_at(const TabPtrs& T, uint32_t Fx, uint32_t plane, uint32_t o) {
-    return tab_at<uint32_t, kOffSpread6>(T, Fx + (bfe6(plane, o) << 2));
+template <class LAY>
+LLVQ_HD uint32_t spread6_at(const TabPtrsOf<LAY>& T, uint32_t Fx, uint32_t plane, uint32_t o) {
+    return tab_at<uint32_t, LAY::kOffSpread6>(T, Fx + (bfe6(plane, o) << 2));
 }
 
 // Marks a product that several table addresses share: without it the compiler repeats the multiplication inside
@@ -180,24 +186,25 @@ struct ClassHit {
     uint64_t Ic;      // index inside the class
 };
 
-LLVQ_HD ClassHit find_class(const TabPtrs& T, uint64_t I) {
+template <class LAY>
+LLVQ_HD ClassHit find_class(const TabPtrsOf<LAY>& T, uint64_t I) {
     // the bucket of the top bits names the class of the bucket's first index; the class of I is that one or one of
     // the next few.  Three candidates are tested per round (their offsets are read together), so that the rare lane
     // whose bucket spans several small classes does not make its whole wavefront wait for one table read per class.
     // The class is carried as the byte offset of its cls_off entry, so the candidates' addresses are constants
     // apart; the table ends with offset[ncls] = N and three entries above every index, which no lane passes.
-    uint32_t c8 = tab_at<uint16_t, kOffBucket>(T, (uint32_t)(I >> kBucketShift) * 2u);
+    uint32_t c8 = tab_at<uint16_t, LAY::kOffBucket>(T, (uint32_t)(I >> LAY::kBucketShift) * 2u);
     for (;;) {
-        const uint64_t o1 = tab_at<uint64_t, kOffClsOff + 8>(T, c8);
-        const uint64_t o2 = tab_at<uint64_t, kOffClsOff + 16>(T, c8);
-        const uint64_t o3 = tab_at<uint64_t, kOffClsOff + 24>(T, c8);
+        const uint64_t o1 = tab_at<uint64_t, LAY::kOffClsOff + 8>(T, c8);
+        const uint64_t o2 = tab_at<uint64_t, LAY::kOffClsOff + 16>(T, c8);
+        const uint64_t o3 = tab_at<uint64_t, LAY::kOffClsOff + 24>(T, c8);
         const bool p1 = I >= o1, p2 = I >= o2, p3 = I >= o3;     // monotone: p3 implies p2 implies p1
         c8 += (p1 ? 8u : 0u) + (p2 ? 8u : 0u) + (p3 ? 8u : 0u);
         if (!wave_or(p3)) break;
     }
     ClassHit h;
     h.cid = c8 >> 3;
-    h.Ic = I - tab_at<uint64_t, kOffClsOff>(T, c8);
+    h.Ic = I - tab_at<uint64_t, LAY::kOffClsOff>(T, c8);
     return h;
 }
 
@@ -214,19 +221,19 @@ struct Front {
 };
 
 // BIG_GLOBAL: the Golay words and the inner-word planes are read from global memory instead of LDS
-// (GS_LDS: only the inner-word planes are; the kernel has copied the blob up to kOffInner);
+// (GS_LDS: only the inner-word planes are; the kernel has copied the blob up to LAY::kOffInner);
 // REC_GLOBAL: so is the class record
-template <bool BIG_GLOBAL = false, bool REC_GLOBAL = false, bool GS_LDS = false>
-LLVQ_HD Front decode_front(const TabPtrs& T, const ClassHit& hit) {
+template <bool BIG_GLOBAL = false, bool REC_GLOBAL = false, bool GS_LDS = false, class LAY = Lay13>
+LLVQ_HD Front decode_front(const TabPtrsOf<LAY>& T, const ClassHit& hit) {
     Front F;
-    const ClassRec R = REC_GLOBAL ? gtab_at<ClassRec, kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)))
-                                  : tab_at<ClassRec, kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)));
+    const ClassRec R = REC_GLOBAL ? gtab_at<ClassRec, LAY::kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)))
+                                  : tab_at<ClassRec, LAY::kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)));
     const uint32_t f0 = R.f0, f1 = R.f1;
     // r = Ic mod A, then B sign bits, then the permutation rank I''.  All quotients are exact: the operands are
     // integers below 2^48 held in doubles and the reciprocals are nudged upwards.
     const uint32_t acode = (f1 >> F1_ACODE) & 3u;
-    const double A = tab_at<double, kOffAtab>(T, acode * 16u);
-    const double invA = tab_at<double, kOffAtab + 8>(T, acode * 16u);
+    const double A = tab_at<double, LAY::kOffAtab>(T, acode * 16u);
+    const double invA = tab_at<double, LAY::kOffAtab + 8>(T, acode * 16u);
     // Ic < 2^48 as a double: its bits under the exponent of 2^52, minus 2^52 (two instructions instead of two
     // conversions, a scaling and an addition)
     const double x = __builtin_bit_cast(double, hit.Ic | 0x4330000000000000ull) - 4503599627370496.0;
@@ -241,47 +248,52 @@ LLVQ_HD Front decode_front(const TabPtrs& T, const ClassHit& hit) {
     F.d = (uint32_t)dd;
     const uint32_t rin = (uint32_t)((double)rem * (double)R.invP1);
     const uint32_t rho1 = rem - mul24(rin, R.P1);             // rem < 2^22
-    const uint32_t oc = (((f1 >> F1_GOFF) & 4095u) + r) * 4u, o0 = (R.tb0 + rin) * 4u, o1 = (R.tb1 + rho1) * 4u;
-    F.c = (BIG_GLOBAL && !GS_LDS) ? gtab_at<uint32_t, kOffGs>(T, oc) : tab_at<uint32_t, kOffGs>(T, oc);
-    F.e0 = BIG_GLOBAL ? gtab_at<uint32_t, kOffInner>(T, o0) : tab_at<uint32_t, kOffInner>(T, o0);
-    F.e1 = BIG_GLOBAL ? gtab_at<uint32_t, kOffInner>(T, o1) : tab_at<uint32_t, kOffInner>(T, o1);
-    const uint32_t j = tab_at<uint8_t, kOffGuess>(T, ((f1 >> F1_GROW) & 63u) * kGuessBuckets + (F.d >> ((f1 >> F1_GSHIFT) & 31u)));
+    const uint32_t tb0 = R.tb0 | (LAY::kWide ? ((f0 >> F0_TB0_HI) & 255u) << 16 : 0u);
+    const uint32_t oc = (((f1 >> F1_GOFF) & 4095u) + r) * 4u, o0 = (tb0 + rin) * 4u, o1 = (R.tb1 + rho1) * 4u;
+    F.c = (BIG_GLOBAL && !GS_LDS) ? gtab_at<uint32_t, LAY::kOffGs>(T, oc) : tab_at<uint32_t, LAY::kOffGs>(T, oc);
+    // (an F1_STEPS class needs its digit itself; the table entry that tb0 + rin then names is only read, never used)
+    F.e0 = BIG_GLOBAL ? gtab_at<uint32_t, LAY::kOffInner>(T, o0) : tab_at<uint32_t, LAY::kOffInner>(T, o0);
+    F.e1 = BIG_GLOBAL ? gtab_at<uint32_t, LAY::kOffInner>(T, o1) : tab_at<uint32_t, LAY::kOffInner>(T, o1);
+    if constexpr (LAY::kWide) { if ((f1 >> F1_STEPS) & 1u) F.e0 = rin; }
+    const uint32_t j = tab_at<uint8_t, LAY::kOffGuess>(T, ((f1 >> F1_GROW) & 63u) * kGuessBuckets + (F.d >> ((f1 >> F1_GSHIFT) & 31u)));
     F.sp_j = (uint32_t)(uint16_t)(R.sp + j) | (j << 16);
     F.cid = hit.cid; F.f0 = f0; F.f1 = f1;
     F.vt8_lo = R.vt8_lo; F.vt8_hi = R.vt8_hi; F.vti_lo = R.vti_lo; F.vti_hi = R.vti_hi;
-    F.rnorm = tab_at<float, kOffRnorm>(T, (f0 >> (F0_M - 2)) & 60u);
+    F.rnorm = tab_at<float, LAY::kOffRnorm>(T, (f0 >> (F0_M - 2)) & (LAY::kWide ? 124u : 60u));
     return F;
 }
 
 // App. A step 4, first part: the q-subset U of the outer domain's n slots with rank d, relative to the domain
 // (bit i = slot i of the domain); needs only the digits, not the Golay word
-LLVQ_HD uint32_t decode_subset(const TabPtrs& T, const Front& F) {
+template <class LAY>
+LLVQ_HD uint32_t decode_subset(const TabPtrsOf<LAY>& T, const Front& F) {
     uint32_t j = F.sp_j >> 16, eo = (F.sp_j & 0xFFFFu) * (uint32_t)sizeof(SplitEnt);
-    SplitEnt e = tab_at<SplitEnt, kOffSplit>(T, eo);
-    uint32_t nbase = tab_at<uint32_t, kOffSplit + sizeof(SplitEnt)>(T, eo);   // one past the last entry is never used
+    SplitEnt e = tab_at<SplitEnt, LAY::kOffSplit>(T, eo);
+    uint32_t nbase = tab_at<uint32_t, LAY::kOffSplit + sizeof(SplitEnt)>(T, eo);   // one past the last entry is never used
     const uint32_t jmax = (F.f1 >> F1_JMAX) & 15u;
     for (;;) {
         const bool more = j < jmax && F.d >= nbase;
         if (more) {
             j++;
             eo += (uint32_t)sizeof(SplitEnt);
-            e = tab_at<SplitEnt, kOffSplit>(T, eo);
-            nbase = tab_at<uint32_t, kOffSplit + sizeof(SplitEnt)>(T, eo);
+            e = tab_at<SplitEnt, LAY::kOffSplit>(T, eo);
+            nbase = tab_at<uint32_t, LAY::kOffSplit + sizeof(SplitEnt)>(T, eo);
         }
         if (!wave_or(more)) break;
     }
     const uint32_t dl = F.d - e.base;
     const uint32_t rk_hi = (uint32_t)((double)dl * (double)e.inv);
     const uint32_t rk_lo = dl - mul24(rk_hi, e.div);          // dl < C(24, 12) < 2^22
-    return (uint32_t)tab_at<uint16_t, kOffLut12>(T, (e.b12lo + rk_lo) * 2u) |
-           ((uint32_t)tab_at<uint16_t, kOffLut12>(T, (e.b12hi + rk_hi) * 2u) << 12);
+    return (uint32_t)tab_at<uint16_t, LAY::kOffLut12>(T, (e.b12lo + rk_lo) * 2u) |
+           ((uint32_t)tab_at<uint16_t, LAY::kOffLut12>(T, (e.b12hi + rk_hi) * 2u) << 12);
 }
 
 // App. A step 4, second part: placement and signs for the subset U.  w[0..3] receive the nibble words of the block.
-LLVQ_HD BlockInfo decode_place(const TabPtrs& T, const Front& F, uint32_t U, uint32_t (&w)[4]) {
+template <class LAY>
+LLVQ_HD BlockInfo decode_place(const TabPtrsOf<LAY>& T, const Front& F, uint32_t U, uint32_t (&w)[4]) {
     BlockInfo info;
     const uint32_t f0 = F.f0;
-    info.cid = F.cid; info.m = (f0 >> F0_M) & 15u;
+    info.cid = F.cid; info.m = (f0 >> F0_M) & (LAY::kWide ? 31u : 15u);
     info.rnorm = F.rnorm;
     info.vt8_lo = F.vt8_lo; info.vt8_hi = F.vt8_hi; info.vti_lo = F.vti_lo; info.vti_hi = F.vti_hi;
     {
@@ -318,7 +330,7 @@ LLVQ_HD BlockInfo decode_place(const TabPtrs& T, const Front& F, uint32_t U, uin
 #pragma unroll
         for (int k = 0; k < 4; k++) {
             const uint32_t omk = bfe6(om, 6 * k);
-            uks[k] = tab_at<uint8_t, kOffPdep6>(T, omk * kPdepPitch + bfe6(U, ou));
+            uks[k] = tab_at<uint8_t, LAY::kOffPdep6>(T, omk * kPdepPitch + bfe6(U, ou));
             ou += popc32(omk);
         }
 #pragma unroll
@@ -344,16 +356,37 @@ LLVQ_HD BlockInfo decode_place(const TabPtrs& T, const Front& F, uint32_t U, uin
             w[k] = lut3<0xEA>(gA0, dkeep, v);
         }
     }
+    if constexpr (LAY::kWide) {
+        const bool steps = (F.f1 >> F1_STEPS) & 1u;
+        if (wave_any(steps)) { if (steps) place_by_steps(T, F, w); }
+    }
     return info;
 }
 
+// Placement of the blocks whose class carries F1_STEPS (Lay19): the nibble words from the class's WideRec
+template <class LAY>
+LLVQ_HD void place_by_steps(const TabPtrsOf<LAY>& T, const Front& F, uint32_t (&w)[4]) {
+    const WideRec& R = *reinterpret_cast<const WideRec*>(T.gbase + LAY::kOffWideRec + F.cid * (uint32_t)sizeof(WideRec));
+    uint32_t n[4] = {0, 0, 0, 0};
+    // nibbles of chunk k that hold a 1 where `occ` is set
+    auto ones = [&](uint32_t occ, int k) { return tab_at<uint32_t, LAY::kOffSpread6>(T, 63u * 4u * kSpreadPitch + (bfe6(occ, 6 * k) << 2)) & 0x01011111u; };
+    const uint32_t neg = wide_place(reinterpret_cast<const uint32_t*>(T.gbase + LAY::kOffBinom), R, F.c, F.s, F.d, F.e0, 0u, [&](uint32_t occ, int code, int) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) n[k] |= ones(occ, k) * (uint32_t)code;
+    });
+#pragma unroll
+    for (int k = 0; k < 4; k++) w[k] = n[k] | (ones(neg, k) << 3);
+}
+
 // App. A step 4 in one call
-LLVQ_HD BlockInfo decode_back(const TabPtrs& T, const Front& F, uint32_t (&w)[4]) {
+template <class LAY>
+LLVQ_HD BlockInfo decode_back(const TabPtrsOf<LAY>& T, const Front& F, uint32_t (&w)[4]) {
     return decode_place(T, F, decode_subset(T, F), w);
 }
 
 // Decodes one index I (must be < npoints); w[0..3] receive the nibble words.
-LLVQ_HD BlockInfo decode_block(const TabPtrs& T, uint64_t I, uint32_t (&w)[4]) {
+template <class LAY>
+LLVQ_HD BlockInfo decode_block(const TabPtrsOf<LAY>& T, uint64_t I, uint32_t (&w)[4]) {
     return decode_back(T, decode_front(T, find_class(T, I)), w);
 }
 

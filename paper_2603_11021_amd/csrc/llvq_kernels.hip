@@ -29,6 +29,8 @@ namespace {
 using llvq::ClassRec;
 using llvq::TableLayout;
 using llvq::TabPtrs;
+using llvq::Lay13;
+using llvq::Lay19;
 
 constexpr int kThreads = 1024;
 
@@ -181,10 +183,10 @@ __device__ __forceinline__ void load_raw_near(const unsigned char* __restrict__ 
     r.g = *reinterpret_cast<const uint16_t*>(gain0 + 2u * k);
 }
 
-template <int FMT>
+template <int FMT, class LAY = Lay13>
 __device__ __forceinline__ void finish_block(const RawBlock& r, const Code& cd, uint64_t& I, uint16_t& g) {
     uint64_t v;
-    if constexpr (FMT == LLVQ_IDX_U64) v = ((uint64_t)r.a | ((uint64_t)r.b << 32)) & 0xFFFFFFFFFFFFull;
+    if constexpr (FMT == LLVQ_IDX_U64) v = ((uint64_t)r.a | ((uint64_t)r.b << 32)) & LAY::kWordMask;
     else if constexpr (FMT == LLVQ_IDX_U24) v = (uint64_t)(r.a | (r.b << 8) | (r.c << 16));
     else v = (uint64_t)r.a | ((uint64_t)r.c << 32);
     g = cd.lut ? cd.lut[min((uint32_t)(v >> cd.shape_bits), cd.lut_last)] : r.g;
@@ -233,17 +235,24 @@ struct BatchDeal {
     }
 };
 
+// Bytes of the blob that a kernel copies into LDS: everything, the small tables, or (Lay19) the small tables and the Golay
+// words, while class records and inner-word planes are read from global memory
+template <class LAY, bool BIG_GLOBAL>
+__device__ __forceinline__ uint32_t table_bytes_of(const TableLayout& lay) {
+    return LAY::kWide ? Lay19::kOffCls : BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes;
+}
+
 // ---- llvq_decode_i8 ---------------------------------------------------------------------------------
 // BIG_GLOBAL as in matmul_kernel below: with the two big tables in global memory the LDS part is 66 KB and two
 // workgroups share a compute unit (eight waves per SIMD, 64 registers per lane), which wins on launches that are not
 // dominated by their HBM traffic
-template <int FMT, bool BIG_GLOBAL, bool DYNAMIC>
+template <int FMT, bool BIG_GLOBAL, bool DYNAMIC, class LAY = Lay13>
 __global__ void __launch_bounds__(kThreads, BIG_GLOBAL ? 8 : 4) decode_i8_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
                                                              const void* __restrict__ idx, Code cd, size_t n,
                                                              uint32_t* __restrict__ out) {
-    BatchDeal<DYNAMIC> deal(n, BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes);
-    load_tables(blob, BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
+    BatchDeal<DYNAMIC> deal(n, table_bytes_of<LAY, BIG_GLOBAL>(lay));
+    load_tables(blob, table_bytes_of<LAY, BIG_GLOBAL>(lay));
+    const auto T = llvq::make_tab_ptrs<LAY>(lds_origin(), blob, lay);
     // The streamed arrays are addressed as scalar base + 32-bit lane offset (BatchDeal).  The next word is requested
     // (always: past the end the last one is read again) before this block is decoded.
     const uint32_t t = deal.t;
@@ -260,10 +269,10 @@ __global__ void __launch_bounds__(kThreads, BIG_GLOBAL ? 8 : 4) decode_i8_kernel
         const size_t base = deal.base;
         uint64_t I;
         uint16_t gdummy;
-        finish_block<FMT>(raw, cd, I, gdummy);
+        finish_block<FMT, LAY>(raw, cd, I, gdummy);
         const bool ok = I < T.npoints;
         uint32_t w[4], o[6];
-        const llvq::BlockInfo bi = llvq::decode_back(T, llvq::decode_front<BIG_GLOBAL>(T, llvq::find_class(T, ok ? I : 0)), w);
+        const llvq::BlockInfo bi = llvq::decode_back(T, llvq::decode_front<BIG_GLOBAL, LAY::kWide, LAY::kWide>(T, llvq::find_class(T, ok ? I : 0)), w);
         llvq::nibbles_to_i8(w, bi.vti_lo, bi.vti_hi, o);
         if (base + t < n) {
             uint2* dst = reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(out + 6 * base) + llvq::mul24(t, 24u));
@@ -291,13 +300,13 @@ __device__ __forceinline__ void chunk_fp8(uint32_t w, uint32_t vt_lo, uint32_t v
 }
 
 // ---- llvq_decode (shape-gain reconstruction) ------------------------------------------------------------
-template <int FMT, int OUT, bool BIG_GLOBAL>
+template <int FMT, int OUT, bool BIG_GLOBAL, class LAY = Lay13>
 __global__ void __launch_bounds__(kThreads, BIG_GLOBAL ? 8 : 4) dequant_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
                                                            const void* __restrict__ idx, const uint16_t* __restrict__ gain,
                                                            Code cd, size_t n, void* __restrict__ out) {
-    BatchDeal<!BIG_GLOBAL> deal(n, BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes);
-    load_tables(blob, BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
+    BatchDeal<!BIG_GLOBAL || LAY::kWide> deal(n, table_bytes_of<LAY, BIG_GLOBAL>(lay));
+    load_tables(blob, table_bytes_of<LAY, BIG_GLOBAL>(lay));
+    const auto T = llvq::make_tab_ptrs<LAY>(lds_origin(), blob, lay);
     // batches and addressing as in decode_i8_kernel; the next word and gain are requested before this block is decoded
     const uint32_t t = deal.t;
     auto request = [&](size_t base, RawBlock& r) {
@@ -315,10 +324,10 @@ __global__ void __launch_bounds__(kThreads, BIG_GLOBAL ? 8 : 4) dequant_kernel(c
         const bool live = base + t < n;
         uint64_t I;
         uint16_t gb;
-        finish_block<FMT>(raw, cd, I, gb);
+        finish_block<FMT, LAY>(raw, cd, I, gb);
         const bool ok = I < T.npoints;
         uint32_t w[4];
-        const llvq::BlockInfo bi = llvq::decode_back(T, llvq::decode_front<BIG_GLOBAL>(T, llvq::find_class(T, ok ? I : 0)), w);
+        const llvq::BlockInfo bi = llvq::decode_back(T, llvq::decode_front<BIG_GLOBAL, LAY::kWide, LAY::kWide>(T, llvq::find_class(T, ok ? I : 0)), w);
         const uint32_t vt_lo = bi.vt8_lo, vt_hi = bi.vt8_hi;
         const float g = __half2float(__ushort_as_half(gb));
         const float scale = ok ? g * bi.rnorm : 0.0f;
@@ -397,7 +406,7 @@ struct MatItems {
     int strip_end[kMaxItems];      // the same in strips of 128 rows (panel_kernel)
 };
 
-template <int FMT, typename X2, bool BIG_GLOBAL, bool DYNAMIC, bool MULTI = false>
+template <int FMT, typename X2, bool BIG_GLOBAL, bool DYNAMIC, bool MULTI = false, class LAY = Lay13>
 __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
                                                           const void* __restrict__ idx, const uint16_t* __restrict__ gain,
                                                           const uint32_t* __restrict__ x, int M, int N, int KB,
@@ -434,7 +443,7 @@ __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* _
         load_raw_near<FMT>(idx0, gain0, min((uint32_t)wave * 64u + (uint32_t)lane, nblk - 1), first_raw);
     }
     // one workgroup per compute unit: the tables are copied once per launch and workgroup
-    const uint32_t table_bytes = BIG_GLOBAL ? llvq::kOffInner : lay.blob_bytes;      // short launches: small tables + Golay words
+    const uint32_t table_bytes = LAY::kWide ? Lay19::kOffCls : BIG_GLOBAL ? Lay13::kOffInner : lay.blob_bytes;      // short launches: small tables + Golay words
     float* ysum = reinterpret_cast<float*>(g_lds + table_bytes);      // [kRowsPerPass][kMaxMChunk]
     // the first block number no wave has taken yet: the first two batches of a wave are fixed, after them it takes the
     // next free one, so waves on a SIMD that gets through its batches sooner end up with more of them
@@ -443,7 +452,7 @@ __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* _
     for (int i = threadIdx.x; i < kRowsPerPass * kMaxMChunk; i += kThreads) ysum[i] = 0.0f;
     if (DYNAMIC && threadIdx.x == 0) *next_free = 2 * kThreads;
     load_tables(blob, table_bytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
+    const auto T = llvq::make_tab_ptrs<LAY>(lds_origin(), blob, lay);
     const size_t xpitch = (size_t)KB * 12;                              // dwords per activation row
 
     // rows_per_pass <= kRowsPerPass keeps a pass below 2^24 blocks (block numbers inside a pass go through 24-bit multiplies)
@@ -480,11 +489,11 @@ __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* _
             auto fetch = [&](uint32_t base, Fetch& f) { load_raw_near<FMT>(idx0, gain0, place(base, f), f.raw); };
             auto front_of = [&](Fetch& f, bool& ok) {
                 uint64_t I;
-                finish_block<FMT>(f.raw, cd, I, f.g);
+                finish_block<FMT, LAY>(f.raw, cd, I, f.g);
                 ok = f.live && I < T.npoints;
                 // long launches (all tables in LDS) read the class record through the otherwise idle vector cache: the LDS
                 // gather pipe is as busy as the vector ALUs there, and three 16-byte gathers per block are a tenth of its load
-                return llvq::decode_front<BIG_GLOBAL, !BIG_GLOBAL, true>(T, llvq::find_class(T, ok ? I : 0));
+                return llvq::decode_front<BIG_GLOBAL, !BIG_GLOBAL || LAY::kWide, true>(T, llvq::find_class(T, ok ? I : 0));
             };
             uint32_t base = (uint32_t)wave * 64, next = base + kThreads, taken = 0;
             Fetch cur, nxt;
@@ -865,8 +874,25 @@ template <> struct Mma16<bf16x2_t> {
     }
 };
 
+// eight activations as fp32
+__device__ __forceinline__ void widen(u32x4 a, half2_t, float (&f)[8]) {
+    const half8_t h = __builtin_bit_cast(half8_t, a);
+#pragma unroll
+    for (int i = 0; i < 8; i++) f[i] = (float)h[i];
+}
+__device__ __forceinline__ void widen(u32x4 a, bf16x2_t, float (&f)[8]) {
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        f[2 * i] = __builtin_bit_cast(float, a[i] << 16);
+        f[2 * i + 1] = __builtin_bit_cast(float, a[i] & 0xFFFF0000u);
+    }
+}
+
 // TT: token tiles of 16 (M <= 16 TT); MULTI: the row tiles are those of up to four matrices that share x (`items`).
-template <int FMT, typename X2, int TT, bool MULTI = false>
+// LAY = Lay19 (TT = 1): these contexts promise exact products with fp32 sums at every M, so weights and activations enter
+// as fp32, channel t of the lane's block through its own v_mfma_f32_16x16x4_f32 (lane l supplies k = l / 16, its own block).
+// 24 of them take 768 of the about 1400 cycles that the decode keeps a SIMD's vector ALUs busy per step.
+template <int FMT, typename X2, int TT, bool MULTI = false, class LAY = Lay13>
 __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
                                                         const void* __restrict__ idx_in, const uint16_t* __restrict__ gain_in,
                                                         const uint32_t* __restrict__ x, int M, int N_in, int KB, Code cd,
@@ -874,9 +900,10 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
     constexpr int kWaves = kThreads / 64;
     constexpr int kPassTiles = kTilePassSlots / TT;                      // row tiles per pass
     constexpr int kTerms = Mma<X2>::kTerms;
-    load_tables(blob, llvq::kOffInner);          // the small tables and the Golay words; the inner-word planes stay in global memory
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
-    float* slots = reinterpret_cast<float*>(g_lds + llvq::kOffInner);      // [kWaves][kPassTiles][TT][256]
+    constexpr uint32_t kTableBytes = LAY::kWide ? Lay19::kOffCls : Lay13::kOffInner;
+    load_tables(blob, kTableBytes);          // the small tables and the Golay words; the inner-word planes stay in global memory
+    const auto T = llvq::make_tab_ptrs<LAY>(lds_origin(), blob, lay);
+    float* slots = reinterpret_cast<float*>(g_lds + kTableBytes);      // [kWaves][kPassTiles][TT][256]
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, kgrp = lane >> 4;
     const uint32_t S = ((uint32_t)KB + 3) / 4;                            // steps per row tile
@@ -931,9 +958,9 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
         };
         auto front_of = [&](const Blk& q, bool& ok, uint16_t& gb) {
             uint64_t I;
-            finish_block<FMT>(q.raw, cd, I, gb);
+            finish_block<FMT, LAY>(q.raw, cd, I, gb);
             ok = q.live && I < T.npoints;
-            return llvq::decode_front<true, false, true>(T, llvq::find_class(T, ok ? I : 0));
+            return llvq::decode_front<true, LAY::kWide, true>(T, llvq::find_class(T, ok ? I : 0));
         };
         Blk cur_blk, nxt_blk;
         llvq::Front F, Fn;
@@ -959,19 +986,29 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
             const llvq::BlockInfo bi = llvq::decode_back(T, F, w);
             const float scale = ok_cur ? __half2float(__ushort_as_half(g_cur)) * bi.rnorm : 0.0f;
             uint32_t wt[kTerms][12];
+            float wf[LAY::kWide ? 24 : 1];
 #pragma unroll
             for (int c = 0; c < 4; c++) {
                 uint32_t fe, fo, o[kTerms];
                 chunk_fp8(w[c], bi.vt8_lo, bi.vt8_hi, fe, fo);
-                Mma<X2>::weights(fe, false, scale, o);
+                if constexpr (LAY::kWide) {
+                    typedef float float2_t __attribute__((ext_vector_type(2)));
+                    const float2_t f0 = __builtin_amdgcn_cvt_pk_f32_fp8(fe, false), f1 = __builtin_amdgcn_cvt_pk_f32_fp8(fo, false),
+                                   f2 = __builtin_amdgcn_cvt_pk_f32_fp8(fe, true);
+                    const float f[6] = {f0[0], f0[1], f1[0], f1[1], f2[0], f2[1]};
 #pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
-                Mma<X2>::weights(fo, false, scale, o);
+                    for (int i = 0; i < 6; i++) wf[6 * c + i] = f[i] * scale;
+                } else {
+                    Mma<X2>::weights(fe, false, scale, o);
 #pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
-                Mma<X2>::weights(fe, true, scale, o);
+                    for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
+                    Mma<X2>::weights(fo, false, scale, o);
 #pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
+                    for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
+                    Mma<X2>::weights(fe, true, scale, o);
+#pragma unroll
+                    for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
+                }
             }
             if constexpr (kMore) Fn = front_of(nxt_blk, ok_nxt, g_nxt);
             // one channel group j at a time through the wave's buffer: LDS operations of a wave execute in order, so
@@ -984,11 +1021,18 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
                 for (int t = 0; t < TT; t++) *reinterpret_cast<u32x4*>(stage + t * 256 + st_unit) = xl[t][j];
 #pragma unroll
                 for (int t = 0; t < TT; t++) xa[t] = *reinterpret_cast<const u32x4*>(stage + t * 256 + rd_unit);
+                if constexpr (LAY::kWide) {
+                    float xf[8];
+                    widen(xa[0], X2{}, xf);
 #pragma unroll
-                for (int r = 0; r < kTerms; r++) {
-                    const u32x4 bw = {wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]};
+                    for (int i = 0; i < 8; i++) acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xf[i], wf[8 * j + i], acc[0], 0, 0, 0);
+                } else {
 #pragma unroll
-                    for (int t = 0; t < TT; t++) acc[t] = Mma16<X2>::mma(xa[t], bw, acc[t]);
+                    for (int r = 0; r < kTerms; r++) {
+                        const u32x4 bw = {wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]};
+#pragma unroll
+                        for (int t = 0; t < TT; t++) acc[t] = Mma16<X2>::mma(xa[t], bw, acc[t]);
+                    }
                 }
             }
             // leaving this row tile (or the pass): park the accumulated tile in this wave's slot and start from zero
@@ -1546,78 +1590,6 @@ __global__ void __launch_bounds__(kValidateStaticThreads) validate_sum_kernel(co
 
 }  // namespace
 
-// ---- contexts with m_max > 13: the dequantiser of llvq_wide.h, one thread per block ----------------------------------
-namespace {
-
-constexpr uint64_t kWideIndexMask = (1ull << 56) - 1;      // 64-bit words of these contexts carry the index in their low 56 bits
-
-template <int FMT>
-__device__ __forceinline__ uint64_t wide_index(const void* __restrict__ idx, size_t k) {
-    return load_index<FMT>(idx, k) & kWideIndexMask;
-}
-
-template <int FMT>
-__global__ void __launch_bounds__(256) wide_decode_i8_kernel(llvq::WidePtrs T, const void* __restrict__ idx, size_t n, uint2* __restrict__ out) {
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-        const uint64_t I = wide_index<FMT>(idx, k);
-        uint32_t o[6] = {0, 0, 0, 0, 0, 0};
-        float rnorm;
-        if (I < T.npoints) llvq::wide_decode(T, I, o, rnorm);
-        out[3 * k] = make_uint2(o[0], o[1]);
-        out[3 * k + 1] = make_uint2(o[2], o[3]);
-        out[3 * k + 2] = make_uint2(o[4], o[5]);
-    }
-}
-
-__device__ __forceinline__ float wide_coord(const uint32_t (&o)[6], int i) { return (float)(int8_t)(o[i >> 2] >> (8 * (i & 3))); }
-
-template <int FMT, int OUT>
-__global__ void __launch_bounds__(256) wide_dequant_kernel(llvq::WidePtrs T, const void* __restrict__ idx, const uint16_t* __restrict__ gain,
-                                                           size_t n, void* __restrict__ out) {
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-        const uint64_t I = wide_index<FMT>(idx, k);
-        uint32_t o[6] = {0, 0, 0, 0, 0, 0};
-        float rnorm = 0.0f;
-        if (I < T.npoints) llvq::wide_decode(T, I, o, rnorm);
-        const float scale = __half2float(__ushort_as_half(gain[k])) * rnorm;
-#pragma unroll
-        for (int i = 0; i < 24; i++) {
-            const float v = wide_coord(o, i) * scale;
-            if constexpr (OUT == LLVQ_F32) reinterpret_cast<float*>(out)[24 * k + i] = v;
-            else if constexpr (OUT == LLVQ_F16) reinterpret_cast<__half*>(out)[24 * k + i] = __float2half_rn(v);
-            else reinterpret_cast<__bf16*>(out)[24 * k + i] = (__bf16)v;
-        }
-    }
-}
-
-// y must be zero when this kernel starts: every block adds its M partial dot products to y with atomic adds
-template <int FMT, bool BF16>
-__global__ void __launch_bounds__(256) wide_matmul_kernel(llvq::WidePtrs T, const uint16_t* __restrict__ x, int M, const void* __restrict__ idx,
-                                                          const uint16_t* __restrict__ gain, int N, int KB, float* __restrict__ y) {
-    const size_t n = (size_t)N * KB;
-    for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
-        const uint64_t I = wide_index<FMT>(idx, k);
-        if (I >= T.npoints) continue;                                   // the zero block contributes nothing
-        uint32_t o[6];
-        float rnorm;
-        llvq::wide_decode(T, I, o, rnorm);
-        const float scale = __half2float(__ushort_as_half(gain[k])) * rnorm;
-        const size_t row = k / KB, b = k - row * KB;
-        for (int m = 0; m < M; m++) {
-            const uint16_t* xp = x + ((size_t)m * KB + b) * 24;
-            float acc = 0.0f;
-#pragma unroll
-            for (int i = 0; i < 24; i++) {
-                const float xv = BF16 ? __builtin_bit_cast(float, (uint32_t)xp[i] << 16) : __half2float(__ushort_as_half(xp[i]));
-                acc = fmaf(wide_coord(o, i), xv, acc);
-            }
-            atomicAdd(y + (size_t)m * N + row, acc * scale);
-        }
-    }
-}
-
-}  // namespace
-
 // ---- C ABI -------------------------------------------------------------------------------------------
 struct llvq_ctx {
     int device = 0;
@@ -1625,7 +1597,7 @@ struct llvq_ctx {
     int num_cu = 0;
     llvq::TableLayout lay{};
     llvq::EncLayout enc_lay{};
-    uint64_t shell_off[16] = {};            // first index of each shell
+    uint64_t shell_off[24] = {};            // first index of each shell
     unsigned char* d_blob = nullptr;
     unsigned char* d_enc_blob = nullptr;
     llvq::SearchLayout search_lay{};
@@ -1636,14 +1608,7 @@ struct llvq_ctx {
     unsigned long long* d_counter = nullptr;
     unsigned int* d_validate_scratch = nullptr;   // address of g_validate_scratch on this context's device (not owned)
     uint64_t index_mask = 0xFFFFFFFFFFFFull;      // bits of a stored word that hold the index (56 for 64-bit words of wide contexts)
-    // contexts with m_max > 13: the tables of llvq_wide.h in global memory; the table-driven kernels are not available
-    bool wide = false;
-    llvq::WideRec* d_wrecs = nullptr;
-    uint64_t* d_wcls_off = nullptr;
-    uint32_t* d_wgs = nullptr;
-    uint32_t* d_wbinom = nullptr;
-    uint64_t wide_shell_off[24] = {};
-    llvq::WidePtrs wide_ptrs() const { return llvq::WidePtrs{d_wrecs, d_wcls_off, d_wgs, d_wbinom, lay.ncls, lay.npoints}; }
+    bool wide = false;                            // m_max > 13: d_blob is in layout Lay19, dequantiser calls only
     rocblas_handle blas = nullptr;          // created at the first llvq_matmul_ws call that takes the two-step path
     // text of the last failure: written under the lock (calls may fail on several threads at once), read without it
     std::mutex err_mu;
@@ -1751,7 +1716,7 @@ static int launch_dequant(llvq_ctx* ctx, const void* d_idx, const void* d_gain, 
 }
 
 // MULTI: N is the number of rows of all matrices of `items` together; d_idx, d_gain and d_y are not used
-template <int FMT, typename X2, bool MULTI = false>
+template <int FMT, typename X2, bool MULTI = false, class LAY = Lay13>
 static int launch_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
                          const MatItems& items = MatItems{}) {
     // one persistent workgroup per compute unit (the tables fill its LDS), rows split evenly among them
@@ -1762,17 +1727,17 @@ static int launch_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_id
     // from 64 batches of 64 blocks per compute unit on (four per wave; measured on Llama-3-8B and 70B shapes), copying
     // all tables into LDS pays, and so does dealing the batches to the waves as they finish
     const bool short_launch = (size_t)N * (size_t)KB / 64 < (size_t)ctx->num_cu * 64;
-    const size_t lds = (short_launch ? llvq::kOffInner : ctx->lay.blob_bytes) + (size_t)kRowsPerPass * kMaxMChunk * sizeof(float) + 16;   // row sums + batch counter
+    const size_t lds = (LAY::kWide ? Lay19::kOffCls : short_launch ? Lay13::kOffInner : ctx->lay.blob_bytes) + (size_t)kRowsPerPass * kMaxMChunk * sizeof(float) + 16;   // row sums + batch counter
     const int rows_pass = std::max(1, std::min(kRowsPerPass, ((1 << 24) - 1) / KB));       // KB < 2^24 (checked by the caller)
 #define LLVQ_LAUNCH_MATMUL(BG, DYN)                                                                                         \
     do {                                                                                                                    \
-        if (int rc = set_lds<matmul_kernel<FMT, X2, BG, DYN, MULTI>>(ctx, lds)) return rc;                                  \
-        hipLaunchKernelGGL((matmul_kernel<FMT, X2, BG, DYN, MULTI>), dim3(grid), dim3(kThreads), lds, st, ctx->d_blob,      \
+        if (int rc = set_lds<matmul_kernel<FMT, X2, BG, DYN, MULTI, LAY>>(ctx, lds)) return rc;                                  \
+        hipLaunchKernelGGL((matmul_kernel<FMT, X2, BG, DYN, MULTI, LAY>), dim3(grid), dim3(kThreads), lds, st, ctx->d_blob,      \
                            ctx->lay, d_idx, reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), \
                            M, N, KB, cd, kb_magic, rows, rows_pass, items, d_y);                                             \
     } while (0)
     if (short_launch) LLVQ_LAUNCH_MATMUL(true, false);
-    else LLVQ_LAUNCH_MATMUL(false, true);
+    else LLVQ_LAUNCH_MATMUL(LAY::kWide, true);
 #undef LLVQ_LAUNCH_MATMUL
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "matmul launch");
@@ -1799,7 +1764,7 @@ static int launch_mfma_cfg(llvq_ctx* ctx, const void* d_x, int M, const void* d_
 
 constexpr int kTileMaxM = 32;       // up to this many activation rows the batched-decode kernel with row tiles per workgroup is used
 
-template <int FMT, typename X2, int TT, bool MULTI = false>
+template <int FMT, typename X2, int TT, bool MULTI = false, class LAY = Lay13>
 static int launch_tile(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
                        const MatItems& items = MatItems{}) {
     // persistent workgroups, whole row tiles split evenly among them
@@ -1807,9 +1772,9 @@ static int launch_tile(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx,
     int grid = std::min(ctx->num_cu, n_tiles);
     const int per_wg = (n_tiles + grid - 1) / grid;
     grid = (n_tiles + per_wg - 1) / per_wg;
-    const size_t lds = llvq::kOffInner + (size_t)(kThreads / 64) * kTilePassSlots * 256 * sizeof(float);
-    if (int rc = set_lds<tile_kernel<FMT, X2, TT, MULTI>>(ctx, lds)) return rc;
-    hipLaunchKernelGGL((tile_kernel<FMT, X2, TT, MULTI>), dim3(grid), dim3(kThreads), lds, st, ctx->d_blob, ctx->lay, d_idx,
+    const size_t lds = (LAY::kWide ? Lay19::kOffCls : Lay13::kOffInner) + (size_t)(kThreads / 64) * kTilePassSlots * 256 * sizeof(float);
+    if (int rc = set_lds<tile_kernel<FMT, X2, TT, MULTI, LAY>>(ctx, lds)) return rc;
+    hipLaunchKernelGGL((tile_kernel<FMT, X2, TT, MULTI, LAY>), dim3(grid), dim3(kThreads), lds, st, ctx->d_blob, ctx->lay, d_idx,
                        reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, n_tiles, per_wg, items, d_y);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "tile matmul launch");
@@ -2102,42 +2067,45 @@ bool plain_fmt(int fmt) { return fmt == LLVQ_IDX_U48 || fmt == LLVQ_IDX_U64 || f
 
 }  // namespace
 
+// contexts with m_max > 13: the same kernels over the tables of Lay19
 namespace {
 
-int wide_grid(const llvq_ctx* ctx, size_t n) { return (int)std::max<size_t>(1, std::min<size_t>((n + 255) / 256, (size_t)ctx->num_cu * 16)); }
-
-template <int FMT>
-int wide_launch_decode_i8(llvq_ctx* ctx, const void* d_idx, size_t n, int8_t* d_out, hipStream_t st) {
-    hipLaunchKernelGGL(wide_decode_i8_kernel<FMT>, dim3(wide_grid(ctx, n)), dim3(256), 0, st, ctx->wide_ptrs(), d_idx, n, reinterpret_cast<uint2*>(d_out));
-    return 0;
-}
-
-template <int FMT>
-int wide_launch_dequant(llvq_ctx* ctx, const void* d_idx, const void* d_gain, size_t n, void* d_out, int out_dtype, hipStream_t st) {
-    const uint16_t* g = reinterpret_cast<const uint16_t*>(d_gain);
-    const dim3 grid(wide_grid(ctx, n));
-    if (out_dtype == LLVQ_F16) hipLaunchKernelGGL((wide_dequant_kernel<FMT, LLVQ_F16>), grid, dim3(256), 0, st, ctx->wide_ptrs(), d_idx, g, n, d_out);
-    else if (out_dtype == LLVQ_BF16) hipLaunchKernelGGL((wide_dequant_kernel<FMT, LLVQ_BF16>), grid, dim3(256), 0, st, ctx->wide_ptrs(), d_idx, g, n, d_out);
-    else hipLaunchKernelGGL((wide_dequant_kernel<FMT, LLVQ_F32>), grid, dim3(256), 0, st, ctx->wide_ptrs(), d_idx, g, n, d_out);
-    return 0;
-}
-
-template <int FMT>
-int wide_launch_matmul(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, const void* d_idx, const void* d_gain, int N, int KB, float* d_y, hipStream_t st) {
-    const size_t ny = (size_t)M * N, n = (size_t)N * KB;
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 4096)), dim3(256), 0, st, d_y, ny, 0.0f);
-    const uint16_t* x = reinterpret_cast<const uint16_t*>(d_x);
-    const uint16_t* g = reinterpret_cast<const uint16_t*>(d_gain);
-    if (x_dtype == LLVQ_BF16) hipLaunchKernelGGL((wide_matmul_kernel<FMT, true>), dim3(wide_grid(ctx, n)), dim3(256), 0, st, ctx->wide_ptrs(), x, M, d_idx, g, N, KB, d_y);
-    else hipLaunchKernelGGL((wide_matmul_kernel<FMT, false>), dim3(wide_grid(ctx, n)), dim3(256), 0, st, ctx->wide_ptrs(), x, M, d_idx, g, N, KB, d_y);
-    return 0;
-}
-
 constexpr int kWideMaxBatch = 16;      // activation rows the wide contexts' product accepts
+
+Code wide_code(int fmt) {
+    Code cd = plain_code(fmt);
+    if (fmt == LLVQ_IDX_U64) cd.mask = Lay19::kWordMask;      // these words carry the index in their low 56 bits
+    return cd;
+}
 
 int wide_finish(llvq_ctx* ctx, const char* what) {
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, what);
+}
+
+// 78 KB of tables: two workgroups share a compute unit
+constexpr size_t kWideBulkLds = Lay19::kOffCls + 16;           // + the batch counter
+
+template <int FMT>
+int wide_launch_decode_i8(llvq_ctx* ctx, const void* d_idx, size_t n, int8_t* d_out, hipStream_t st) {
+    if (int rc = set_lds<decode_i8_kernel<FMT, true, true, Lay19>>(ctx, kWideBulkLds)) return rc;
+    hipLaunchKernelGGL((decode_i8_kernel<FMT, true, true, Lay19>), dim3(grid_for(ctx, n, 2)), dim3(kThreads), kWideBulkLds, st, ctx->d_blob, ctx->lay,
+                       d_idx, wide_code(FMT), n, reinterpret_cast<uint32_t*>(d_out));
+    return wide_finish(ctx, "decode_i8 launch");
+}
+
+template <int FMT, int OUT>
+int wide_launch_dequant(llvq_ctx* ctx, const void* d_idx, const void* d_gain, size_t n, void* d_out, hipStream_t st) {
+    if (int rc = set_lds<dequant_kernel<FMT, OUT, true, Lay19>>(ctx, kWideBulkLds)) return rc;
+    hipLaunchKernelGGL((dequant_kernel<FMT, OUT, true, Lay19>), dim3(grid_for(ctx, n, 2)), dim3(kThreads), kWideBulkLds, st, ctx->d_blob, ctx->lay,
+                       d_idx, reinterpret_cast<const uint16_t*>(d_gain), wide_code(FMT), n, d_out);
+    return wide_finish(ctx, "dequant launch");
+}
+
+template <int FMT, typename X2>
+int wide_launch_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, int N, int KB, float* d_y, hipStream_t st) {
+    if (M < kMfmaMinM) return launch_matmul<FMT, X2, false, Lay19>(ctx, d_x, M, d_idx, d_gain, wide_code(FMT), N, KB, d_y, st);
+    return launch_tile<FMT, X2, 1, false, Lay19>(ctx, d_x, M, d_idx, d_gain, wide_code(FMT), N, KB, d_y, st);
 }
 
 }  // namespace
@@ -2157,25 +2125,21 @@ const char* llvq_strerror(int rc) {
 
 const char* llvq_last_hip_error(const llvq_ctx* ctx) { return ctx ? ctx->err : ""; }
 
-// a context for 14 <= m_max <= 19: the tables of llvq_wide.h in global memory
+// a context for 14 <= m_max <= 19: the decoder's tables in layout Lay19
 static int create_wide(llvq_ctx** out, int m_max, int device) {
     llvq::WideTables tabs;
     if (!llvq::build_wide_tables(m_max, tabs)) return LLVQ_EINVAL;
     llvq_ctx* ctx = new (std::nothrow) llvq_ctx;
     if (!ctx) return LLVQ_EINVAL;
     ctx->device = device; ctx->m_max = m_max; ctx->wide = true;
-    ctx->lay = llvq::TableLayout{};
-    ctx->lay.ncls = tabs.lay.ncls; ctx->lay.npoints = tabs.lay.npoints;
-    ctx->index_mask = kWideIndexMask;
-    for (int m = 0; m < 24; m++) ctx->wide_shell_off[m] = tabs.shell_off[m];
+    ctx->lay = tabs.tab;
+    ctx->index_mask = Lay19::kWordMask;
+    for (int m = 0; m < 24; m++) ctx->shell_off[m] = tabs.shell_off[m];
     hipDeviceProp_t prop;
-    auto upload = [&](auto** dst, const auto& v) {
-        const size_t bytes = v.size() * sizeof(v[0]);
-        return hipMalloc(reinterpret_cast<void**>(dst), bytes) == hipSuccess && hipMemcpy(*dst, v.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
-    };
     if (hipSetDevice(device) != hipSuccess || hipGetDeviceProperties(&prop, device) != hipSuccess ||
-        !upload(&ctx->d_wrecs, tabs.recs) || !upload(&ctx->d_wcls_off, tabs.cls_off) || !upload(&ctx->d_wgs, tabs.gs) ||
-        !upload(&ctx->d_wbinom, tabs.binom) || hipMalloc(&ctx->d_counter, sizeof(unsigned long long)) != hipSuccess ||
+        hipMalloc(&ctx->d_blob, tabs.blob.size()) != hipSuccess ||
+        hipMemcpy(ctx->d_blob, tabs.blob.data(), tabs.blob.size(), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMalloc(&ctx->d_counter, sizeof(unsigned long long)) != hipSuccess ||
         hipGetSymbolAddress(reinterpret_cast<void**>(&ctx->d_validate_scratch), HIP_SYMBOL(g_validate_scratch)) != hipSuccess) {
         llvq_destroy(ctx);
         return LLVQ_EHIP;
@@ -2249,10 +2213,6 @@ void llvq_destroy(llvq_ctx* ctx) {
     if (ctx->d_tile_a) (void)hipFree(ctx->d_tile_a);
     if (ctx->d_tile_scale) (void)hipFree(ctx->d_tile_scale);
     if (ctx->blas) (void)rocblas_destroy_handle(ctx->blas);
-    if (ctx->d_wrecs) (void)hipFree(ctx->d_wrecs);
-    if (ctx->d_wcls_off) (void)hipFree(ctx->d_wcls_off);
-    if (ctx->d_wgs) (void)hipFree(ctx->d_wgs);
-    if (ctx->d_wbinom) (void)hipFree(ctx->d_wbinom);
     delete ctx;
 }
 
@@ -2262,7 +2222,7 @@ int llvq_num_classes(const llvq_ctx* ctx) { return ctx ? (int)ctx->lay.ncls : 0;
 uint64_t llvq_shell_offset(const llvq_ctx* ctx, int m) {
     if (!ctx || m < 2) return 0;
     if (m > ctx->m_max) return ctx->lay.npoints;
-    return ctx->wide ? ctx->wide_shell_off[m] : ctx->shell_off[m];
+    return ctx->shell_off[m];
 }
 
 
@@ -2273,8 +2233,7 @@ int llvq_decode_i8(llvq_ctx* ctx, const void* d_idx, int fmt, size_t n_blocks, i
         if (!d_out) return LLVQ_EINVAL;
         if (int rc = check_idx(d_idx, fmt)) return rc;
         if (!aligned(d_out, 8)) return LLVQ_EALIGN;
-        LLVQ_BY_FMT(fmt, wide_launch_decode_i8<F>(ctx, d_idx, n_blocks, d_out, reinterpret_cast<hipStream_t>(stream)));
-        return wide_finish(ctx, "decode_i8 launch");
+        return LLVQ_BY_FMT(fmt, wide_launch_decode_i8<F>(ctx, d_idx, n_blocks, d_out, reinterpret_cast<hipStream_t>(stream)));
     }
     return decode_i8_impl(ctx, d_idx, fmt, plain_code(fmt), n_blocks, d_out, stream);
 }
@@ -2288,8 +2247,10 @@ int llvq_decode(llvq_ctx* ctx, const void* d_idx, int fmt, const void* d_gain, s
         if (!d_out) return LLVQ_EINVAL;
         if (int rc = check_idx(d_idx, fmt)) return rc;
         if (!aligned(d_out, 16) || !aligned(d_gain, 2)) return LLVQ_EALIGN;
-        LLVQ_BY_FMT(fmt, wide_launch_dequant<F>(ctx, d_idx, d_gain, n_blocks, d_out, out_dtype, reinterpret_cast<hipStream_t>(stream)));
-        return wide_finish(ctx, "dequant launch");
+        hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+        if (out_dtype == LLVQ_F16) return LLVQ_BY_FMT(fmt, (wide_launch_dequant<F, LLVQ_F16>(ctx, d_idx, d_gain, n_blocks, d_out, st)));
+        if (out_dtype == LLVQ_BF16) return LLVQ_BY_FMT(fmt, (wide_launch_dequant<F, LLVQ_BF16>(ctx, d_idx, d_gain, n_blocks, d_out, st)));
+        return LLVQ_BY_FMT(fmt, (wide_launch_dequant<F, LLVQ_F32>(ctx, d_idx, d_gain, n_blocks, d_out, st)));
     }
     return decode_impl(ctx, d_idx, fmt, d_gain, plain_code(fmt), n_blocks, d_out, out_dtype, stream);
 }
@@ -2303,8 +2264,9 @@ int llvq_matmul(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, const void* 
         if (M > kWideMaxBatch) return LLVQ_ENOTIMPL;
         if (int rc = check_idx(d_idx, fmt)) return rc;
         if (!aligned(d_x, 16) || !aligned(d_gain, 2) || !aligned(d_y, 4)) return LLVQ_EALIGN;
-        LLVQ_BY_FMT(fmt, wide_launch_matmul<F>(ctx, d_x, x_dtype, M, d_idx, d_gain, N, KB, d_y, reinterpret_cast<hipStream_t>(stream)));
-        return wide_finish(ctx, "matmul launch");
+        hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+        if (x_dtype == LLVQ_F16) return LLVQ_BY_FMT(fmt, (wide_launch_matmul<F, half2_t>(ctx, d_x, M, d_idx, d_gain, N, KB, d_y, st)));
+        return LLVQ_BY_FMT(fmt, (wide_launch_matmul<F, bf16x2_t>(ctx, d_x, M, d_idx, d_gain, N, KB, d_y, st)));
     }
     return matmul_impl(ctx, d_x, x_dtype, M, d_idx, fmt, d_gain, plain_code(fmt), N, KB, d_y, stream);
 }

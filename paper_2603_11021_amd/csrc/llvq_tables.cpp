@@ -38,14 +38,6 @@ std::vector<uint32_t> masks_in_colex_order(int nbits, int p) {
     return out;
 }
 
-// deposit the low bits of `src` into the set bits of `mask`, lowest first
-uint32_t deposit(uint32_t src, uint32_t mask) {
-    uint32_t out = 0;
-    for (int pos = 0, k = 0; pos < 32; pos++)
-        if ((mask >> pos) & 1u) { if ((src >> k) & 1u) out |= 1u << pos; k++; }
-    return out;
-}
-
 struct Leader {
     std::vector<int> val, cnt;   // distinct absolute values descending, multiplicities
     int m = 0;
@@ -96,17 +88,6 @@ uint8_t fp8_e4m3(int v) {   // small non-negative integers are exact in e4m3 (bi
     int frac = ((v << 3) >> e) & 7;   // three mantissa bits below the leading one (v <= 15)
     return (uint8_t)(((e + 7) << 3) | frac);
 }
-
-template <typename T>
-uint32_t append(std::vector<unsigned char>& blob, const std::vector<T>& v) {
-    while (blob.size() % 16) blob.push_back(0);
-    uint32_t off = (uint32_t)blob.size();
-    const unsigned char* p = reinterpret_cast<const unsigned char*>(v.data());
-    blob.insert(blob.end(), p, p + v.size() * sizeof(T));
-    return off;
-}
-
-
 
 // The 4096 Golay words in (weight, message) order and every class of shells 2..m_max in index order (paper Sec. 2.3-2.5,
 // 3.2): shell_off[m] receives N(m-1) for m <= m_max, `total` N(m_max).
@@ -214,6 +195,216 @@ ClassShape shape_of(const Leader& L) {
     return S;
 }
 
+// The tables that do not depend on the layout: lut12, inner-word planes, subset ranking and its guess table, and the class
+// records that refer to them.
+struct DecoderParts {
+    std::vector<uint16_t> lut12;
+    int b12[14];
+    std::vector<uint32_t> inner;
+    std::vector<SplitEnt> split;
+    std::vector<uint8_t> guess;
+    struct SplitInfo { uint16_t sp; int shift, jmax, row; };
+
+    DecoderParts() {
+        // lut12: colex rank -> mask, grouped by popcount
+        for (int p = 0; p <= 12; p++) {
+            b12[p] = (int)lut12.size();
+            for (uint32_t mk : masks_in_colex_order(12, p)) lut12.push_back((uint16_t)mk);
+        }
+        b12[13] = (int)lut12.size();
+        inner_table(std::vector<int>{}, 0);          // entry 0 is all zero: the table of an empty word
+    }
+
+    // First entry of the inner-word table of a pattern, built on first use; -1: two 16-bit planes cannot hold it.
+    // Pattern = multiplicities of the values of the word in descending value order, over q slots.
+    // Entry rho: mixed radix, digit of the largest value least significant, each digit the colex rank of
+    // the subset that value occupies among the slots still free; the smallest value takes the rest.
+    // Planes: bit k of plane a/b = bit 0/1 of (symbol index + sym_base) of the value on slot k.
+    int64_t inner_table(const std::vector<int>& cnt, int sym_base) {
+        auto key = std::make_pair(cnt, sym_base);
+        auto it = inner_base_.find(key);
+        if (it != inner_base_.end()) return it->second;
+        int q = 0;
+        for (int c : cnt) q += c;
+        if (q > 16 || (int)cnt.size() + sym_base > 4) return -1;
+        uint64_t P = multinomial(cnt);
+        uint32_t base = (uint32_t)inner.size();
+        std::vector<std::vector<uint32_t>> cm(cnt.size());
+        for (size_t i = 0; i < cnt.size(); i++) cm[i] = masks_in_colex_order(q, cnt[i]);   // over-long lists are harmless
+        for (uint64_t rho = 0; rho < P; rho++) {
+            uint64_t r = rho;
+            uint32_t freemask = (1u << q) - 1u, pa = 0, pb = 0;
+            for (size_t i = 0; i < cnt.size(); i++) {
+                uint32_t occ;
+                int nfree = popcnt(freemask);
+                if (i + 1 == cnt.size()) occ = freemask;
+                else {
+                    uint64_t radix = g_binom[nfree][cnt[i]];
+                    occ = wide_deposit(cm[i][r % radix], freemask);
+                    r /= radix;
+                }
+                int sym = (int)i + sym_base;
+                if (sym & 1) pa |= occ;
+                if (sym & 2) pb |= occ;
+                freemask &= ~occ;
+            }
+            inner.push_back(pa | (pb << 16));
+        }
+        inner_base_[key] = base;
+        return base;
+    }
+
+    // q-subsets of n slots, slots 0..11 low, 12..n-1 high; order: number j of high slots, then colex rank
+    // of the high part, then colex rank of the low part.
+    SplitInfo split_table(int n, int q) {
+        auto key = std::make_pair(n, q);
+        auto it = split_of_.find(key);
+        if (it != split_of_.end()) return it->second;
+        int nl = std::min(n, 12), nh = n - nl;
+        int jmin = std::max(0, q - nl), jmax = std::min(q, nh);
+        SplitInfo si;
+        si.sp = (uint16_t)((int)split.size() - jmin);      // entry of j is split[sp + j]
+        si.jmax = jmax;
+        si.row = (int)(guess.size() / kGuessBuckets);
+        std::vector<uint64_t> bases;
+        uint64_t base = 0;
+        for (int j = jmin; j <= jmax; j++) {
+            SplitEnt e{};
+            uint64_t div = g_binom[nl][q - j];
+            e.base = (uint32_t)base;
+            e.div = (uint16_t)div;
+            e.inv = reciprocal_up(div);
+            e.b12lo = (uint16_t)b12[q - j];
+            e.b12hi = (uint16_t)b12[j];
+            split.push_back(e);
+            bases.push_back(base);
+            base += g_binom[nh][j] * div;
+        }
+        uint64_t total = base;                              // C(n, q)
+        int shift = 0;
+        while (((total - 1) >> shift) >= kGuessBuckets) shift++;
+        si.shift = shift;
+        for (uint32_t b = 0; b < kGuessBuckets; b++) {
+            uint64_t d0 = (uint64_t)b << shift;
+            int j = jmin;
+            while (j < jmax && bases[j + 1 - jmin] <= d0) j++;
+            guess.push_back((uint8_t)j);
+        }
+        split_of_[key] = si;
+        return si;
+    }
+
+    static float reciprocal_up(uint64_t div) {
+        float inv = 1.0f / (float)div;
+        while ((double)inv * (double)div < 1.0) inv = std::nextafterf(inv, 2.0f);
+        return inv;
+    }
+
+    // Everything of a class record that the two layouts have in common: digits, values, subset ranking.  tb0 and tb1 are
+    // the first inner-word entries of the outer domain and of the direct F1 word.  Value codes: outer domain = all positions
+    // (odd, w = 24) and classes placed step by step: code 0 = outside value, first_code + i = i-th minority value; otherwise
+    // 0 = zero, 1 + i = i-th nonzero F0 value, 4 + i = i-th F1 value.
+    ClassRec record(const Leader& L, const ClassShape& S, const int* woff, uint32_t tb0, uint32_t tb1, int first_code, SplitInfo& si) {
+        ClassRec R{};
+        const uint64_t Pin = multinomial(S.mc), P1 = S.f1direct ? multinomial(S.dc) : 1, PP = P1 * Pin;
+        si = split_table(S.n, S.q);
+        R.PP = (uint32_t)PP;
+        R.invPP = (1.0 / (double)PP) * (1.0 + std::ldexp(1.0, -50));
+        R.invP1 = reciprocal_up(P1);
+        R.P1 = (uint16_t)P1; R.tb0 = (uint16_t)tb0; R.tb1 = (uint16_t)tb1; R.sp = si.sp;
+        const int acode = L.A == 1 ? 0 : (L.A == 759 ? 1 : (L.A == 2576 ? 2 : 3));
+        const int wm1 = (!L.odd && L.w > 0) ? L.w - 1 : 0;
+        R.f0 = (uint32_t)(L.odd ? 1 : 0) << F0_ODD | (uint32_t)(S.f1direct ? 1 : 0) << F0_F1DIRECT |
+               (uint32_t)(S.outer_all ? 1 : 0) << F0_OUTER_ALL | (uint32_t)wm1 << F0_WM1 |
+               (uint32_t)((!L.odd && L.w > 0) ? 1 : 0) << F0_FEN | (uint32_t)S.kappa << F0_KAPPA |
+               (uint32_t)L.B << F0_B | (uint32_t)L.m << F0_M;
+        R.f1 = (uint32_t)(L.odd ? 0 : woff[L.w]) << F1_GOFF | (uint32_t)acode << F1_ACODE | (uint32_t)si.shift << F1_GSHIFT |
+               (uint32_t)si.jmax << F1_JMAX | (uint32_t)si.row << F1_GROW;
+        int code_val[8] = {S.outside, 0, 0, 0, 0, 0, 0, 0};
+        for (size_t i = 0; i < S.mv.size(); i++) code_val[first_code + i] = S.mv[i];
+        for (size_t i = 0; i < S.dv.size(); i++) code_val[4 + i] = S.dv[i];
+        uint64_t v8 = 0, vi = 0;
+        for (int k = 0; k < 8; k++) {
+            int v = code_val[k];
+            bool neg = L.odd && (v % 4 == 3);      // odd classes: x_i = 1 + 2 c_i (mod 4); the word bit flips it again
+            v8 |= (uint64_t)(fp8_e4m3(v) | (neg ? 0x80 : 0)) << (8 * k);
+            vi |= (uint64_t)(uint8_t)(int8_t)(neg ? -v : v) << (8 * k);
+        }
+        R.vt8_lo = (uint32_t)v8; R.vt8_hi = (uint32_t)(v8 >> 32);
+        R.vti_lo = (uint32_t)vi; R.vti_hi = (uint32_t)(vi >> 32);
+        return R;
+    }
+
+private:
+    std::map<std::pair<std::vector<int>, int>, uint32_t> inner_base_;
+    std::map<std::pair<int, int>, SplitInfo> split_of_;
+};
+
+// 6-bit deposit tables (the same in both layouts)
+template <class LAY>
+void put_deposit_tables(unsigned char* blob) {
+    for (uint32_t F = 0; F < 64; F++)
+        for (uint32_t mbits = 0; mbits < 64; mbits++) {
+            uint32_t dep = wide_deposit(mbits, F);
+            blob[LAY::kOffPdep6 + F * kPdepPitch + mbits] = (uint8_t)dep;
+            uint32_t sp = 0;
+            for (int p = 0; p < 6; p++) {
+                if ((dep >> p) & 1u) sp |= 1u << (4 * kNibbleSlot[p]);
+                if ((F >> p) & 1u) sp |= 4u << (4 * kNibbleSlot[p]);
+            }
+            std::memcpy(blob + LAY::kOffSpread6 + 4 * (F * kSpreadPitch + mbits), &sp, 4);
+        }
+}
+
+// Lays the tables out as LAY says and fills `lay`; false: something does not fit
+template <class LAY>
+bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const std::vector<ClassRec>& recs, const std::vector<Leader>& cls,
+                   uint64_t npoints, int m_max, TableLayout& lay, std::vector<unsigned char>& blob) {
+    const uint32_t ncls = (uint32_t)cls.size();
+    std::vector<uint64_t> cls_off(ncls + 4, ~0ull);      // the search reads up to three entries past offset[ncls] = N
+    for (uint32_t ci = 0; ci < ncls; ci++) cls_off[ci] = cls[ci].offset;
+    cls_off[ncls] = npoints;
+    // bucket table: index >> shift -> class holding the first index of the bucket
+    std::vector<uint16_t> bucket(4096);
+    for (uint32_t b = 0; b < 4096; b++) {
+        uint64_t first = (uint64_t)b << LAY::kBucketShift;
+        uint32_t ci = (uint32_t)(std::upper_bound(cls_off.begin(), cls_off.begin() + ncls, first) - cls_off.begin());
+        bucket[b] = (uint16_t)(8u * (ci == 0 ? 0 : ci - 1));
+    }
+    std::vector<double> atab = {1.0, 1.0, 759.0, (1.0 / 759.0) * (1.0 + std::ldexp(1.0, -50)),
+                                2576.0, (1.0 / 2576.0) * (1.0 + std::ldexp(1.0, -50)), 4096.0, 1.0 / 4096.0};
+    const uint64_t inner_end = LAY::kOffInner + (uint64_t)D.inner.size() * sizeof(uint32_t);
+    const uint32_t cls_end = LAY::kWide ? Lay19::kOffWideRec : Lay13::kLdsBytes, split_end = LAY::kWide ? Lay19::kLdsBytes : Lay13::kOffCls;
+    if (D.guess.size() > LAY::kOffAtab - LAY::kOffGuess || cls_off.size() * 8 > LAY::kOffRnorm - LAY::kOffClsOff ||
+        (size_t)(m_max + 1) * sizeof(float) > LAY::kOffSplit - LAY::kOffRnorm ||
+        (D.split.size() + 1) * sizeof(SplitEnt) > split_end - LAY::kOffSplit || recs.size() * sizeof(ClassRec) > cls_end - LAY::kOffCls ||
+        npoints > (4096ull << LAY::kBucketShift) || inner_end > LAY::kMaxBlob)
+        return false;
+    blob.assign((inner_end + 15u) & ~(uint64_t)15u, 0);
+    auto put = [&](uint32_t off, const void* src, size_t bytes) { std::memcpy(blob.data() + off, src, bytes); };
+    put(LAY::kOffGs, gs.data(), gs.size() * 4);
+    put_deposit_tables<LAY>(blob.data());
+    put(LAY::kOffLut12, D.lut12.data(), D.lut12.size() * 2);
+    put(LAY::kOffBucket, bucket.data(), bucket.size() * 2);
+    put(LAY::kOffGuess, D.guess.data(), D.guess.size());
+    put(LAY::kOffAtab, atab.data(), atab.size() * 8);
+    put(LAY::kOffClsOff, cls_off.data(), cls_off.size() * 8);
+    for (int m = 1; m <= m_max; m++) {
+        const float rn = (float)(1.0 / std::sqrt(16.0 * m));
+        put(LAY::kOffRnorm + 4 * m, &rn, sizeof rn);
+    }
+    put(LAY::kOffSplit, D.split.data(), D.split.size() * sizeof(SplitEnt));
+    put(LAY::kOffCls, recs.data(), recs.size() * sizeof(ClassRec));
+    put(LAY::kOffInner, D.inner.data(), D.inner.size() * 4);
+    lay = TableLayout{};
+    lay.lds_bytes = LAY::kLdsBytes;
+    lay.blob_bytes = (uint32_t)blob.size();
+    lay.ncls = ncls;
+    lay.inner_entries = (uint32_t)D.inner.size();
+    lay.npoints = npoints;
+    return true;
+}
+
 }  // namespace
 
 bool build_wide_tables(int m_max, WideTables& out) {
@@ -258,6 +449,43 @@ bool build_wide_tables(int m_max, WideTables& out) {
         for (size_t i = 0; i < S.dv.size(); i++) { R.dv[i] = (int8_t)S.dv[i]; R.dc[i] = (uint8_t)S.dc[i]; }
         out.recs[ci] = R;
     }
+    // The tables of the table-driven decoder.  The direct F1 words' planes come first, the largest last: their entry
+    // numbers have 16 bits, and 80,551 planes fit because only the first entry of a table has to be named.
+    DecoderParts D;
+    std::map<std::pair<uint64_t, std::vector<int>>, bool> direct;
+    for (const Leader& L : cls) {
+        const ClassShape S = shape_of(L);
+        direct[{multinomial(S.dc), S.dc}] = true;
+    }
+    for (const auto& word : direct) {
+        const int64_t tb1 = D.inner_table(word.first.second, 0);
+        if (tb1 < 0 || tb1 > 0xFFFF) return false;
+    }
+    std::vector<ClassRec> recs(cls.size());
+    uint64_t most_steps = 0;
+    for (size_t ci = 0; ci < cls.size(); ci++) {
+        const Leader& L = cls[ci];
+        const ClassShape S = shape_of(L);
+        if (L.size >= (1ull << 52) || out.recs[ci].Pin * out.recs[ci].P1 >= (1u << 22) || out.recs[ci].P1 > 0xFFFF) return false;
+        int64_t tb0 = D.inner_table(S.mc, S.mc.empty() || S.outer_all ? 0 : 1);
+        const bool steps = tb0 < 0;
+        if (steps) {
+            if (S.f1direct || S.mv.size() > 7) return false;
+            most_steps = std::max(most_steps, out.recs[ci].Pin);
+            tb0 = 0;
+        }
+        DecoderParts::SplitInfo si;
+        ClassRec R = D.record(L, S, woff, (uint32_t)tb0 & 0xFFFFu, (uint32_t)D.inner_table(S.dc, 0), S.outer_all && !steps ? 4 : 1, si);
+        if (tb0 >= (1 << 24)) return false;
+        R.f0 |= (uint32_t)(tb0 >> 16) << F0_TB0_HI;
+        if (steps) R.f1 |= 1u << F1_STEPS;
+        recs[ci] = R;
+    }
+    if (most_steps > D.inner.size() || D.guess.size() / kGuessBuckets > 64) return false;      // the decoder reads (and drops) entry rin of a step class
+    if (!assemble_blob<Lay19>(D, out.gs, recs, cls, total, m_max, out.tab, out.blob)) return false;
+    if (out.recs.size() * sizeof(WideRec) > Lay19::kOffBinom - Lay19::kOffWideRec || out.binom.size() * 4 > Lay19::kOffInner - Lay19::kOffBinom) return false;
+    std::memcpy(out.blob.data() + Lay19::kOffWideRec, out.recs.data(), out.recs.size() * sizeof(WideRec));
+    std::memcpy(out.blob.data() + Lay19::kOffBinom, out.binom.data(), out.binom.size() * 4);
     return true;
 }
 
@@ -272,164 +500,31 @@ bool build_tables(int m_max, Tables& out) {
     const uint32_t ncls = (uint32_t)cls.size();
     if (running >= (1ull << 48)) return false;
 
-    // ---- lut12: colex rank -> mask, grouped by popcount ---------------------------------------------
-    std::vector<uint16_t> lut12;
-    int b12[14];
-    for (int p = 0; p <= 12; p++) {
-        b12[p] = (int)lut12.size();
-        for (uint32_t mk : masks_in_colex_order(12, p)) lut12.push_back((uint16_t)mk);
-    }
-    b12[13] = (int)lut12.size();
-
-    // ---- inner-word tables ------------------------------------------------------------------------
-    // Pattern = multiplicities of the values of the word in descending value order, over q slots.
-    // Entry rho: mixed radix, digit of the largest value least significant, each digit the colex rank of
-    // the subset that value occupies among the slots still free; the smallest value takes the rest.
-    // Planes: bit k of plane a/b = bit 0/1 of (symbol index + sym_base) of the value on slot k.
-    std::vector<uint32_t> inner;
-    std::map<std::pair<std::vector<int>, int>, uint32_t> inner_base;
-    auto inner_table = [&](const std::vector<int>& cnt, int sym_base) -> int64_t {
-        auto key = std::make_pair(cnt, sym_base);
-        auto it = inner_base.find(key);
-        if (it != inner_base.end()) return it->second;
-        int q = 0;
-        for (int c : cnt) q += c;
-        if (q > 16 || (int)cnt.size() + sym_base > 4) return -1;
-        uint64_t P = multinomial(cnt);
-        uint32_t base = (uint32_t)inner.size();
-        std::vector<std::vector<uint32_t>> cm(cnt.size());
-        for (size_t i = 0; i < cnt.size(); i++) cm[i] = masks_in_colex_order(q, cnt[i]);   // over-long lists are harmless
-        for (uint64_t rho = 0; rho < P; rho++) {
-            uint64_t r = rho;
-            uint32_t freemask = (q == 32) ? 0xFFFFFFFFu : ((1u << q) - 1u), pa = 0, pb = 0;
-            for (size_t i = 0; i < cnt.size(); i++) {
-                uint32_t occ;
-                int nfree = popcnt(freemask);
-                if (i + 1 == cnt.size()) occ = freemask;
-                else {
-                    uint64_t radix = g_binom[nfree][cnt[i]];
-                    occ = deposit(cm[i][r % radix], freemask);
-                    r /= radix;
-                }
-                int sym = (int)i + sym_base;
-                if (sym & 1) pa |= occ;
-                if (sym & 2) pb |= occ;
-                freemask &= ~occ;
-            }
-            inner.push_back(pa | (pb << 16));
-        }
-        inner_base[key] = base;
-        return base;
-    };
-    const int64_t dummy_tb = inner_table(std::vector<int>{}, 0);   // one all-zero entry
-    if (dummy_tb != 0) return false;
-
-    // ---- subset ranking tables ---------------------------------------------------------------------
-    // q-subsets of n slots, slots 0..11 low, 12..n-1 high; order: number j of high slots, then colex rank
-    // of the high part, then colex rank of the low part.
-    std::vector<SplitEnt> split;
-    std::vector<uint8_t> guess;
-    struct SplitInfo { uint16_t sp; int shift, jmax, row; };
-    std::map<std::pair<int, int>, SplitInfo> split_of;
-    auto split_table = [&](int n, int q) -> SplitInfo {
-        auto key = std::make_pair(n, q);
-        auto it = split_of.find(key);
-        if (it != split_of.end()) return it->second;
-        int nl = std::min(n, 12), nh = n - nl;
-        int jmin = std::max(0, q - nl), jmax = std::min(q, nh);
-        SplitInfo si;
-        si.sp = (uint16_t)((int)split.size() - jmin);      // entry of j is split[sp + j]
-        si.jmax = jmax;
-        si.row = (int)(guess.size() / kGuessBuckets);
-        std::vector<uint64_t> bases;
-        uint64_t base = 0;
-        for (int j = jmin; j <= jmax; j++) {
-            SplitEnt e{};
-            uint64_t div = g_binom[nl][q - j];
-            e.base = (uint32_t)base;
-            e.div = (uint16_t)div;
-            float inv = 1.0f / (float)div;
-            while ((double)inv * (double)div < 1.0) inv = std::nextafterf(inv, 2.0f);
-            e.inv = inv;
-            e.b12lo = (uint16_t)b12[q - j];
-            e.b12hi = (uint16_t)b12[j];
-            split.push_back(e);
-            bases.push_back(base);
-            base += g_binom[nh][j] * div;
-        }
-        uint64_t total = base;                              // C(n, q)
-        int shift = 0;
-        while (((total - 1) >> shift) >= kGuessBuckets) shift++;
-        si.shift = shift;
-        for (uint32_t b = 0; b < kGuessBuckets; b++) {
-            uint64_t d0 = (uint64_t)b << shift;
-            int j = jmin;
-            while (j < jmax && bases[j + 1 - jmin] <= d0) j++;
-            guess.push_back((uint8_t)j);
-        }
-        split_of[key] = si;
-        return si;
-    };
+    DecoderParts D;
+    const std::vector<SplitEnt>& split = D.split;
 
     // ---- class records ---------------------------------------------------------------------------
     std::vector<ClassRec> recs(ncls);
     std::vector<EncRec> encs(ncls);
-    std::vector<uint64_t> cls_off(ncls + 4, ~0ull);      // the search reads up to three entries past offset[ncls] = N
     for (uint32_t ci = 0; ci < ncls; ci++) {
         const Leader& L = cls[ci];
-        ClassRec R{};
-        cls_off[ci] = L.offset;
         const ClassShape S = shape_of(L);
         const bool f1direct = S.f1direct, outer_all = S.outer_all;
         const std::vector<int>&mv = S.mv, &mc = S.mc, &dv = S.dv, &dc = S.dc;
-        const int n = S.n, q = S.q, outside = S.outside;
+        const int outside = S.outside;
         uint64_t Pin = multinomial(mc);
         uint64_t P1 = f1direct ? multinomial(dc) : 1;
         // consistency with the class cardinality
-        uint64_t arr = g_binom[n][q] * Pin * P1;
-        if (arr != L.P1 * L.P0) return false;
+        if (g_binom[S.n][S.q] * Pin * P1 != L.P1 * L.P0) return false;
         int sym_base0 = outer_all ? 0 : 1;
-        int64_t tb0 = mc.empty() ? dummy_tb : inner_table(mc, sym_base0);
-        int64_t tb1 = f1direct ? inner_table(dc, 0) : dummy_tb;
+        int64_t tb0 = D.inner_table(mc, mc.empty() ? 0 : sym_base0);
+        int64_t tb1 = D.inner_table(dc, 0);
         if (tb0 < 0 || tb1 < 0 || tb0 > 0xFFFF || tb1 > 0xFFFF) return false;
-        SplitInfo si = split_table(n, q);
-        uint64_t PP = P1 * Pin;
-        if (PP >= (1u << 22) || P1 > 0xFFFF) return false;
-        R.PP = (uint32_t)PP;
-        R.invPP = (1.0 / (double)PP) * (1.0 + std::ldexp(1.0, -50));
-        float i1 = 1.0f / (float)P1;
-        while ((double)i1 * (double)P1 < 1.0) i1 = std::nextafterf(i1, 2.0f);
-        R.invP1 = i1;
-        R.P1 = (uint16_t)P1; R.tb0 = (uint16_t)tb0; R.tb1 = (uint16_t)tb1; R.sp = si.sp;
-        const int kappa = S.kappa;
-        int acode = L.A == 1 ? 0 : (L.A == 759 ? 1 : (L.A == 2576 ? 2 : 3));
-        int wm1 = (!L.odd && L.w > 0) ? L.w - 1 : 0;
-        R.f0 = (uint32_t)(L.odd ? 1 : 0) << F0_ODD | (uint32_t)(f1direct ? 1 : 0) << F0_F1DIRECT |
-               (uint32_t)(outer_all ? 1 : 0) << F0_OUTER_ALL | (uint32_t)wm1 << F0_WM1 |
-               (uint32_t)((!L.odd && L.w > 0) ? 1 : 0) << F0_FEN | (uint32_t)kappa << F0_KAPPA |
-               (uint32_t)L.B << F0_B | (uint32_t)L.m << F0_M | (uint32_t)n << F0_N | (uint32_t)q << F0_Q;
-        int goff = L.odd ? 0 : woff[L.w];
-        R.f1 = (uint32_t)goff << F1_GOFF | (uint32_t)acode << F1_ACODE | (uint32_t)si.shift << F1_GSHIFT |
-               (uint32_t)si.jmax << F1_JMAX | (uint32_t)si.row << F1_GROW;
-        // value of each nibble code.  Outer domain = all positions (odd, w = 24): code 0 = outside value,
-        // 4 + i = i-th minority value.  Otherwise: 0 = zero, 1 + i = i-th nonzero F0 value, 4 + i = i-th F1 value.
-        int code_val[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        if (outer_all) {
-            code_val[0] = outside;
-            for (size_t i = 0; i < mv.size(); i++) code_val[4 + i] = mv[i];
-        } else {
-            for (size_t i = 0; i < mv.size(); i++) code_val[1 + i] = mv[i];
-            for (size_t i = 0; i < dv.size(); i++) code_val[4 + i] = dv[i];
-        }
-        uint64_t v8 = 0, vi = 0;
-        for (int k = 0; k < 8; k++) {
-            int v = code_val[k];
-            bool neg = L.odd && (v % 4 == 3);      // odd classes: x_i = 1 + 2 c_i (mod 4); the word bit flips it again
-            v8 |= (uint64_t)(fp8_e4m3(v) | (neg ? 0x80 : 0)) << (8 * k);
-            vi |= (uint64_t)(uint8_t)(int8_t)(neg ? -v : v) << (8 * k);
-        }
-        R.vt8_lo = (uint32_t)v8; R.vt8_hi = (uint32_t)(v8 >> 32);
-        R.vti_lo = (uint32_t)vi; R.vti_hi = (uint32_t)(vi >> 32);
+        if (P1 * Pin >= (1u << 22) || P1 > 0xFFFF) return false;
+        DecoderParts::SplitInfo si;
+        ClassRec R = D.record(L, S, woff, (uint32_t)tb0, (uint32_t)tb1, outer_all ? 4 : 1, si);
+        R.f0 |= (uint32_t)S.n << F0_N | (uint32_t)S.q << F0_Q;
+        const int goff = (int)((R.f1 >> F1_GOFF) & 4095u), acode = (int)((R.f1 >> F1_ACODE) & 3u);
         recs[ci] = R;
 
         // the same class seen from the encoder: key of the leader, code of each absolute value, ranking radices
@@ -479,64 +574,7 @@ bool build_tables(int m_max, Tables& out) {
                (uint32_t)dig1 << E1_DIG1 | (uint32_t)sym_base0 << E1_SYM0;
         encs[ci] = E;
     }
-    cls_off[ncls] = running;
-
-    // ---- bucket table: index >> shift -> class holding the first index of the bucket --------------------
-    const uint32_t bucket_shift = kBucketShift, nbuckets = 1u << (48 - kBucketShift);
-    std::vector<uint16_t> bucket(nbuckets);
-    for (uint32_t b = 0; b < nbuckets; b++) {
-        uint64_t first = (uint64_t)b << bucket_shift;
-        uint32_t ci = (uint32_t)(std::upper_bound(cls_off.begin(), cls_off.begin() + ncls, first) - cls_off.begin());
-        bucket[b] = (uint16_t)(8u * (ci == 0 ? 0 : ci - 1));
-    }
-
-    // ---- 6-bit deposit tables ---------------------------------------------------------------------
-    std::vector<uint8_t> pdep6(64 * kPdepPitch, 0);
-    std::vector<uint32_t> spread6(64 * kSpreadPitch, 0);
-    for (uint32_t F = 0; F < 64; F++)
-        for (uint32_t mbits = 0; mbits < 64; mbits++) {
-            uint32_t dep = deposit(mbits, F);
-            pdep6[F * kPdepPitch + mbits] = (uint8_t)dep;
-            uint32_t sp = 0;
-            for (int p = 0; p < 6; p++) {
-                if ((dep >> p) & 1u) sp |= 1u << (4 * kNibbleSlot[p]);
-                if ((F >> p) & 1u) sp |= 4u << (4 * kNibbleSlot[p]);
-            }
-            spread6[F * kSpreadPitch + mbits] = sp;
-        }
-
-    // ---- blob ------------------------------------------------------------------------------------
-    std::vector<double> atab = {1.0, 1.0, 759.0, (1.0 / 759.0) * (1.0 + std::ldexp(1.0, -50)),
-                                2576.0, (1.0 / 2576.0) * (1.0 + std::ldexp(1.0, -50)), 4096.0, 1.0 / 4096.0};
-    TableLayout lay{};
-    const uint32_t inner_end = kOffInner + (uint32_t)(inner.size() * sizeof(uint32_t));
-    if (guess.size() > kOffAtab - kOffGuess || cls_off.size() * 8 > kOffRnorm - kOffClsOff ||
-        (split.size() + 1) * sizeof(SplitEnt) > kOffCls - kOffSplit || recs.size() * sizeof(ClassRec) > kLdsBytes - kOffCls ||
-        inner_end > kMaxBlob)
-        return false;
-    std::vector<unsigned char> blob((inner_end + 15u) & ~15u, 0);
-    auto put = [&](uint32_t off, const void* src, size_t bytes) { std::memcpy(blob.data() + off, src, bytes); };
-    put(kOffGs, gs.data(), gs.size() * 4);
-    put(kOffSpread6, spread6.data(), spread6.size() * 4);
-    put(kOffPdep6, pdep6.data(), pdep6.size());
-    put(kOffLut12, lut12.data(), lut12.size() * 2);
-    put(kOffBucket, bucket.data(), bucket.size() * 2);
-    put(kOffGuess, guess.data(), guess.size());
-    put(kOffAtab, atab.data(), atab.size() * 8);
-    put(kOffClsOff, cls_off.data(), cls_off.size() * 8);
-    float rnorm[16];
-    for (int m = 0; m < 16; m++) rnorm[m] = m >= 1 ? (float)(1.0 / std::sqrt(16.0 * m)) : 0.0f;
-    put(kOffRnorm, rnorm, sizeof rnorm);
-    put(kOffSplit, split.data(), split.size() * sizeof(SplitEnt));
-    put(kOffCls, recs.data(), recs.size() * sizeof(ClassRec));
-    put(kOffInner, inner.data(), inner.size() * 4);
-    lay.lds_bytes = kLdsBytes;
-    lay.blob_bytes = (uint32_t)blob.size();
-    lay.ncls = ncls;
-    lay.inner_entries = (uint32_t)inner.size();
-    lay.npoints = running;
-    out.lay = lay;
-    out.blob.swap(blob);
+    if (!assemble_blob<Lay13>(D, gs, recs, cls, running, m_max, out.lay, out.blob)) return false;
 
     // ---- encoder blob ------------------------------------------------------------------------------
     // ginv: any 12 cyclically consecutive coordinates of a cyclic code are an information set, so the low 12

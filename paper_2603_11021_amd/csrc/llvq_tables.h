@@ -37,11 +37,13 @@ static_assert(sizeof(ClassRec) == 48, "ClassRec layout");
 //     [2] outer_all (outer domain = all 24 positions: odd classes and w = 24)
 //     [3..7] wm1 = max(w-1,0)  [8] forced-sign enable  [9] kappa (parity of negative F1 signs)
 //     [10..14] B  [15..18] m  [19..23] n (slots of the outer domain)  [24..28] q (subset size)
+//     Lay19 (whose decoder needs neither n nor q): m takes [15..19], bits 16..23 of tb0 sit in [20..27]
+enum { F0_TB0_HI = 20 };
 enum { F0_ODD = 0, F0_F1DIRECT = 1, F0_OUTER_ALL = 2, F0_WM1 = 3, F0_FEN = 8, F0_KAPPA = 9,
        F0_B = 10, F0_M = 15, F0_N = 19, F0_Q = 24 };
 // f1: [0..11] first Golay word of the class in gs  [12..13] code of A  [14..18] guess shift
-//     [19..22] jmax  [23..28] row of the guess table
-enum { F1_GOFF = 0, F1_ACODE = 12, F1_GSHIFT = 14, F1_JMAX = 19, F1_GROW = 23 };
+//     [19..22] jmax  [23..28] row of the guess table  [29] placed step by step (Lay19 only)
+enum { F1_GOFF = 0, F1_ACODE = 12, F1_GSHIFT = 14, F1_JMAX = 19, F1_GROW = 23, F1_STEPS = 29 };
 
 struct alignas(16) SplitEnt {
     uint32_t base;       // number of subsets with fewer high slots
@@ -62,21 +64,54 @@ static_assert(sizeof(SplitEnt) == 16, "SplitEnt layout");
 constexpr uint32_t kSpreadPitch = 65;      // dwords per mask row of spread6: entry (F, m) at F * 65 + m, so that equal m of
                                            // different masks (all-zero sources are frequent) fall into different LDS banks
 constexpr uint32_t kPdepPitch  = 68;       // bytes per mask row of pdep6 (17 dwords, for the same reason)
-constexpr uint32_t kOffSpread6 = 0;        // 64 x 65 x u32
-constexpr uint32_t kOffPdep6   = 16640;    // 64 x 68 x u8
-constexpr uint32_t kOffLut12   = 20992;    // 4096 x u16
-constexpr uint32_t kOffBucket  = 29184;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
-constexpr uint32_t kOffGuess   = 37376;    // up to 48 rows x 64 x u8
-constexpr uint32_t kOffAtab    = 40448;    // 4 x {A, 1/A} doubles
-constexpr uint32_t kOffClsOff  = 40512;    // (ncls + 4) x u64, ncls <= 383: offsets, N, and three entries above every index
-constexpr uint32_t kOffRnorm   = 43616;    // 16 x float: 1/sqrt(16 m)
-constexpr uint32_t kOffSplit   = 43680;    // up to 352 x SplitEnt
-constexpr uint32_t kOffCls     = 49312;    // ncls x ClassRec
-constexpr uint32_t kLdsBytes   = 67712;    // end of the LDS-resident part
-constexpr uint32_t kOffGs      = 67712;    // 4096 x u32 (global memory)
-constexpr uint32_t kOffInner   = 84096;    // inner-word planes, u32 (global memory)
-constexpr uint32_t kMaxBlob    = 84096 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
-constexpr uint32_t kBucketShift = 36;      // bucket index = I >> 36 (4096 buckets cover 48 bits)
+struct Lay13 {
+    static constexpr bool kWide = false;
+    static constexpr uint32_t kOffSpread6 = 0;        // 64 x 65 x u32
+    static constexpr uint32_t kOffPdep6   = 16640;    // 64 x 68 x u8
+    static constexpr uint32_t kOffLut12   = 20992;    // 4096 x u16
+    static constexpr uint32_t kOffBucket  = 29184;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
+    static constexpr uint32_t kOffGuess   = 37376;    // up to 48 rows x 64 x u8
+    static constexpr uint32_t kOffAtab    = 40448;    // 4 x {A, 1/A} doubles
+    static constexpr uint32_t kOffClsOff  = 40512;    // (ncls + 4) x u64, ncls <= 383: offsets, N, and three entries above every index
+    static constexpr uint32_t kOffRnorm   = 43616;    // 16 x float: 1/sqrt(16 m)
+    static constexpr uint32_t kOffSplit   = 43680;    // up to 352 x SplitEnt
+    static constexpr uint32_t kOffCls     = 49312;    // ncls x ClassRec
+    static constexpr uint32_t kLdsBytes   = 67712;    // end of the LDS-resident part
+    static constexpr uint32_t kOffGs      = 67712;    // 4096 x u32 (global memory)
+    static constexpr uint32_t kOffInner   = 84096;    // inner-word planes, u32 (global memory)
+    static constexpr uint32_t kMaxBlob    = 84096 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
+    static constexpr uint32_t kBucketShift = 36;      // bucket index = I >> 36 (4096 buckets cover 48 bits)
+    static constexpr uint64_t kWordMask   = (1ull << 48) - 1;    // bits of a 64-bit word that hold index and gain code
+};
+
+// The unions up to shell 19: 1,457 classes, 55-bit indices, at most 2^49.6 points per class (so the quotients stay exact
+// in fp64), 5 MB of inner-word planes.  The planes and whatever follows the Golay words stay in global memory: 69 KB of
+// class records beside the small tables and the Golay words would fit LDS, but then one workgroup fills a compute unit and
+// a launch copies 146 KB.  Classes that three-bit value codes with two 16-bit planes cannot describe (subsets of more than
+// 16 slots or more than four minority values: 3 in a million indices) carry F1_STEPS and are placed step by step from
+// their WideRec (llvq_wide.h).  Against the step-by-step decoder with all tables in global memory that this replaced:
+// 4096 x 4104 at M = 1 236 -> 16.9 us, 4 M blocks to int8 430 -> 58 us (M = 16: 21.1 us).
+struct Lay19 {
+    static constexpr bool kWide = true;
+    static constexpr uint32_t kOffSpread6 = 0;
+    static constexpr uint32_t kOffPdep6   = 16640;
+    static constexpr uint32_t kOffLut12   = 20992;
+    static constexpr uint32_t kOffBucket  = 29184;
+    static constexpr uint32_t kOffGuess   = 37376;    // up to 63 rows x 64 x u8
+    static constexpr uint32_t kOffAtab    = 41408;
+    static constexpr uint32_t kOffClsOff  = 41472;    // (ncls + 4) x u64, ncls <= 1457
+    static constexpr uint32_t kOffRnorm   = 53168;    // 20 x float
+    static constexpr uint32_t kOffSplit   = 53248;    // up to 512 x SplitEnt
+    static constexpr uint32_t kLdsBytes   = 61440;
+    static constexpr uint32_t kOffGs      = 61440;    // 4096 x u32
+    static constexpr uint32_t kOffCls     = 77824;    // ncls x ClassRec (global memory)
+    static constexpr uint32_t kOffWideRec = 147760;   // ncls x WideRec (global memory)
+    static constexpr uint32_t kOffBinom   = 241008;   // 25 x 25 x u32 (global memory)
+    static constexpr uint32_t kOffInner   = 243520;   // inner-word planes (global memory)
+    static constexpr uint32_t kMaxBlob    = 243520 + 4 * (1u << 24);
+    static constexpr uint32_t kBucketShift = 43;      // 4096 buckets cover 55 bits
+    static constexpr uint64_t kWordMask   = (1ull << 56) - 1;
+};
 constexpr uint32_t kGuessBuckets = 64;     // buckets of the subset-split guess table per (n, q)
 
 struct TableLayout {

@@ -1,15 +1,14 @@
-// Dequantiser for the larger unions of shells, Lambda_24(m_max) with 14 <= m_max <= 19 (paper Table 1, row m = 19:
-// 23,546,209,100,646,960 points, 55-bit indices; App. A steps 1-4).  Up to shell 19 there are 1,457 classes, up to six
-// distinct absolute values per class (five up to shell 13), values up to 17 and arrangement ranks of 38 bits, which the
-// table-driven decoder of llvq_decode_core.h is not laid out for (three-bit value codes, two symbol planes, class
-// tables that fill LDS for 383 classes).  This one follows the same index format step by step with plain 64-bit
-// integer arithmetic and loops over the 24 positions: class records and offsets stay in global memory, subsets are
-// unranked against a table of binomial coefficients.  It is several times slower than the table-driven decoder and
-// is used only by contexts created with m_max > 13.  The same source compiles for the host, where a test harness
-// runs it against the tables without a GPU.
+// The larger unions of shells, Lambda_24(m_max) with 14 <= m_max <= 19 (paper Table 1, row m = 19: 23,546,209,100,646,960
+// points, 55-bit indices; App. A steps 1-4), decoded step by step with plain 64-bit integer arithmetic, subsets unranked
+// against a table of binomial coefficients.  The kernels decode these unions with the tables of llvq_decode_core.h
+// (layout Lay19); what those tables cannot describe, the few classes with subsets of more than 16 slots or more than four
+// minority values (3 in a million indices), is placed by wide_place below.  wide_decode is the whole procedure in one
+// call, without any of the tables; a test harness runs it on the host.
 #pragma once
 #include <cstdint>
 #include <vector>
+
+#include "llvq_tables.h"
 
 #if defined(__HIPCC__)
 #define LLVQ_WHD __host__ __device__ inline
@@ -85,18 +84,54 @@ LLVQ_WHD uint32_t wide_deposit(uint32_t src, uint32_t mask) {
 
 // Lays the values of a word (multiplicities cnt[0..nv-1], descending value order) onto the set bits of `slots`
 // according to the mixed-radix rank rho: digit of the largest value least significant, each digit the colex rank of
-// the subset that value takes among the slots still free; the last value takes what is left.  occ[i] = positions of value i.
-LLVQ_WHD void wide_inner_word(const uint32_t* binom, const uint8_t* cnt, int nv, uint64_t rho, uint32_t slots, uint32_t* occ) {
+// the subset that value takes among the slots still free; the last value takes what is left.  put(i, positions of value i).
+template <class Put>
+LLVQ_WHD void wide_inner_word(const uint32_t* binom, const uint8_t* cnt, int nv, uint64_t rho, uint32_t slots, Put put) {
     uint32_t freemask = slots;
-    for (int i = 0; i < nv; i++) {
+    for (int i = 0; i + 1 < nv; i++) {
         const int nfree = (int)wide_popc(freemask);
-        if (i + 1 == nv) { occ[i] = freemask; break; }
         const uint32_t radix = binom[nfree * 25 + cnt[i]];
         const uint32_t digit = (uint32_t)(rho % radix);
         rho /= radix;
-        occ[i] = wide_deposit(wide_colex_unrank(binom, nfree, cnt[i], digit), freemask);
-        freemask &= ~occ[i];
+        const uint32_t occ = wide_deposit(wide_colex_unrank(binom, nfree, cnt[i], digit), freemask);
+        put(i, occ);
+        freemask &= ~occ;
     }
+    put(nv - 1, freemask);
+}
+
+// App. A step 4 for a block of class R whose Golay word c and digits are known: calls emit(positions, code, value) for the
+// outside value (code 0), the minority values (codes 1, 2, ..) and the direct F1 values (codes 8, 9, ..) and returns the
+// positions whose sign is flipped.
+template <class Emit>
+LLVQ_WHD uint32_t wide_place(const uint32_t* binom, const WideRec& R, uint32_t c, uint32_t s, uint32_t d, uint64_t rin, uint32_t rho1, Emit emit) {
+    const bool odd = R.flags & WF_ODD, outer_all = R.flags & WF_OUTER_ALL, f1direct = R.flags & WF_F1DIRECT;
+    const uint32_t om = outer_all ? 0xFFFFFFu : (~c & 0xFFFFFFu);
+    // the q-subset U of the outer domain's n slots: slots 0..11 low, the rest high; ordered by the number j of high
+    // slots, then the colex rank of the high part, then that of the low part
+    const int n = R.n, q = R.q, nl = n < 12 ? n : 12, nh = n - nl;
+    int j = q - nl > 0 ? q - nl : 0;
+    const int jmax = q < nh ? q : nh;
+    uint32_t base = 0;
+    for (; j < jmax; j++) {
+        const uint32_t cnt = binom[nh * 25 + j] * binom[nl * 25 + (q - j)];
+        if (d < base + cnt) break;
+        base += cnt;
+    }
+    const uint32_t dl = d - base, div = binom[nl * 25 + (q - j)];
+    const uint32_t U_rel = wide_colex_unrank(binom, nl, q - j, dl % div) | (wide_colex_unrank(binom, nh, j, dl / div) << 12);
+    const uint32_t U = wide_deposit(U_rel, om);
+    emit(om & ~U, 0, (int)R.outside);
+    if (R.nm) wide_inner_word(binom, R.mc, R.nm, rin, U, [&](int i, uint32_t occ) { emit(occ, 1 + i, (int)R.mv[i]); });
+    if (f1direct) wide_inner_word(binom, R.dc, R.nd, rho1, c, [&](int i, uint32_t occ) { emit(occ, 8 + i, (int)R.dv[i]); });
+    // signs: even classes take w - 1 free bits on the word's support (the last slot is forced by condition (iii)),
+    // then one bit per slot of U; odd classes are negated where the word has a 1
+    if (odd) return c;
+    const uint32_t wm1 = R.w ? R.w - 1u : 0u;
+    uint32_t s1 = s & ((1u << wm1) - 1u);
+    const uint32_t forced = ((R.flags & WF_FEN) ? 1u : 0u) & (((R.flags & WF_KAPPA) ? 1u : 0u) ^ wide_popc(s1)) & 1u;
+    s1 |= forced << wm1;
+    return wide_deposit(s1, c) | wide_deposit(s >> wm1, U);
 }
 
 // Decodes index I < npoints into 24 int8 coordinates (six dwords, position order); returns the shell.
@@ -119,46 +154,11 @@ LLVQ_WHD uint32_t wide_decode(const WidePtrs& T, uint64_t I, uint32_t (&out)[6],
     const uint64_t rin = t % R.Pin;
     const uint32_t d = (uint32_t)(t / R.Pin);
     // step 4: Golay word, placement, signs
-    const uint32_t c = T.gs[R.goff + r];
-    const bool odd = R.flags & WF_ODD, outer_all = R.flags & WF_OUTER_ALL, f1direct = R.flags & WF_F1DIRECT;
-    const uint32_t om = outer_all ? 0xFFFFFFu : (~c & 0xFFFFFFu);
-    // the q-subset U of the outer domain's n slots: slots 0..11 low, the rest high; ordered by the number j of high
-    // slots, then the colex rank of the high part, then that of the low part
-    const int n = R.n, q = R.q, nl = n < 12 ? n : 12, nh = n - nl;
-    int j = q - nl > 0 ? q - nl : 0;
-    const int jmax = q < nh ? q : nh;
-    uint32_t base = 0;
-    for (; j < jmax; j++) {
-        const uint32_t cnt = T.binom[nh * 25 + j] * T.binom[nl * 25 + (q - j)];
-        if (d < base + cnt) break;
-        base += cnt;
-    }
-    const uint32_t dl = d - base, div = T.binom[nl * 25 + (q - j)];
-    const uint32_t U_rel = wide_colex_unrank(T.binom, nl, q - j, dl % div) | (wide_colex_unrank(T.binom, nh, j, dl / div) << 12);
-    const uint32_t U = wide_deposit(U_rel, om);
-    uint32_t occ_m[kWideMaxMinor] = {0, 0, 0, 0, 0}, occ_d[kWideMaxDirect] = {0, 0, 0, 0};
-    if (R.nm) wide_inner_word(T.binom, R.mc, R.nm, rin, U, occ_m);
-    if (f1direct) wide_inner_word(T.binom, R.dc, R.nd, rho1, c, occ_d);
-    // signs: even classes take w - 1 free bits on the word's support (the last slot is forced by condition (iii)),
-    // then one bit per slot of U; odd classes are negated where the word has a 1
-    uint32_t neg;
-    if (odd) {
-        neg = c;
-    } else {
-        const uint32_t wm1 = R.w ? R.w - 1u : 0u;
-        uint32_t s1 = s & ((1u << wm1) - 1u);
-        const uint32_t forced = ((R.flags & WF_FEN) ? 1u : 0u) & (((R.flags & WF_KAPPA) ? 1u : 0u) ^ wide_popc(s1)) & 1u;
-        s1 |= forced << wm1;
-        neg = wide_deposit(s1, c) | wide_deposit(s >> wm1, U);
-    }
-    int8_t x[24];
-    for (int p = 0; p < 24; p++) {
-        const uint32_t bit = 1u << p;
-        int v = (om & ~U & bit) ? R.outside : 0;
-        for (int i = 0; i < kWideMaxMinor; i++) if (occ_m[i] & bit) v = R.mv[i];
-        for (int i = 0; i < kWideMaxDirect; i++) if (occ_d[i] & bit) v = R.dv[i];
-        x[p] = (int8_t)((neg & bit) ? -v : v);
-    }
+    int8_t x[24] = {};
+    const uint32_t neg = wide_place(T.binom, R, T.gs[R.goff + r], s, d, rin, rho1, [&](uint32_t occ, int, int v) {
+        for (int p = 0; p < 24; p++) if ((occ >> p) & 1u) x[p] = (int8_t)v;
+    });
+    for (int p = 0; p < 24; p++) if ((neg >> p) & 1u) x[p] = (int8_t)-x[p];
     for (int k = 0; k < 6; k++)
         out[k] = (uint32_t)(uint8_t)x[4 * k] | ((uint32_t)(uint8_t)x[4 * k + 1] << 8) | ((uint32_t)(uint8_t)x[4 * k + 2] << 16) |
                  ((uint32_t)(uint8_t)x[4 * k + 3] << 24);
@@ -169,6 +169,8 @@ LLVQ_WHD uint32_t wide_decode(const WidePtrs& T, uint64_t I, uint32_t (&out)[6],
 // host-side tables of the wide decoder
 struct WideTables {
     WideLayout lay;
+    TableLayout tab;                   // the tables of llvq_decode_core.h in layout Lay19
+    std::vector<unsigned char> blob;
     uint64_t shell_off[24];            // index of the first point of shell m (N(m-1)); entries above m_max hold N(m_max)
     std::vector<WideRec> recs;
     std::vector<uint64_t> cls_off;     // ncls + 1 entries

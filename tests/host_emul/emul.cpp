@@ -74,4 +74,18 @@ uint64_t emul_wide_decode_i8(const uint64_t* idx, uint64_t n, int8_t* out) {
     return bad;
 }
 
+// the same indices through the table-driven decoder in the layout of these unions (what the kernels run)
+uint64_t emul_wide_tab_decode_i8(const uint64_t* idx, uint64_t n, int8_t* out) {
+    const auto T = llvq::make_tab_ptrs<llvq::Lay19>(g_wide.blob.data(), g_wide.blob.data(), g_wide.tab);
+    uint64_t bad = 0;
+    for (uint64_t k = 0; k < n; k++) {
+        if (idx[k] >= T.npoints) { bad++; std::memset(out + 24 * k, 0, 24); continue; }
+        uint32_t w[4], o[6];
+        const llvq::BlockInfo bi = llvq::decode_block(T, idx[k], w);
+        llvq::nibbles_to_i8(w, bi.vti_lo, bi.vti_hi, o);
+        std::memcpy(out + 24 * k, o, 24);
+    }
+    return bad;
+}
+
 }  // extern "C"
