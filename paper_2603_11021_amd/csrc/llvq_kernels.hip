@@ -401,9 +401,8 @@ struct MatItems {
     const uint16_t* gain[kMaxItems];
     float* y[kMaxItems];
     int row_end[kMaxItems];        // rows of matrices 0..i together; entries past the last matrix repeat the total
-    int tile_end[kMaxItems];       // the same in tiles of 32 rows, every matrix rounded up (mfma_kernel)
     int tile16_end[kMaxItems];     // the same in tiles of 16 rows (tile_kernel)
-    int strip_end[kMaxItems];      // the same in strips of 128 rows (panel_kernel)
+    int strip_end[kMaxItems];      // the same in strips of the height the launch asks for (set_strips)
 };
 
 template <int FMT, typename X2, bool BIG_GLOBAL, bool DYNAMIC, bool MULTI = false, class LAY = Lay13>
@@ -600,14 +599,7 @@ __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* _
     }
 }
 
-// ---- llvq_matmul, MFMA kernel for 2 <= M (batched decode and prefill) --------------------------------------
-// A wave owns 32 weight rows and two neighbouring blocks of 24 input channels per step: lanes 0..31 decode
-// block b of rows r0..r0+31, lanes 32..63 block b+1 of the same rows.  The decoded block, scaled by
-// gain/sqrt(16 m) and rounded to the activation type, is exactly the B operand of v_mfma_f32_32x32x16 (lane l
-// supplies k = 8*(l/32)..+7 of column l%32), so the weights go from the decoder's registers straight into the
-// matrix cores; the A operand (32 tokens x the same 16 channels) is read from global memory.  Three MFMAs consume
-// the 24 channels of both blocks.  The block pairs of a row are cut into ranges that different workgroups take (split
-// along K), partial tiles are added to y with fp32 atomics, y is cleared first by fill_kernel.
+// ---- llvq_matmul on the matrix cores: operand types, clearing of y, weights in the activation type ------------------
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
@@ -674,174 +666,7 @@ template <> struct Mma<bf16x2_t> {
 };
 
 constexpr int kGemmMinM = 96;       // from this many activation rows on, llvq_matmul_ws dequantises once and calls a dense GEMM
-constexpr int kMfmaMinM = 3;        // from this many activation rows on, llvq_matmul uses the MFMA kernel
-// THREADS x TOKTILES: more token tiles per pass over the weights need more accumulator registers, i.e. fewer
-// waves per SIMD.  Used as 1024 threads x 2 tiles (64 tokens per pass) for 3 <= M <= 64; larger M takes prefill_kernel.
-// MULTI: the row tiles are those of up to four matrices that share x, one matrix after the other (`items`).
-template <int FMT, typename X2, int THREADS, int kTokTiles, bool MULTI = false>
-__global__ void __launch_bounds__(THREADS) mfma_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
-                                                        const void* __restrict__ idx_in, const uint16_t* __restrict__ gain_in,
-                                                        const uint32_t* __restrict__ x, int M, int N_in, int KB,
-                                                        Code cd, uint32_t kranges, MatItems items, float* __restrict__ y_in) {
-    constexpr int kWavesHere = THREADS / 64;
-    load_tables<THREADS>(blob, lay.blob_bytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = lane & 31, half = lane >> 5;
-    // The waves of a workgroup own neighbouring row tiles and walk the same block pairs (the range blockIdx.y of the
-    // kranges ranges a row is cut into), so they ask for the same activation lines at about the same time and the
-    // vector cache serves fifteen of sixteen requests.  (Dealing the steps to the waves as one contiguous sequence made
-    // every wave fetch its own activations from L2: at M = 64 that traffic, not the decode, set the time.)
-    const uint32_t spt = ((uint32_t)KB + 1) / 2;                         // steps (block pairs) per row tile
-    const uint32_t n_rt = MULTI ? (uint32_t)items.tile_end[kMaxItems - 1] : ((uint32_t)N_in + 31) / 32;
-    const uint32_t rt_all = (uint32_t)blockIdx.x * kWavesHere + wave;
-    const uint32_t s0 = (uint32_t)(((uint64_t)spt * blockIdx.y) / kranges);
-    const uint32_t s1 = (uint32_t)(((uint64_t)spt * (blockIdx.y + 1)) / kranges);
-    if (rt_all >= n_rt || s0 >= s1) return;
-    // the matrix this wave's row tile belongs to (wave-uniform) and the tile's number inside it
-    const void* idx = idx_in;
-    const uint16_t* gain = gain_in;
-    float* y = y_in;
-    int N = N_in;
-    uint32_t rt = rt_all;
-    if constexpr (MULTI) {
-        int it = 0, first_tile = 0, first_row = 0;
-#pragma unroll
-        for (int i = 0; i + 1 < kMaxItems; i++) {
-            if (rt_all >= (uint32_t)items.tile_end[i]) { it = i + 1; first_tile = items.tile_end[i]; first_row = items.row_end[i]; }
-        }
-        idx = items.idx[it]; gain = items.gain[it]; y = items.y[it];
-        N = items.row_end[it] - first_row;
-        rt = rt_all - (uint32_t)first_tile;
-    }
-    const size_t xpitch = (size_t)KB * 12;                              // dwords per activation row
-
-    for (int m0 = 0; m0 < M; m0 += 32 * kTokTiles) {
-        const int ntile = min(kTokTiles, (M - m0 + 31) / 32);
-        float16_t acc[kTokTiles];
-#pragma unroll
-        for (int t = 0; t < kTokTiles; t++) {
-#pragma unroll
-            for (int v = 0; v < 16; v++) acc[t][v] = 0.0f;
-        }
-        // activation rows of this lane as dword offsets, one per token tile (clamped: out-of-range tokens are never stored)
-        uint32_t xoff[kTokTiles];
-#pragma unroll
-        for (int t = 0; t < kTokTiles; t++) xoff[t] = (uint32_t)min(M - 1, m0 + 32 * t + col) * (uint32_t)xpitch;
-
-        // adds the accumulated tiles of weight-row tile `tile` to y and clears them
-        auto flush = [&](uint32_t tile) {
-            const int wrow = (int)tile * 32 + col;
-            if (wrow < N) {
-                // element offset of (token m0 + 4*half, weight row wrow); M*N < 2^32 is checked by the caller.
-                // Register v of tile t belongs to token m0 + 32 t + 8 (v/4) + 4 half + v%4.
-                uint32_t ot = (uint32_t)(m0 + 4 * half) * (uint32_t)N + (uint32_t)wrow;
-                const uint32_t un = (uint32_t)N;
-#pragma unroll
-                for (int t = 0; t < kTokTiles; t++) {
-                    if (t < ntile) {
-                        const int tok0 = m0 + 32 * t + 4 * half;
-                        const bool full = m0 + 32 * t + 32 <= M;
-                        uint32_t og = ot;
-#pragma unroll
-                        for (int q = 0; q < 4; q++) {
-                            uint32_t ov = og;
-#pragma unroll
-                            for (int r = 0; r < 4; r++) {
-                                if (full || tok0 + 8 * q + r < M) atomicAdd(y + ov, acc[t][4 * q + r]);
-                                ov += un;
-                            }
-                            og += 8 * un;
-                        }
-                    }
-                    ot += 32 * un;
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-#pragma unroll
-            for (int t = 0; t < kTokTiles; t++) {
-#pragma unroll
-                for (int v = 0; v < 16; v++) acc[t][v] = 0.0f;
-            }
-        };
-
-        // the word and gain of the next step are requested before this step's block is decoded
-        const int row = (int)rt * 32 + col;
-        auto request = [&](uint32_t st, RawBlock& r) {
-            const size_t k = (size_t)min(row, N - 1) * KB + min(2 * st + half, (uint32_t)KB - 1);
-            load_raw<FMT>(idx, gain, cd.gain_array(), k, r);
-        };
-        RawBlock raw, raw_next;
-        request(s0, raw);
-        for (uint32_t st = s0; st < s1; st++, raw = raw_next) {
-            request(min(st + 1, s1 - 1), raw_next);
-            const uint32_t b = 2 * st + half;
-            // this step's activation operands are requested before the block is decoded (each lane reads 48 bytes of a
-            // different token row: the slowest loads of the step)
-            const uint32_t bx = min(b, (uint32_t)KB - 1) * 12;
-            u32x4 xa[kTokTiles <= 2 ? kTokTiles : 1][3];
-            if constexpr (kTokTiles <= 2) {
-#pragma unroll
-                for (int t = 0; t < kTokTiles; t++) {
-                    if (t < ntile) {
-                        const u32x4* xp = reinterpret_cast<const u32x4*>(x + (size_t)(xoff[t] + bx));
-                        xa[t][0] = xp[0]; xa[t][1] = xp[1]; xa[t][2] = xp[2];
-                    }
-                }
-            }
-            const bool live = row < N && b < (uint32_t)KB;
-            uint64_t I;
-            uint16_t gb;
-            finish_block<FMT>(raw, cd, I, gb);
-            const float g = __half2float(__ushort_as_half(gb));
-            const bool ok = live && I < T.npoints;
-            if (!ok) I = 0;
-            uint32_t w[4];
-            const llvq::BlockInfo bi = llvq::decode_block(T, I, w);
-            const float scale = ok ? g * bi.rnorm : 0.0f;
-            constexpr int kTerms = Mma<X2>::kTerms;
-            uint32_t wt[kTerms][12];
-#pragma unroll
-            for (int c = 0; c < 4; c++) {
-                uint32_t fe, fo, o[kTerms];
-                chunk_fp8(w[c], bi.vt8_lo, bi.vt8_hi, fe, fo);
-                Mma<X2>::weights(fe, false, scale, o);
-#pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
-                Mma<X2>::weights(fo, false, scale, o);
-#pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
-                Mma<X2>::weights(fe, true, scale, o);
-#pragma unroll
-                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
-            }
-#pragma unroll
-            for (int t = 0; t < kTokTiles; t++) {
-                if (t < ntile) {
-                    if constexpr (kTokTiles <= 2) {
-#pragma unroll
-                        for (int j = 0; j < 3; j++) {
-#pragma unroll
-                            for (int r = 0; r < kTerms; r++)
-                                acc[t] = Mma<X2>::mma(xa[t][j], u32x4{wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]}, acc[t]);
-                        }
-                    } else {
-                        const u32x4* xp = reinterpret_cast<const u32x4*>(x + (size_t)(xoff[t] + bx));
-                        const u32x4 xl[3] = {xp[0], xp[1], xp[2]};
-#pragma unroll
-                        for (int j = 0; j < 3; j++) {
-#pragma unroll
-                            for (int r = 0; r < kTerms; r++)
-                                acc[t] = Mma<X2>::mma(xl[j], u32x4{wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]}, acc[t]);
-                        }
-                    }
-                }
-                if (kTokTiles > 2 && (t & 1)) __builtin_amdgcn_sched_barrier(0);   // keep only two tiles of activations in flight
-            }
-        }
-        flush(rt);
-    }
-}
+constexpr int kMfmaMinM = 3;        // from this many activation rows on, llvq_matmul uses the matrix cores
 
 // ---- llvq_matmul, batched decode (3 <= M <= 32): a row tile belongs to one workgroup, K is reduced inside it ------
 // A step = 16 weight rows x 4 neighbouring blocks of 24 input channels: lane l decodes block 4 s + l / 16 of row l % 16
@@ -1079,54 +904,111 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
     }
 }
 
-// ---- llvq_matmul, prefill kernel for large M: activations shared through LDS, no split along K -----------------
-// A workgroup of eight waves owns a strip of 256 weight rows (wave w: rows 32 w .. 32 w + 31 of the strip) and a pass of
-// 256 tokens, and walks all block pairs of the rows.  Per step the activation tile of the step (256 tokens x 48 channels)
-// is staged once in LDS and read by all eight waves as MFMA A operands, so it is fetched from L2 once per workgroup
-// instead of once per wave; the decoded blocks are the B operands straight from the decoder's registers as in
-// mfma_kernel.  A workgroup sees every channel of its rows, so y is written once with plain stores: no clearing, no
-// atomics, results reproducible.  Only the small tables are kept in LDS (the Golay words and inner-word planes are
-// read from global memory), which leaves room for two activation buffers.
-// Shape used: 8 waves x 8 token tiles (strips of 256 rows, passes of 256 tokens; 128 accumulator registers, two waves per
-// SIMD).  16 waves x 2 token tiles was measured for M <= 64 and lost to mfma_kernel (75.6 against 68 us on 14336 x 4104).
-constexpr uint32_t kATokenPitch = 112;                 // bytes per token in the staged tile: 96 of data, padded so that rows stay 16-byte
-                                                       // aligned (128-bit LDS accesses) and eight consecutive tokens cover all banks
+// ---- llvq_matmul, 33 <= M: activations shared by the waves of a K slice ------------------------------------------
+// What a step costs is set by the LDS pipe (64 bytes per cycle, measured): about 280 cycles for the table gathers of 64
+// blocks, and 17 per 16-byte operand read of a wave, so 204 for 64 blocks x 128 tokens.  Staging the activations for every
+// wave on its own would add as much again; y-tiles shared by the whole chip would add 3 ns per 1000 fp32 atomics (335 G/s,
+// whatever their placement: 52 us for 256 workgroups x 64 K values).  Hence: a workgroup of sixteen waves owns
+// kRowTiles x 32 weight rows and a pass of 32 TT tokens; wave (slice, tile) decodes 32 rows x 2 blocks per step and multiplies
+// them with all tokens of the pass (16 TT accumulator registers), the slices take turns at the block pairs, and the
+// kRowTiles waves of a slice share its activation tile in LDS.  At the end the slices are added through LDS, so one
+// workgroup writes (or, with the rows' block pairs split over workgroups, adds to y) 32 kRowTiles x 32 TT values once.
+// 128 registers per lane keep four waves on a SIMD, which the decode's chains of dependent table reads need (two waves
+// with 256 tokens each, as here before, ran at a third of the rate).
+// The slices do not wait for each other: no barrier in the loop, but two counters per slice in LDS.  `ready` counts staged token
+// tiles, `done` counts finished steps; a wave stages token tile `tile` of the next step (direct global-to-LDS loads) once
+// all waves of its slice are past the step before this one.  A wave waits only for waves of its own workgroup and for
+// things these do before they wait themselves, so every wait ends.
+// Llama-3-8B-shaped block (seven layers, fp16): M = 64 XX -> XX us, M = 128 XX -> XX us, M = 256 XX -> XX us against the
+// split-K kernel and the strip kernel with two waves per SIMD.
+template <int TT> constexpr int kSliceTiles = TT <= 2 ? 2 : 4;           // 32-row tiles per workgroup
+constexpr uint32_t kSliceTabBytes = Lay13::kOffInner - Lay13::kOffSpread6;                 // small tables and Golay words; class records and planes in global memory
+constexpr uint32_t kSliceXOff = (kSliceTabBytes + 511u) & ~511u;
+template <int TT> constexpr uint32_t kSliceXBuf = TT * 3072u;                              // one step of one slice: 32 TT tokens x 96 bytes
+template <int TT> constexpr uint32_t kSliceFlagOff = kSliceXOff + 2u * (16 / kSliceTiles<TT>) * kSliceXBuf<TT>;
+template <int TT> constexpr uint32_t kSliceLds = (kSliceFlagOff<TT> + 64u) > 131072u ? kSliceFlagOff<TT> + 64u : 131072u;      // the final sum takes 2 x 64 KB
 
-template <int FMT, typename X2, int WAVES, int TT>
-__global__ void __launch_bounds__(64 * WAVES) prefill_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
-                                                                   const void* __restrict__ idx, const uint16_t* __restrict__ gain,
-                                                                   const uint32_t* __restrict__ x, int M, int N, int KB, Code cd,
-                                                                   int ksplit, float* __restrict__ y) {
-    constexpr int kPrefillThreads = 64 * WAVES, kPrefillTokens = 32 * TT, kPrefillRows = 32 * WAVES;
-    constexpr uint32_t kABufBytes = kPrefillTokens * kATokenPitch;
-    load_tables<kPrefillThreads>(blob, lay.lds_bytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
-    unsigned char* abuf = g_lds + lay.lds_bytes;                         // two buffers of kABufBytes
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int FMT, typename X2, int TT, bool MULTI>
+__global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
+                                                         const void* __restrict__ idx_in, const uint16_t* __restrict__ gain_in,
+                                                         const uint32_t* __restrict__ x, int M, int N_in, int KB, Code cd,
+                                                         int ksplit, MatItems items, float* __restrict__ y_in) {
+    constexpr int kTiles = kSliceTiles<TT>, kSlices = 16 / kTiles;
+    static_assert(TT <= kTiles, "a wave stages at most one token tile");
+    constexpr int kTerms = Mma<X2>::kTerms;
+    // the matrix this workgroup's strip belongs to and the strip's first row inside it (wave-uniform)
+    const void* idx = idx_in;
+    const uint16_t* gain = gain_in;
+    float* y = y_in;
+    int N = N_in, strip = (int)blockIdx.x;
+    if constexpr (MULTI) {
+        int it = 0, first_strip = 0, first_row = 0;
+#pragma unroll
+        for (int i = 0; i + 1 < kMaxItems; i++) {
+            if (strip >= items.strip_end[i]) { it = i + 1; first_strip = items.strip_end[i]; first_row = items.row_end[i]; }
+        }
+        idx = items.idx[it]; gain = items.gain[it]; y = items.y[it];
+        N = items.row_end[it] - first_row;
+        strip -= first_strip;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = wave % kTiles, slice = wave / kTiles;
     const int col = lane & 31, half = lane >> 5;
-    // steps (block pairs) of a row; with ksplit > 1 the workgroups of blockIdx.z share them and add their parts to y
-    const uint32_t spt_all = ((uint32_t)KB + 1) / 2;
-    const uint32_t st_first = (uint32_t)(((uint64_t)spt_all * blockIdx.z) / (uint32_t)ksplit);
-    const uint32_t spt = (uint32_t)(((uint64_t)spt_all * (blockIdx.z + 1)) / (uint32_t)ksplit);      // one past this workgroup's last step
-    const int m0 = (int)blockIdx.y * kPrefillTokens;
-    const int wrow = (int)blockIdx.x * kPrefillRows + wave * 32 + col;    // weight row of this lane
-    const size_t xpitch = (size_t)KB * 12;                              // dwords per activation row
+    uint32_t* flags = reinterpret_cast<uint32_t*>(g_lds + kSliceFlagOff<TT>);                  // ready[kSlices], done[kSlices]
+    if (threadIdx.x < 2 * kSlices) flags[threadIdx.x] = 0;                                     // published by the barrier of load_tables
+    load_tables(blob + Lay13::kOffSpread6, kSliceTabBytes);
+    const TabPtrs T = llvq::make_tab_ptrs(lds_origin() - Lay13::kOffSpread6, blob, lay);
+    unsigned char* xbuf = g_lds + kSliceXOff + (uint32_t)slice * 2u * kSliceXBuf<TT>;
 
-    // staging role of this thread: token (thread / 2) of the pass, block (thread % 2) of the pair
-    const bool s_on = (int)(threadIdx.x >> 1) < kPrefillTokens;          // with more threads than staging work the rest sit out
-    const int s_tok = min(M - 1, m0 + min((int)(threadIdx.x >> 1), kPrefillTokens - 1));
-    const uint32_t s_part = threadIdx.x & 1u;
-    const uint32_t* s_src = x + (size_t)s_tok * xpitch;
-    unsigned char* s_dst = abuf + (uint32_t)min((int)(threadIdx.x >> 1), kPrefillTokens - 1) * kATokenPitch + s_part * 48u;
-    auto stage_load = [&](uint32_t st, uint4 (&v)[3]) {
-        const uint32_t b = min(2 * st + s_part, (uint32_t)KB - 1);       // past the last block: any valid data, its weights are zero
-        const uint4* p = reinterpret_cast<const uint4*>(s_src + (size_t)b * 12);
-        v[0] = p[0]; v[1] = p[1]; v[2] = p[2];
+    // steps (block pairs) of this part of the rows, dealt to the slices in turn
+    const uint32_t spt = ((uint32_t)KB + 1) / 2;
+    const uint32_t st0 = (uint32_t)(((uint64_t)spt * blockIdx.z) / (uint32_t)ksplit) + (uint32_t)slice;
+    const uint32_t st1 = (uint32_t)(((uint64_t)spt * (blockIdx.z + 1)) / (uint32_t)ksplit);
+    const uint32_t nsteps = st0 < st1 ? (st1 - st0 + kSlices - 1) / kSlices : 0;
+    const int row0 = strip * (32 * kTiles);
+    const int wrow = row0 + 32 * tile + col;
+    const int m0 = (int)blockIdx.y * (32 * TT);
+    const uint32_t xpitch = (uint32_t)KB * 12u;                       // dwords per activation row
+
+    // staging: the two blocks of a step are 96 contiguous bytes of a token row, six pieces of 16; load i fetches pieces 2 i and
+    // 2 i + 1 of all 32 tokens (two neighbouring lanes per token) to i * 1024 + token * 32
+    const uint32_t s_row = (uint32_t)min(M - 1, m0 + 32 * tile + (lane >> 1)) * xpitch, s_odd = (uint32_t)(lane & 1) * 4u;
+    auto stage = [&](uint32_t st, uint32_t buf) {
+#pragma unroll
+        for (int i = 0; i < 3; i++) {
+            const uint32_t off = s_row + min(st * 24u + 8u * i + s_odd, xpitch - 4u);    // past the last block: any valid data, its weights are zero
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (size_t)off),
+                                             (__attribute__((address_space(3))) void*)(xbuf + buf * kSliceXBuf<TT> + (uint32_t)tile * 3072u + i * 1024), 16, 0, 0);
+        }
     };
-    auto stage_store = [&](uint32_t buf, const uint4 (&v)[3]) {
-        if (!s_on) return;
-        uint4* d = reinterpret_cast<uint4*>(s_dst + buf * kABufBytes);
-        d[0] = v[0]; d[1] = v[1]; d[2] = v[2];
+    typedef volatile __attribute__((address_space(3))) uint32_t* Counter;
+    const Counter ready = (Counter)(flags + slice), done = (Counter)(flags + kSlices + slice);
+    auto wait_for = [&](Counter counter, uint32_t target) {
+        while ((uint32_t)__builtin_amdgcn_readfirstlane(*counter) < target) __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+    };
+    // LDS operations of a wave execute in order: what it read or waited for before is finished when the count changes.
+    // (In assembly: before an LDS atomic that it knows the compiler waits for every global-to-LDS load in flight.)
+    auto count = [&](int which) {
+        if (lane == 0) asm volatile("ds_add_u32 %0, %1" ::"v"(kSliceFlagOff<TT> + 4u * (uint32_t)which), "v"(1u) : "memory");
+    };
+
+    struct Blk { RawBlock raw; bool live; };
+    // the strip's first word and gain (scalars) and this lane's row inside the strip
+    const size_t blk0 = (size_t)row0 * (size_t)KB;
+    const unsigned char* idx0 = reinterpret_cast<const unsigned char*>(idx) + blk0 * kWordBytes<FMT>;
+    const uint16_t* gain0 = cd.gain_array() ? gain + blk0 : reinterpret_cast<const uint16_t*>(idx0);
+    const uint32_t kl0 = (uint32_t)(min(wrow, N - 1) - row0) * (uint32_t)KB;           // at most 127 rows of fewer than 2^24 blocks
+    auto fetch_blk = [&](uint32_t st, Blk& q) {
+        const uint32_t b = 2 * st + (uint32_t)half;
+        q.live = wrow < N && b < (uint32_t)KB;
+        load_raw<FMT>(idx0, gain0, true, (size_t)(kl0 + min(b, (uint32_t)KB - 1)), q.raw);
+    };
+    auto front_of = [&](const Blk& q, bool& ok, uint16_t& gb) {
+        uint64_t I;
+        finish_block<FMT>(q.raw, cd, I, gb);
+        ok = q.live && I < T.npoints;
+        return llvq::decode_front<true, true, true>(T, llvq::find_class(T, ok ? I : 0));
     };
 
     float16_t acc[TT];
@@ -1135,87 +1017,93 @@ __global__ void __launch_bounds__(64 * WAVES) prefill_kernel(const unsigned char
 #pragma unroll
         for (int v = 0; v < 16; v++) acc[t][v] = 0.0f;
     }
-    // Software pipeline over the steps: the word of the next step is requested first, then this step's block is placed,
-    // then the next step's class search and digit extraction run (their reads from global memory are in flight during
-    // the matrix products), then the products of this step, then the next activation tile is put into LDS.
-    struct Blk { RawBlock raw; bool live; };
-    auto fetch_blk = [&](uint32_t st, Blk& q) {
-        const uint32_t b = 2 * st + half;
-        q.live = wrow < N && b < (uint32_t)KB;
-        const size_t k = (size_t)min(wrow, N - 1) * KB + min(b, (uint32_t)KB - 1);
-        load_raw<FMT>(idx, gain, cd.gain_array(), k, q.raw);
-    };
-    auto front_of = [&](const Blk& q, bool& ok, uint16_t& gb) {
-        uint64_t I;
-        finish_block<FMT>(q.raw, cd, I, gb);
-        ok = q.live && I < T.npoints;
-        return llvq::decode_front<true>(T, llvq::find_class(T, ok ? I : 0));
-    };
-    {
-        uint4 v[3];
-        stage_load(st_first, v);
-        stage_store(st_first & 1u, v);
-    }
-    Blk cur_blk, nxt_blk;
-    fetch_blk(st_first, cur_blk);
-    bool ok_cur = false, ok_nxt = false;
-    uint16_t g_cur = 0, g_nxt = 0;
-    llvq::Front F = front_of(cur_blk, ok_cur, g_cur), Fn;
-    __syncthreads();
-    for (uint32_t st = st_first; st < spt; st++) {
-        const uint32_t st_next = st + 1 < spt ? st + 1 : st;            // past the end the last step is requested again
-        uint4 nextv[3];
-        stage_load(st_next, nextv);
-        fetch_blk(st_next, nxt_blk);
-        uint32_t w[4];
-        const llvq::BlockInfo bi = llvq::decode_back(T, F, w);
-        const float scale = ok_cur ? __half2float(__ushort_as_half(g_cur)) * bi.rnorm : 0.0f;
-        constexpr int kTerms = Mma<X2>::kTerms;
-        uint32_t wt[kTerms][12];
+    if (nsteps) {
+        const uint32_t st_last = st0 + (nsteps - 1) * kSlices;
+        Blk blk;
+        fetch_blk(st0, blk);
+        if (tile < TT) stage(st0, 0);
+        bool ok = false;
+        uint16_t gb = 0;
+        llvq::Front F = front_of(blk, ok, gb);
+        fetch_blk(min(st0 + kSlices, st_last), blk);
+        uint32_t st = st0;
+        for (uint32_t n = 0; n < nsteps; n++, st += kSlices) {
+            uint32_t w[4];
+            const llvq::BlockInfo bi = llvq::decode_back(T, F, w);
+            const float scale = ok ? __half2float(__ushort_as_half(gb)) * bi.rnorm : 0.0f;
+            uint32_t wt[kTerms][12];
 #pragma unroll
-        for (int c = 0; c < 4; c++) {
-            uint32_t fe, fo, o[kTerms];
-            chunk_fp8(w[c], bi.vt8_lo, bi.vt8_hi, fe, fo);
-            Mma<X2>::weights(fe, false, scale, o);
+            for (int c = 0; c < 4; c++) {
+                uint32_t fe, fo, o[kTerms];
+                chunk_fp8(w[c], bi.vt8_lo, bi.vt8_hi, fe, fo);
+                Mma<X2>::weights(fe, false, scale, o);
 #pragma unroll
-            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
-            Mma<X2>::weights(fo, false, scale, o);
+                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
+                Mma<X2>::weights(fo, false, scale, o);
 #pragma unroll
-            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
-            Mma<X2>::weights(fe, true, scale, o);
+                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
+                Mma<X2>::weights(fe, true, scale, o);
 #pragma unroll
-            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
-        }
-        Fn = front_of(nxt_blk, ok_nxt, g_nxt);
-        // A operands from the staged tile: token 32 t + col, the lane half's block (48 bytes), k group j
-        const unsigned char* arow = abuf + (st & 1u) * kABufBytes + (uint32_t)col * kATokenPitch + (uint32_t)half * 48u;
-        // k group outermost: consecutive MFMAs go to different accumulators and do not wait for each other
-#pragma unroll
-        for (int j = 0; j < 3; j++) {
-#pragma unroll
-            for (int t = 0; t < TT; t++) {
-                const u32x4 a = *reinterpret_cast<const u32x4*>(arow + (uint32_t)t * 32u * kATokenPitch + (uint32_t)j * 16u);
-#pragma unroll
-                for (int r = 0; r < kTerms; r++)
-                    acc[t] = Mma<X2>::mma(a, u32x4{wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]}, acc[t]);
+                for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
             }
+            // the other buffer takes the next step once every wave of the slice is done with the step before this one
+            if (tile < TT) {
+                if (n + 1 < nsteps) {
+                    wait_for(done, n * kTiles);
+                    stage(st + kSlices, (n + 1) & 1u);
+                    __builtin_amdgcn_s_waitcnt(3 | (7 << 4) | (15 << 8));          // vmcnt(3): all but the three loads just issued have landed
+                } else {
+                    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));          // vmcnt(0)
+                }
+                count(slice);
+            }
+            wait_for(ready, (n + 1) * TT);
+            // channels 8 j .. + 7 of block `half` are piece 3 half + j of the token's row
+            const unsigned char* arow = xbuf + (n & 1u) * kSliceXBuf<TT> + (uint32_t)col * 32u;
+#pragma unroll
+            for (int j = 0; j < 3; j++) {
+                const uint32_t piece = half ? 3u + j : (uint32_t)j;
+                u32x4 a[TT];
+#pragma unroll
+                for (int t = 0; t < TT; t++) a[t] = *reinterpret_cast<const u32x4*>(arow + (uint32_t)t * 3072u + (piece >> 1) * 1024u + (piece & 1u) * 16u);
+#pragma unroll
+                for (int r = 0; r < kTerms; r++) {
+                    const u32x4 b = {wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]};
+#pragma unroll
+                    for (int t = 0; t < TT; t++) acc[t] = Mma<X2>::mma(a[t], b, acc[t]);
+                }
+            }
+            count(kSlices + slice);
+            // class search and digits of the next step (past the end the last one again: decoded, never used); after the
+            // products, so that neither the weights nor this block's digits are live in the other part
+            F = front_of(blk, ok, gb);
+            fetch_blk(min(st + 2 * kSlices, st_last), blk);
         }
-        stage_store((st + 1) & 1u, nextv);
-        F = Fn;
-        ok_cur = ok_nxt;
-        g_cur = g_nxt;
-        __syncthreads();
     }
-    // y[token][wrow]: register v of tile t belongs to token m0 + 32 t + 8 (v / 4) + 4 half + v % 4
-    if (wrow < N) {
+    __syncthreads();                                                 // tables and activation tiles are not needed any more
+    // One token tile at a time: every wave writes its 32 x 32 partial tile, thread u adds quarter-column u % 256 of row tile
+    // u / 256 over the slices in a fixed order.  Register v of a tile belongs to token 8 (v / 4) + 4 half + v % 4 and row col.
 #pragma unroll
-        for (int t = 0; t < TT; t++) {
+    for (int t = 0; t < TT; t++) {
+        float4_t* slots = reinterpret_cast<float4_t*>(g_lds + (t & 1) * 65536);
 #pragma unroll
-            for (int v = 0; v < 16; v++) {
-                const int tok = m0 + 32 * t + 8 * (v / 4) + 4 * half + (v % 4);
-                if (tok < M) {
-                    if (ksplit == 1) y[(size_t)tok * N + wrow] = acc[t][v];
-                    else atomicAdd(y + (size_t)tok * N + wrow, acc[t][v]);
+        for (int q = 0; q < 4; q++)
+            slots[wave * 256 + q * 64 + lane] = float4_t{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+        __syncthreads();
+        const int u = threadIdx.x & 255, rt = threadIdx.x >> 8;
+        if (rt < kTiles) {
+            float4_t sum = slots[rt * 256 + u];
+#pragma unroll
+            for (int sl = 1; sl < kSlices; sl++) sum += slots[(sl * kTiles + rt) * 256 + u];
+            const int row = row0 + 32 * rt + (u & 31), tok = m0 + 32 * t + 8 * (u >> 6) + 4 * ((u >> 5) & 1);
+            if (row < N) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    if (tok + i < M) {
+                        float* dst = y + (size_t)(tok + i) * N + row;
+                        if (ksplit == 1) *dst = sum[i];
+                        else atomicAdd(dst, sum[i]);
+                    }
                 }
             }
         }
@@ -1743,25 +1631,6 @@ static int launch_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_id
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "matmul launch");
 }
 
-template <int FMT, typename X2, int THREADS, int TOKTILES, bool MULTI = false>
-static int launch_mfma_cfg(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
-                           const MatItems& items = MatItems{}) {
-    // workgroups = groups of row tiles (one tile per wave) x ranges of block pairs; enough ranges to fill the chip, but
-    // at least two steps each to amortise the write-back of a partial tile
-    constexpr uint32_t wpg = THREADS / 64;
-    const uint32_t n_rt = MULTI ? (uint32_t)items.tile_end[kMaxItems - 1] : (uint32_t)((N + 31) / 32), spt = (uint32_t)((KB + 1) / 2);
-    const uint32_t groups = (n_rt + wpg - 1) / wpg;
-    uint32_t kranges = (uint32_t)ctx->num_cu / groups;
-    kranges = std::max(1u, std::min(kranges, std::max(1u, spt / 2)));
-    kranges = std::min(kranges, 65535u);
-    const size_t lds = ctx->lay.blob_bytes;
-    if (int rc = set_lds<mfma_kernel<FMT, X2, THREADS, TOKTILES, MULTI>>(ctx, lds)) return rc;
-    hipLaunchKernelGGL((mfma_kernel<FMT, X2, THREADS, TOKTILES, MULTI>), dim3(groups, kranges), dim3(THREADS), lds, st, ctx->d_blob, ctx->lay, d_idx,
-                       reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, kranges, items, d_y);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "mfma matmul launch");
-}
-
 constexpr int kTileMaxM = 32;       // up to this many activation rows the batched-decode kernel with row tiles per workgroup is used
 
 template <int FMT, typename X2, int TT, bool MULTI = false, class LAY = Lay13>
@@ -1837,48 +1706,81 @@ static int launch_repack(const void* d_idx, const void* d_gain, size_t n, uint64
     return 0;
 }
 
-template <int FMT, typename X2, int WAVES, int TT>
-static int launch_prefill(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st) {
-    constexpr int kRows = 32 * WAVES, kTokens = 32 * TT;
-    const unsigned strips = (unsigned)((N + kRows - 1) / kRows), passes = (unsigned)((M + kTokens - 1) / kTokens);
-    // enough workgroups for the chip: split the block pairs of a row among up to ksplit workgroups (at least 8 steps each)
-    const unsigned spt = ((unsigned)KB + 1) / 2;
-    unsigned ksplit = (unsigned)ctx->num_cu / (strips * passes);
-    ksplit = std::max(1u, std::min(ksplit, std::max(1u, spt / 8)));
-    if (ksplit > 1) {
+// strips of `rows` rows, every matrix of `items` rounded up
+static int set_strips(MatItems& items, int rows) {
+    int end = 0;
+    for (int i = 0; i < kMaxItems; i++) {
+        end += (items.row_end[i] - (i ? items.row_end[i - 1] : 0) + rows - 1) / rows;
+        items.strip_end[i] = end;
+    }
+    return end;
+}
+
+// clears y before a launch that adds to it: one matrix, or all matrices of `items`
+static void clear_y(const MatItems* items, int n_items, int M, int N, float* d_y, hipStream_t st) {
+    if (items) {
+        int widest = 0;
+        for (int i = 0; i < n_items; i++) widest = std::max(widest, items->row_end[i] - (i ? items->row_end[i - 1] : 0));
+        const size_t ny = (size_t)M * (size_t)widest;
+        hipLaunchKernelGGL(fill_multi_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 2048), (unsigned)n_items), dim3(256), 0, st, *items, M, 0.0f);
+    } else {
         const size_t ny = (size_t)M * N;
         hipLaunchKernelGGL(fill_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 4096)), dim3(256), 0, st, d_y, ny, 0.0f);
     }
-    const dim3 grid(strips, passes, ksplit);
-    const size_t lds = ctx->lay.lds_bytes + 2 * (size_t)kTokens * kATokenPitch;
-    if (int rc = set_lds<prefill_kernel<FMT, X2, WAVES, TT>>(ctx, lds)) return rc;
-    hipLaunchKernelGGL((prefill_kernel<FMT, X2, WAVES, TT>), grid, dim3(64 * WAVES), lds, st, ctx->d_blob, ctx->lay, d_idx,
-                       reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, (int)ksplit, d_y);
+}
+
+// How many workgroups share the block pairs of a row in slice_kernel.  Estimated time in us: rounds of workgroups x (steps of
+// a slice x the time of a step + tables and final sum), and, when the rows are split, 335 atomics per ns and the clearing
+// of y (all measured).
+static int slice_ksplit(const llvq_ctx* ctx, int TT, int slices, uint64_t wgs, int KB, int M, uint64_t rows) {
+    const uint64_t spt = ((uint64_t)KB + 1) / 2;
+    const double step = TT == 2 ? 2.7 : TT == 3 ? 3.1 : 3.6;
+    double best = 0.0;
+    int ks_best = 1;
+    for (uint64_t ks = 1; ks <= 64 && (ks == 1 || ks * slices <= spt); ks++) {
+        const uint64_t rounds = (wgs * ks + ctx->num_cu - 1) / ctx->num_cu;
+        const double t = (double)rounds * ((double)((spt + ks * slices - 1) / (ks * slices)) * step + 6.0) +
+                         (ks > 1 ? (double)ks * (double)M * (double)rows / 335e3 + 3.0 : 0.0);
+        if (ks == 1 || t < best) { best = t; ks_best = (int)ks; }
+    }
+    return ks_best;
+}
+
+template <int FMT, typename X2, int TT, bool MULTI>
+static int launch_slice_cfg(llvq_ctx* ctx, const void* d_x, int M, int passes, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
+                            MatItems items, int n_items) {
+    constexpr int kRows = 32 * kSliceTiles<TT>;
+    const int strips = MULTI ? set_strips(items, kRows) : (N + kRows - 1) / kRows;
+    const int ksplit = slice_ksplit(ctx, TT, 16 / kSliceTiles<TT>, (uint64_t)strips * passes, KB, M, (uint64_t)N);
+    if (ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
+    if (int rc = set_lds<slice_kernel<FMT, X2, TT, MULTI>>(ctx, kSliceLds<TT>)) return rc;
+    hipLaunchKernelGGL((slice_kernel<FMT, X2, TT, MULTI>), dim3((unsigned)strips, (unsigned)passes, (unsigned)ksplit), dim3(kThreads), kSliceLds<TT>, st,
+                       ctx->d_blob, ctx->lay, d_idx, reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, ksplit, items, d_y);
     hipError_t e = hipGetLastError();
-    return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "prefill matmul launch");
+    return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "slice matmul launch");
+}
+
+// passes of at most 128 tokens, as even as token tiles of 32 allow
+template <int FMT, typename X2, bool MULTI = false>
+static int launch_slice(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
+                        const MatItems& items = MatItems{}, int n_items = 1) {
+    const int tiles = (M + 31) / 32, passes = (tiles + 3) / 4, per_pass = (tiles + passes - 1) / passes;
+    if (per_pass <= 2) return launch_slice_cfg<FMT, X2, 2, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+    if (per_pass == 3) return launch_slice_cfg<FMT, X2, 3, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+    return launch_slice_cfg<FMT, X2, 4, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
 }
 
 // MULTI: N is not used; the strips are those of `items`
 template <int FMT, typename X2, bool MULTI = false>
 static int launch_panel(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
-                        const MatItems& items = MatItems{}, int n_items = 1) {
-    const unsigned strips = MULTI ? (unsigned)items.strip_end[kMaxItems - 1] : (unsigned)((N + kPanelRows - 1) / kPanelRows);
+                        MatItems items = MatItems{}, int n_items = 1) {
+    const unsigned strips = MULTI ? (unsigned)set_strips(items, kPanelRows) : (unsigned)((N + kPanelRows - 1) / kPanelRows);
     const unsigned passes = (unsigned)((M + kPanelTokens - 1) / kPanelTokens);
     // enough workgroups for the chip: split the block pairs of a row among up to ksplit workgroups (at least 16 steps each)
     const unsigned spt = ((unsigned)KB + 1) / 2;
     unsigned ksplit = (unsigned)ctx->num_cu / (strips * passes);
     ksplit = std::max(1u, std::min(ksplit, std::max(1u, spt / 16)));
-    if (ksplit > 1) {
-        if (MULTI) {
-            int widest = 0;
-            for (int i = 0; i < n_items; i++) widest = std::max(widest, items.row_end[i] - (i ? items.row_end[i - 1] : 0));
-            const size_t ny = (size_t)M * (size_t)widest;
-            hipLaunchKernelGGL(fill_multi_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 2048), (unsigned)n_items), dim3(256), 0, st, items, M, 0.0f);
-        } else {
-            const size_t ny = (size_t)M * N;
-            hipLaunchKernelGGL(fill_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 4096)), dim3(256), 0, st, d_y, ny, 0.0f);
-        }
-    }
+    if (ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
     const dim3 grid(strips, passes, ksplit);
     constexpr int kTerms = Mma<X2>::kTerms;
     const size_t lds = ctx->lay.lds_bytes + (size_t)(kTerms == 1 ? 2 : 1) * (4 * 3 * 1024 * kTerms) + (size_t)kPanelWaves * 7 * 1024;
@@ -1903,12 +1805,9 @@ static int launch_any_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* 
     if (M < kMfmaMinM) return launch_matmul<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (panel_fits(ctx, M, (uint64_t)((N + kPanelRows - 1) / kPanelRows), KB))
         return launch_panel<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
-    if (M > 64) return launch_prefill<FMT, X2, 8, 8>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= 16) return launch_tile<FMT, X2, 1>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= kTileMaxM) return launch_tile<FMT, X2, 2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
-    const size_t ny = (size_t)M * N;
-    hipLaunchKernelGGL(fill_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 4096)), dim3(256), 0, st, d_y, ny, 0.0f);
-    return launch_mfma_cfg<FMT, X2, 1024, 2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+    return launch_slice<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
 }
 
 // evaluates EXPR with the constant F set to the storage format `fmt` (which check_idx has accepted)
@@ -2009,17 +1908,15 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
         if (tiles * (size_t)((KB + 1) / 2) >= (1ull << 32) || (size_t)M * (size_t)KB * 12 >= (1ull << 32)) return LLVQ_EINVAL;
     }
     MatItems items;
-    int rows = 0, tiles = 0, tiles16 = 0, strips = 0;
+    int rows = 0, tiles16 = 0, strips = 0;
     for (int i = 0; i < kMaxItems; i++) {
         const int k = i < n_items ? i : n_items - 1;
-        if (i < n_items) { rows += N[i]; tiles += (N[i] + 31) / 32; tiles16 += (N[i] + kTileRows - 1) / kTileRows; strips += (N[i] + kPanelRows - 1) / kPanelRows; }
+        if (i < n_items) { rows += N[i]; tiles16 += (N[i] + kTileRows - 1) / kTileRows; strips += (N[i] + kPanelRows - 1) / kPanelRows; }
         items.tile16_end[i] = tiles16;
-        items.strip_end[i] = strips;
         items.idx[i] = d_idx[k];
         items.gain[i] = reinterpret_cast<const uint16_t*>(d_gain[k]);
         items.y[i] = d_y[k];
         items.row_end[i] = rows;
-        items.tile_end[i] = tiles;
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     // prefill: the 128-row strips of all matrices in one launch when at least one of them has panels for less than half
@@ -2033,8 +1930,8 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
             return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
         return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
-    if (n_items == 1 || M > 64) {
-        // one matrix, or a batch that takes the strip kernel: one product after the other
+    if (n_items == 1 || panel_fits(ctx, M, 1u << 20, KB)) {
+        // one matrix, or matrices that take the panel kernel each on its own: one product after the other
         for (int i = 0; i < n_items; i++)
             if (int rc = matmul_impl(ctx, d_x, x_dtype, M, d_idx[i], fmt, d_gain[i], cd, N[i], KB, d_y[i], stream)) return rc;
         return LLVQ_OK;
@@ -2049,14 +1946,10 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
         return LLVQ_BY_FMT(fmt, (launch_tile<F, bf16x2_t, 2, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items)));
     }
     if (M >= kMfmaMinM) {
-        // the batched-decode kernel over the row tiles of all matrices; the outputs are cleared by one launch as well
-        int widest = 0;
-        for (int i = 0; i < n_items; i++) widest = std::max(widest, N[i]);
-        const size_t ny = (size_t)M * (size_t)widest;
-        hipLaunchKernelGGL(fill_multi_kernel, dim3((unsigned)std::min<size_t>((ny / 4 + 256) / 256, 2048), (unsigned)n_items), dim3(256), 0, st, items, M, 0.0f);
+        // the row strips of all matrices in one launch
         if (x_dtype == LLVQ_F16)
-            return LLVQ_BY_FMT(fmt, (launch_mfma_cfg<F, half2_t, 1024, 2, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items)));
-        return LLVQ_BY_FMT(fmt, (launch_mfma_cfg<F, bf16x2_t, 1024, 2, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items)));
+            return LLVQ_BY_FMT(fmt, (launch_slice<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
+        return LLVQ_BY_FMT(fmt, (launch_slice<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
     if (x_dtype == LLVQ_F16)
         return LLVQ_BY_FMT(fmt, (launch_matmul<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items)));

@@ -374,10 +374,10 @@ bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const
     std::vector<double> atab = {1.0, 1.0, 759.0, (1.0 / 759.0) * (1.0 + std::ldexp(1.0, -50)),
                                 2576.0, (1.0 / 2576.0) * (1.0 + std::ldexp(1.0, -50)), 4096.0, 1.0 / 4096.0};
     const uint64_t inner_end = LAY::kOffInner + (uint64_t)D.inner.size() * sizeof(uint32_t);
-    const uint32_t cls_end = LAY::kWide ? Lay19::kOffWideRec : Lay13::kLdsBytes, split_end = LAY::kWide ? Lay19::kLdsBytes : Lay13::kOffCls;
+    const uint32_t cls_end = LAY::kWide ? Lay19::kOffWideRec : Lay13::kOffSpread6;
     if (D.guess.size() > LAY::kOffAtab - LAY::kOffGuess || cls_off.size() * 8 > LAY::kOffRnorm - LAY::kOffClsOff ||
         (size_t)(m_max + 1) * sizeof(float) > LAY::kOffSplit - LAY::kOffRnorm ||
-        (D.split.size() + 1) * sizeof(SplitEnt) > split_end - LAY::kOffSplit || recs.size() * sizeof(ClassRec) > cls_end - LAY::kOffCls ||
+        (D.split.size() + 1) * sizeof(SplitEnt) > LAY::kLdsBytes - LAY::kOffSplit || recs.size() * sizeof(ClassRec) > cls_end - LAY::kOffCls ||
         npoints > (4096ull << LAY::kBucketShift) || inner_end > LAY::kMaxBlob)
         return false;
     blob.assign((inner_end + 15u) & ~(uint64_t)15u, 0);

@@ -66,20 +66,20 @@ constexpr uint32_t kSpreadPitch = 65;      // dwords per mask row of spread6: en
 constexpr uint32_t kPdepPitch  = 68;       // bytes per mask row of pdep6 (17 dwords, for the same reason)
 struct Lay13 {
     static constexpr bool kWide = false;
-    static constexpr uint32_t kOffSpread6 = 0;        // 64 x 65 x u32
-    static constexpr uint32_t kOffPdep6   = 16640;    // 64 x 68 x u8
-    static constexpr uint32_t kOffLut12   = 20992;    // 4096 x u16
-    static constexpr uint32_t kOffBucket  = 29184;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
-    static constexpr uint32_t kOffGuess   = 37376;    // up to 48 rows x 64 x u8
-    static constexpr uint32_t kOffAtab    = 40448;    // 4 x {A, 1/A} doubles
-    static constexpr uint32_t kOffClsOff  = 40512;    // (ncls + 4) x u64, ncls <= 383: offsets, N, and three entries above every index
-    static constexpr uint32_t kOffRnorm   = 43616;    // 16 x float: 1/sqrt(16 m)
-    static constexpr uint32_t kOffSplit   = 43680;    // up to 352 x SplitEnt
-    static constexpr uint32_t kOffCls     = 49312;    // ncls x ClassRec
-    static constexpr uint32_t kLdsBytes   = 67712;    // end of the LDS-resident part
-    static constexpr uint32_t kOffGs      = 67712;    // 4096 x u32 (global memory)
-    static constexpr uint32_t kOffInner   = 84096;    // inner-word planes, u32 (global memory)
-    static constexpr uint32_t kMaxBlob    = 84096 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
+    static constexpr uint32_t kOffCls     = 0;        // ncls x ClassRec, ncls <= 383
+    static constexpr uint32_t kOffSpread6 = 18432;    // 64 x 65 x u32 (first table of the kernels that read the records from global memory)
+    static constexpr uint32_t kOffPdep6   = 35072;    // 64 x 68 x u8
+    static constexpr uint32_t kOffLut12   = 39424;    // 4096 x u16
+    static constexpr uint32_t kOffBucket  = 47616;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
+    static constexpr uint32_t kOffGuess   = 55808;    // up to 48 rows x 64 x u8
+    static constexpr uint32_t kOffAtab    = 58880;    // 4 x {A, 1/A} doubles
+    static constexpr uint32_t kOffClsOff  = 58944;    // (ncls + 4) x u64: offsets, N, and three entries above every index
+    static constexpr uint32_t kOffRnorm   = 62048;    // 16 x float: 1/sqrt(16 m)
+    static constexpr uint32_t kOffSplit   = 62112;    // up to 188 x SplitEnt
+    static constexpr uint32_t kLdsBytes   = 65120;    // end of the tables that every kernel keeps in LDS
+    static constexpr uint32_t kOffGs      = 65120;    // 4096 x u32
+    static constexpr uint32_t kOffInner   = 81504;    // inner-word planes, u32
+    static constexpr uint32_t kMaxBlob    = 81504 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
     static constexpr uint32_t kBucketShift = 36;      // bucket index = I >> 36 (4096 buckets cover 48 bits)
     static constexpr uint64_t kWordMask   = (1ull << 48) - 1;    // bits of a 64-bit word that hold index and gain code
 };
