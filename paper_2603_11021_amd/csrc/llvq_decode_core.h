@@ -182,7 +182,7 @@ struct BlockInfo {
 
 // App. A steps 1-2: shell and class of an index (< npoints) in one search over the global class offsets
 struct ClassHit {
-    uint32_t cid;     // class id
+    uint32_t c8;      // 8 x class id
     uint64_t Ic;      // index inside the class
 };
 
@@ -203,7 +203,7 @@ LLVQ_HD ClassHit find_class(const TabPtrsOf<LAY>& T, uint64_t I) {
         if (!wave_or(p3)) break;
     }
     ClassHit h;
-    h.cid = c8 >> 3;
+    h.c8 = c8;
     h.Ic = I - tab_at<uint64_t, LAY::kOffClsOff>(T, c8);
     return h;
 }
@@ -222,12 +222,13 @@ struct Front {
 
 // BIG_GLOBAL: the Golay words and the inner-word planes are read from global memory instead of LDS
 // (GS_LDS: only the inner-word planes are; the kernel has copied the blob up to LAY::kOffInner);
-// REC_GLOBAL: so is the class record
+// REC_GLOBAL: so is the class record (Lay19: and its values)
 template <bool BIG_GLOBAL = false, bool REC_GLOBAL = false, bool GS_LDS = false, class LAY = Lay13>
 LLVQ_HD Front decode_front(const TabPtrsOf<LAY>& T, const ClassHit& hit) {
     Front F;
-    const ClassRec R = REC_GLOBAL ? gtab_at<ClassRec, LAY::kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)))
-                                  : tab_at<ClassRec, LAY::kOffCls>(T, mul24(hit.cid, (uint32_t)sizeof(ClassRec)));
+    const ClassRec R = REC_GLOBAL ? gtab_at<ClassRec, LAY::kOffCls>(T, hit.c8 * 4u) : tab_at<ClassRec, LAY::kOffCls>(T, hit.c8 * 4u);
+    const ClassVals v8 = REC_GLOBAL && LAY::kWide ? gtab_at<ClassVals, LAY::kOffVt8>(T, hit.c8) : tab_at<ClassVals, LAY::kOffVt8>(T, hit.c8);
+    const ClassVals vi = REC_GLOBAL && LAY::kWide ? gtab_at<ClassVals, LAY::kOffVti>(T, hit.c8) : tab_at<ClassVals, LAY::kOffVti>(T, hit.c8);
     const uint32_t f0 = R.f0, f1 = R.f1;
     // r = Ic mod A, then B sign bits, then the permutation rank I''.  All quotients are exact: the operands are
     // integers below 2^48 held in doubles and the reciprocals are nudged upwards.
@@ -257,8 +258,8 @@ LLVQ_HD Front decode_front(const TabPtrsOf<LAY>& T, const ClassHit& hit) {
     if constexpr (LAY::kWide) { if ((f1 >> F1_STEPS) & 1u) F.e0 = rin; }
     const uint32_t j = tab_at<uint8_t, LAY::kOffGuess>(T, ((f1 >> F1_GROW) & 63u) * kGuessBuckets + (F.d >> ((f1 >> F1_GSHIFT) & 31u)));
     F.sp_j = (uint32_t)(uint16_t)(R.sp + j) | (j << 16);
-    F.cid = hit.cid; F.f0 = f0; F.f1 = f1;
-    F.vt8_lo = R.vt8_lo; F.vt8_hi = R.vt8_hi; F.vti_lo = R.vti_lo; F.vti_hi = R.vti_hi;
+    F.cid = hit.c8 >> 3; F.f0 = f0; F.f1 = f1;
+    F.vt8_lo = v8.lo; F.vt8_hi = v8.hi; F.vti_lo = vi.lo; F.vti_hi = vi.hi;
     F.rnorm = tab_at<float, LAY::kOffRnorm>(T, (f0 >> (F0_M - 2)) & (LAY::kWide ? 124u : 60u));
     return F;
 }

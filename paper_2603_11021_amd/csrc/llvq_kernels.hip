@@ -189,7 +189,14 @@ __device__ __forceinline__ void finish_block(const RawBlock& r, const Code& cd, 
     if constexpr (FMT == LLVQ_IDX_U64) v = ((uint64_t)r.a | ((uint64_t)r.b << 32)) & LAY::kWordMask;
     else if constexpr (FMT == LLVQ_IDX_U24) v = (uint64_t)(r.a | (r.b << 8) | (r.c << 16));
     else v = (uint64_t)r.a | ((uint64_t)r.c << 32);
-    g = cd.lut ? cd.lut[min((uint32_t)(v >> cd.shape_bits), cd.lut_last)] : r.g;
+    g = r.g;
+    if (cd.lut) {
+        // the wait for the table's answer stays inside this branch: left in flight, it made the compiler wait for every load
+        // outstanding wherever the two paths' values of g are copied, also in launches without a table
+        uint32_t gl = cd.lut[min((uint32_t)(v >> cd.shape_bits), cd.lut_last)];
+        asm volatile("" : "+v"(gl));
+        g = (uint16_t)gl;
+    }
     if constexpr (FMT == LLVQ_IDX_U64) { if (cd.gain_in_word) g = (uint16_t)(r.b >> 16); }
     I = (v & cd.mask) + cd.base;
 }
@@ -922,7 +929,7 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
 // Llama-3-8B-shaped block (seven layers, fp16): M = 64 XX -> XX us, M = 128 XX -> XX us, M = 256 XX -> XX us against the
 // split-K kernel and the strip kernel with two waves per SIMD.
 template <int TT> constexpr int kSliceTiles = TT <= 2 ? 2 : 4;           // 32-row tiles per workgroup
-constexpr uint32_t kSliceTabBytes = Lay13::kOffInner - Lay13::kOffSpread6;                 // small tables and Golay words; class records and planes in global memory
+constexpr uint32_t kSliceTabBytes = Lay13::kOffGs - Lay13::kOffVt8;                        // class records and small tables; Golay words and planes in global memory
 constexpr uint32_t kSliceXOff = (kSliceTabBytes + 511u) & ~511u;
 template <int TT> constexpr uint32_t kSliceXBuf = TT * 3072u;                              // one step of one slice: 32 TT tokens x 96 bytes
 template <int TT> constexpr uint32_t kSliceFlagOff = kSliceXOff + 2u * (16 / kSliceTiles<TT>) * kSliceXBuf<TT>;
@@ -956,27 +963,32 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
     const int col = lane & 31, half = lane >> 5;
     uint32_t* flags = reinterpret_cast<uint32_t*>(g_lds + kSliceFlagOff<TT>);                  // ready[kSlices], done[kSlices]
     if (threadIdx.x < 2 * kSlices) flags[threadIdx.x] = 0;                                     // published by the barrier of load_tables
-    load_tables(blob + Lay13::kOffSpread6, kSliceTabBytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin() - Lay13::kOffSpread6, blob, lay);
+    load_tables(blob + Lay13::kOffVt8, kSliceTabBytes);
+    const TabPtrs T = llvq::make_tab_ptrs(lds_origin() - Lay13::kOffVt8, blob, lay);
     unsigned char* xbuf = g_lds + kSliceXOff + (uint32_t)slice * 2u * kSliceXBuf<TT>;
 
-    // steps (block pairs) of this part of the rows, dealt to the slices in turn
+    // steps (block pairs) of a row, cut into one run per slice of every workgroup that shares the row
     const uint32_t spt = ((uint32_t)KB + 1) / 2;
-    const uint32_t st0 = (uint32_t)(((uint64_t)spt * blockIdx.z) / (uint32_t)ksplit) + (uint32_t)slice;
-    const uint32_t st1 = (uint32_t)(((uint64_t)spt * (blockIdx.z + 1)) / (uint32_t)ksplit);
-    const uint32_t nsteps = st0 < st1 ? (st1 - st0 + kSlices - 1) / kSlices : 0;
+    const uint32_t part = blockIdx.z * (uint32_t)kSlices + (uint32_t)slice, parts = (uint32_t)(ksplit * kSlices);
+    const uint32_t st0 = (uint32_t)(((uint64_t)spt * part) / parts), nsteps = (uint32_t)(((uint64_t)spt * (part + 1)) / parts) - st0;
     const int row0 = strip * (32 * kTiles);
     const int wrow = row0 + 32 * tile + col;
     const int m0 = (int)blockIdx.y * (32 * TT);
     const uint32_t xpitch = (uint32_t)KB * 12u;                       // dwords per activation row
 
-    // staging: the two blocks of a step are 96 contiguous bytes of a token row, six pieces of 16; load i fetches pieces 2 i and
-    // 2 i + 1 of all 32 tokens (two neighbouring lanes per token) to i * 1024 + token * 32
-    const uint32_t s_row = (uint32_t)min(M - 1, m0 + 32 * tile + (lane >> 1)) * xpitch, s_odd = (uint32_t)(lane & 1) * 4u;
+    // staging: the two blocks of a step are 96 contiguous bytes of a token row, six pieces of 16; unit u = 64 i + lane of load i
+    // is piece u % 6 of token u / 6, so that neighbouring lanes read neighbouring bytes, stored at 96 bytes per token
+    uint32_t s_off[3];
+#pragma unroll
+    for (int i = 0; i < 3; i++) {
+        const uint32_t u = (uint32_t)(64 * i + lane);
+        s_off[i] = (uint32_t)min(M - 1, m0 + 32 * tile + (int)(u / 6)) * xpitch + (u % 6) * 4u;
+    }
     auto stage = [&](uint32_t st, uint32_t buf) {
 #pragma unroll
         for (int i = 0; i < 3; i++) {
-            const uint32_t off = s_row + min(st * 24u + 8u * i + s_odd, xpitch - 4u);    // past the last block: any valid data, its weights are zero
+            uint32_t off = s_off[i] + st * 24u;
+            if (2 * st + 1 >= (uint32_t)KB) off -= (uint32_t)(64 * i + lane) % 6 >= 3 ? 12u : 0u;      // past the last block: its weights are zero, any valid data
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (size_t)off),
                                              (__attribute__((address_space(3))) void*)(xbuf + buf * kSliceXBuf<TT> + (uint32_t)tile * 3072u + i * 1024), 16, 0, 0);
         }
@@ -993,22 +1005,66 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
         if (lane == 0) asm volatile("ds_add_u32 %0, %1" ::"v"(kSliceFlagOff<TT> + 4u * (uint32_t)which), "v"(1u) : "memory");
     };
 
-    struct Blk { RawBlock raw; bool live; };
-    // the strip's first word and gain (scalars) and this lane's row inside the strip
+    auto wait_loads = [] { __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8)); };       // vmcnt(0)
+
+    // Words are fetched for two steps at once (four neighbouring blocks of a row): lane half h loads the words of blocks 2 h and
+    // 2 h + 1, and swapping the upper lanes of the first with the lower lanes of the second leaves every lane the word of its
+    // block in either step.  The vector cache looks up one lane at a time: one load of 12 bytes and one of two gains cost it a
+    // third of what three narrow loads per step did.
     const size_t blk0 = (size_t)row0 * (size_t)KB;
     const unsigned char* idx0 = reinterpret_cast<const unsigned char*>(idx) + blk0 * kWordBytes<FMT>;
-    const uint16_t* gain0 = cd.gain_array() ? gain + blk0 : reinterpret_cast<const uint16_t*>(idx0);
+    const unsigned char* gain0 = cd.gain_array() ? reinterpret_cast<const unsigned char*>(gain + blk0) : idx0;
     const uint32_t kl0 = (uint32_t)(min(wrow, N - 1) - row0) * (uint32_t)KB;           // at most 127 rows of fewer than 2^24 blocks
-    auto fetch_blk = [&](uint32_t st, Blk& q) {
-        const uint32_t b = 2 * st + (uint32_t)half;
-        q.live = wrow < N && b < (uint32_t)KB;
-        load_raw<FMT>(idx0, gain0, true, (size_t)(kl0 + min(b, (uint32_t)KB - 1)), q.raw);
+    const size_t left = (size_t)(N - row0) * (size_t)KB;                               // blocks from the strip's first to the matrix's last
+    const uint32_t kl_last = (uint32_t)min(left, (size_t)0x80000000u) - 1u;
+    struct Two { uint32_t q[4], g; bool late; };
+    auto fetch_two = [&](uint32_t st, bool real, Two& r) {
+        // the last word of the matrix is read as the second of a pair (a matrix of one block is not given to this kernel)
+        const uint32_t k = kl0 + min(2 * (st + (uint32_t)half), (uint32_t)KB - 1);
+        r.late = k >= kl_last;
+        const uint32_t kk = real ? r.late ? k - 1 : k : 0;
+        const unsigned char* p = idx0 + (size_t)kk * kWordBytes<FMT>;
+        if constexpr (FMT == LLVQ_IDX_U64) {
+            typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));
+            const u32x4_a8 v = *reinterpret_cast<const u32x4_a8*>(p);
+            r.q[0] = v[0]; r.q[1] = v[1]; r.q[2] = v[2]; r.q[3] = v[3];
+        } else if constexpr (FMT == LLVQ_IDX_U24) {
+            typedef uint32_t u32_a1 __attribute__((aligned(1)));
+            typedef uint16_t u16_a1 __attribute__((aligned(1)));
+            r.q[0] = *reinterpret_cast<const u32_a1*>(p);
+            r.q[1] = *reinterpret_cast<const u16_a1*>(p + 4);
+        } else {
+            typedef uint32_t u32x3_a2 __attribute__((ext_vector_type(3), aligned(2)));
+            const u32x3_a2 v = *reinterpret_cast<const u32x3_a2*>(p);
+            r.q[0] = v[0]; r.q[1] = v[1]; r.q[2] = v[2];
+        }
+        typedef uint32_t u32_a2 __attribute__((aligned(2)));
+        r.g = *reinterpret_cast<const u32_a2*>(gain0 + 2 * (size_t)kk);
     };
-    auto front_of = [&](const Blk& q, bool& ok, uint16_t& gb) {
+    auto swap_halves = [](uint32_t& a, uint32_t& b) {
+        const auto v = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = v[0]; b = v[1];
+    };
+    auto split_two = [&](const Two& r, RawBlock& first, RawBlock& second) {
+        uint32_t a[2], b[2] = {0, 0}, c[2] = {0, 0}, g[2] = {r.g & 0xFFFFu, r.g >> 16};
+        if constexpr (FMT == LLVQ_IDX_U64) { a[0] = r.q[0]; b[0] = r.q[1]; a[1] = r.q[2]; b[1] = r.q[3]; }
+        else if constexpr (FMT == LLVQ_IDX_U24) { a[0] = r.q[0] & 0xFFFFFFu; a[1] = (r.q[0] >> 24) | (r.q[1] << 8); }
+        else { a[0] = r.q[0]; c[0] = r.q[1] & 0xFFFFu; a[1] = __builtin_amdgcn_alignbit(r.q[2], r.q[1], 16); c[1] = r.q[2] >> 16; }
+        a[0] = r.late ? a[1] : a[0]; g[0] = r.late ? g[1] : g[0];
+        if constexpr (FMT == LLVQ_IDX_U64) b[0] = r.late ? b[1] : b[0];
+        if constexpr (FMT == LLVQ_IDX_U48) c[0] = r.late ? c[1] : c[0];
+        swap_halves(a[0], a[1]);
+        swap_halves(g[0], g[1]);
+        if constexpr (FMT == LLVQ_IDX_U64) swap_halves(b[0], b[1]);
+        if constexpr (FMT == LLVQ_IDX_U48) swap_halves(c[0], c[1]);
+        first = RawBlock{a[0], b[0], c[0], (uint16_t)g[0]};
+        second = RawBlock{a[1], b[1], c[1], (uint16_t)g[1]};
+    };
+    auto front_of = [&](const RawBlock& raw, uint32_t st, bool& ok, uint16_t& gb) {
         uint64_t I;
-        finish_block<FMT>(q.raw, cd, I, gb);
-        ok = q.live && I < T.npoints;
-        return llvq::decode_front<true, true, true>(T, llvq::find_class(T, ok ? I : 0));
+        finish_block<FMT>(raw, cd, I, gb);
+        ok = wrow < N && 2 * st + (uint32_t)half < (uint32_t)KB && I < T.npoints;
+        return llvq::decode_front<true>(T, llvq::find_class(T, ok ? I : 0));
     };
 
     float16_t acc[TT];
@@ -1018,16 +1074,20 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
         for (int v = 0; v < 16; v++) acc[t][v] = 0.0f;
     }
     if (nsteps) {
-        const uint32_t st_last = st0 + (nsteps - 1) * kSlices;
-        Blk blk;
-        fetch_blk(st0, blk);
-        if (tile < TT) stage(st0, 0);
+        Two two;
+        RawBlock raw, held;
+        fetch_two(st0, true, two);
+        if (tile < TT) {
+            stage(st0, 0);
+            wait_loads();
+            count(slice);
+        }
         bool ok = false;
         uint16_t gb = 0;
-        llvq::Front F = front_of(blk, ok, gb);
-        fetch_blk(min(st0 + kSlices, st_last), blk);
-        uint32_t st = st0;
-        for (uint32_t n = 0; n < nsteps; n++, st += kSlices) {
+        split_two(two, raw, held);
+        llvq::Front F = front_of(raw, st0, ok, gb);
+        for (uint32_t n = 0; n < nsteps; n++) {
+            const uint32_t st = st0 + n;
             uint32_t w[4];
             const llvq::BlockInfo bi = llvq::decode_back(T, F, w);
             const float scale = ok ? __half2float(__ushort_as_half(gb)) * bi.rnorm : 0.0f;
@@ -1047,25 +1107,17 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
                 for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
             }
             // the other buffer takes the next step once every wave of the slice is done with the step before this one
-            if (tile < TT) {
-                if (n + 1 < nsteps) {
-                    wait_for(done, n * kTiles);
-                    stage(st + kSlices, (n + 1) & 1u);
-                    __builtin_amdgcn_s_waitcnt(3 | (7 << 4) | (15 << 8));          // vmcnt(3): all but the three loads just issued have landed
-                } else {
-                    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));          // vmcnt(0)
-                }
-                count(slice);
+            if (tile < TT && n + 1 < nsteps) {
+                wait_for(done, n * kTiles);
+                stage(st + 1, (n + 1) & 1u);
             }
             wait_for(ready, (n + 1) * TT);
-            // channels 8 j .. + 7 of block `half` are piece 3 half + j of the token's row
-            const unsigned char* arow = xbuf + (n & 1u) * kSliceXBuf<TT> + (uint32_t)col * 32u;
+            const unsigned char* arow = xbuf + (n & 1u) * kSliceXBuf<TT> + (uint32_t)col * 96u + (uint32_t)half * 48u;
 #pragma unroll
             for (int j = 0; j < 3; j++) {
-                const uint32_t piece = half ? 3u + j : (uint32_t)j;
                 u32x4 a[TT];
 #pragma unroll
-                for (int t = 0; t < TT; t++) a[t] = *reinterpret_cast<const u32x4*>(arow + (uint32_t)t * 3072u + (piece >> 1) * 1024u + (piece & 1u) * 16u);
+                for (int t = 0; t < TT; t++) a[t] = *reinterpret_cast<const u32x4*>(arow + (uint32_t)t * 3072u + (uint32_t)j * 16u);
 #pragma unroll
                 for (int r = 0; r < kTerms; r++) {
                     const u32x4 b = {wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]};
@@ -1074,10 +1126,17 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
                 }
             }
             count(kSlices + slice);
-            // class search and digits of the next step (past the end the last one again: decoded, never used); after the
-            // products, so that neither the weights nor this block's digits are live in the other part
-            F = front_of(blk, ok, gb);
-            fetch_blk(min(st + 2 * kSlices, st_last), blk);
+            // what this wave staged before the products has landed by now; the others need it after their next decode
+            wait_loads();
+            if (tile < TT) count(slice);
+            // Class search and digits of the next step, after the products, so that neither the weights nor this block's digits
+            // are live in the other part.  After an odd step the pair fetched two steps ago is taken apart; the next one is
+            // fetched after an even step.  (After an odd step all lanes fetch one word that is never used: under a condition the
+            // compiler would have to wait for the fetch wherever it waits for the table reads issued before it.)
+            if (n & 1u) split_two(two, raw, held);
+            else raw = held;
+            F = front_of(raw, st + 1, ok, gb);                       // past the end: a dead block
+            fetch_two(min(st + 2, st0 + nsteps - 1), (n & 1u) == 0, two);
         }
     }
     __syncthreads();                                                 // tables and activation tiles are not needed any more
@@ -1802,7 +1861,8 @@ static bool panel_fits(const llvq_ctx* ctx, int M, uint64_t strips, int KB) {
 
 template <int FMT, typename X2>
 static int launch_any_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st) {
-    if (M < kMfmaMinM) return launch_matmul<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+    // (slice_kernel reads words in pairs: a matrix of a single block takes the lane-per-block kernel at every M)
+    if (M < kMfmaMinM || (size_t)N * KB < 2) return launch_matmul<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (panel_fits(ctx, M, (uint64_t)((N + kPanelRows - 1) / kPanelRows), KB))
         return launch_panel<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= 16) return launch_tile<FMT, X2, 1>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
@@ -1930,8 +1990,9 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
             return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
         return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
-    if (n_items == 1 || panel_fits(ctx, M, 1u << 20, KB)) {
-        // one matrix, or matrices that take the panel kernel each on its own: one product after the other
+    if (n_items == 1 || KB == 1 || panel_fits(ctx, M, 1u << 20, KB)) {
+        // one matrix, single-block rows (see launch_any_matmul), or matrices that take the panel kernel each on its own: one
+        // product after the other
         for (int i = 0; i < n_items; i++)
             if (int rc = matmul_impl(ctx, d_x, x_dtype, M, d_idx[i], fmt, d_gain[i], cd, N[i], KB, d_y[i], stream)) return rc;
         return LLVQ_OK;

@@ -195,6 +195,9 @@ ClassShape shape_of(const Leader& L) {
     return S;
 }
 
+// first symbol of the outer domain's inner word (an empty word shares the all-zero table)
+int outer_symbol(const ClassShape& S) { return S.mc.empty() || S.outer_all ? 0 : 1; }
+
 // The tables that do not depend on the layout: lut12, inner-word planes, subset ranking and its guess table, and the class
 // records that refer to them.
 struct DecoderParts {
@@ -203,6 +206,7 @@ struct DecoderParts {
     std::vector<uint32_t> inner;
     std::vector<SplitEnt> split;
     std::vector<uint8_t> guess;
+    std::vector<ClassVals> vt8, vti;          // by record(), one entry per call
     struct SplitInfo { uint16_t sp; int shift, jmax, row; };
 
     DecoderParts() {
@@ -254,6 +258,16 @@ struct DecoderParts {
         return base;
     }
 
+    // Builds the tables of several patterns, those first whose entries are read most often: indices spread evenly over the
+    // union read a fifth of the entries nine times out of ten, and next to each other these share cache lines.
+    typedef std::map<std::pair<std::vector<int>, int>, double> PatternUse;         // (pattern, sym_base) -> points that use it
+    void inner_tables_by_use(const PatternUse& use) {
+        std::vector<std::pair<double, std::pair<std::vector<int>, int>>> order;
+        for (const auto& u : use) order.push_back({-u.second / (double)multinomial(u.first.first), u.first});
+        std::sort(order.begin(), order.end());
+        for (const auto& o : order) inner_table(o.second.first, o.second.second);
+    }
+
     // q-subsets of n slots, slots 0..11 low, 12..n-1 high; order: number j of high slots, then colex rank
     // of the high part, then colex rank of the low part.
     SplitInfo split_table(int n, int q) {
@@ -300,7 +314,7 @@ struct DecoderParts {
         return inv;
     }
 
-    // Everything of a class record that the two layouts have in common: digits, values, subset ranking.  tb0 and tb1 are
+    // Everything of a class's record and value tables that the two layouts have in common: digits, values, subset ranking.  tb0 and tb1 are
     // the first inner-word entries of the outer domain and of the direct F1 word.  Value codes: outer domain = all positions
     // (odd, w = 24) and classes placed step by step: code 0 = outside value, first_code + i = i-th minority value; otherwise
     // 0 = zero, 1 + i = i-th nonzero F0 value, 4 + i = i-th F1 value.
@@ -330,8 +344,8 @@ struct DecoderParts {
             v8 |= (uint64_t)(fp8_e4m3(v) | (neg ? 0x80 : 0)) << (8 * k);
             vi |= (uint64_t)(uint8_t)(int8_t)(neg ? -v : v) << (8 * k);
         }
-        R.vt8_lo = (uint32_t)v8; R.vt8_hi = (uint32_t)(v8 >> 32);
-        R.vti_lo = (uint32_t)vi; R.vti_hi = (uint32_t)(vi >> 32);
+        vt8.push_back({(uint32_t)v8, (uint32_t)(v8 >> 32)});
+        vti.push_back({(uint32_t)vi, (uint32_t)(vi >> 32)});
         return R;
     }
 
@@ -374,10 +388,11 @@ bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const
     std::vector<double> atab = {1.0, 1.0, 759.0, (1.0 / 759.0) * (1.0 + std::ldexp(1.0, -50)),
                                 2576.0, (1.0 / 2576.0) * (1.0 + std::ldexp(1.0, -50)), 4096.0, 1.0 / 4096.0};
     const uint64_t inner_end = LAY::kOffInner + (uint64_t)D.inner.size() * sizeof(uint32_t);
-    const uint32_t cls_end = LAY::kWide ? Lay19::kOffWideRec : Lay13::kOffSpread6;
+    const uint32_t cls_end = LAY::kWide ? Lay19::kOffVt8 : Lay13::kOffSpread6;
     if (D.guess.size() > LAY::kOffAtab - LAY::kOffGuess || cls_off.size() * 8 > LAY::kOffRnorm - LAY::kOffClsOff ||
         (size_t)(m_max + 1) * sizeof(float) > LAY::kOffSplit - LAY::kOffRnorm ||
         (D.split.size() + 1) * sizeof(SplitEnt) > LAY::kLdsBytes - LAY::kOffSplit || recs.size() * sizeof(ClassRec) > cls_end - LAY::kOffCls ||
+        D.vt8.size() != ncls || ncls * sizeof(ClassVals) > (LAY::kWide ? Lay19::kOffVti - Lay19::kOffVt8 : Lay13::kOffVt8) ||
         npoints > (4096ull << LAY::kBucketShift) || inner_end > LAY::kMaxBlob)
         return false;
     blob.assign((inner_end + 15u) & ~(uint64_t)15u, 0);
@@ -395,6 +410,8 @@ bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const
     }
     put(LAY::kOffSplit, D.split.data(), D.split.size() * sizeof(SplitEnt));
     put(LAY::kOffCls, recs.data(), recs.size() * sizeof(ClassRec));
+    put(LAY::kOffVt8, D.vt8.data(), D.vt8.size() * sizeof(ClassVals));
+    put(LAY::kOffVti, D.vti.data(), D.vti.size() * sizeof(ClassVals));
     put(LAY::kOffInner, D.inner.data(), D.inner.size() * 4);
     lay = TableLayout{};
     lay.lds_bytes = LAY::kLdsBytes;
@@ -461,13 +478,19 @@ bool build_wide_tables(int m_max, WideTables& out) {
         const int64_t tb1 = D.inner_table(word.first.second, 0);
         if (tb1 < 0 || tb1 > 0xFFFF) return false;
     }
+    DecoderParts::PatternUse use;
+    for (const Leader& L : cls) {
+        const ClassShape S = shape_of(L);
+        use[{S.mc, outer_symbol(S)}] += (double)L.size;
+    }
+    D.inner_tables_by_use(use);
     std::vector<ClassRec> recs(cls.size());
     uint64_t most_steps = 0;
     for (size_t ci = 0; ci < cls.size(); ci++) {
         const Leader& L = cls[ci];
         const ClassShape S = shape_of(L);
         if (L.size >= (1ull << 52) || out.recs[ci].Pin * out.recs[ci].P1 >= (1u << 22) || out.recs[ci].P1 > 0xFFFF) return false;
-        int64_t tb0 = D.inner_table(S.mc, S.mc.empty() || S.outer_all ? 0 : 1);
+        int64_t tb0 = D.inner_table(S.mc, outer_symbol(S));
         const bool steps = tb0 < 0;
         if (steps) {
             if (S.f1direct || S.mv.size() > 7) return false;
@@ -502,6 +525,13 @@ bool build_tables(int m_max, Tables& out) {
 
     DecoderParts D;
     const std::vector<SplitEnt>& split = D.split;
+    DecoderParts::PatternUse use;
+    for (const Leader& L : cls) {
+        const ClassShape S = shape_of(L);
+        use[{S.mc, outer_symbol(S)}] += (double)L.size;
+        use[{S.dc, 0}] += (double)L.size;
+    }
+    D.inner_tables_by_use(use);
 
     // ---- class records ---------------------------------------------------------------------------
     std::vector<ClassRec> recs(ncls);
@@ -517,7 +547,7 @@ bool build_tables(int m_max, Tables& out) {
         // consistency with the class cardinality
         if (g_binom[S.n][S.q] * Pin * P1 != L.P1 * L.P0) return false;
         int sym_base0 = outer_all ? 0 : 1;
-        int64_t tb0 = D.inner_table(mc, mc.empty() ? 0 : sym_base0);
+        int64_t tb0 = D.inner_table(mc, outer_symbol(S));
         int64_t tb1 = D.inner_table(dc, 0);
         if (tb0 < 0 || tb1 < 0 || tb0 > 0xFFFF || tb1 > 0xFFFF) return false;
         if (P1 * Pin >= (1u << 22) || P1 > 0xFFFF) return false;

@@ -28,10 +28,14 @@ struct alignas(16) ClassRec {
     uint16_t tb1;        // first entry of the direct F1 word's table in `inner`
     uint16_t tb0;        // first entry of the outer domain's inner-word table in `inner`
     uint16_t sp;         // split entry of j is split[sp + j]
-    uint32_t vt8_lo, vt8_hi;   // value of code 0..7 as fp8 e4m3 bytes (sign bit = bit 7)
-    uint32_t vti_lo, vti_hi;   // value of code 0..7 as int8
 };
-static_assert(sizeof(ClassRec) == 48, "ClassRec layout");
+static_assert(sizeof(ClassRec) == 32, "ClassRec layout");
+
+// Values of the codes 0..7 of a class, one byte each.  Two tables of their own, since a kernel needs one of them:
+// fp8 e4m3 (sign bit = bit 7) or int8.
+struct ClassVals {
+    uint32_t lo, hi;
+};
 
 // f0: [0] odd  [1] f1_direct (even class, 0 < w <= 16: F1 planes go through the codeword)
 //     [2] outer_all (outer domain = all 24 positions: odd classes and w = 24)
@@ -66,8 +70,10 @@ constexpr uint32_t kSpreadPitch = 65;      // dwords per mask row of spread6: en
 constexpr uint32_t kPdepPitch  = 68;       // bytes per mask row of pdep6 (17 dwords, for the same reason)
 struct Lay13 {
     static constexpr bool kWide = false;
-    static constexpr uint32_t kOffCls     = 0;        // ncls x ClassRec, ncls <= 383
-    static constexpr uint32_t kOffSpread6 = 18432;    // 64 x 65 x u32 (first table of the kernels that read the records from global memory)
+    static constexpr uint32_t kOffVti     = 0;        // ncls x ClassVals, int8, ncls <= 383
+    static constexpr uint32_t kOffVt8     = 3072;     // ncls x ClassVals, fp8
+    static constexpr uint32_t kOffCls     = 6144;     // ncls x ClassRec
+    static constexpr uint32_t kOffSpread6 = 18432;    // 64 x 65 x u32
     static constexpr uint32_t kOffPdep6   = 35072;    // 64 x 68 x u8
     static constexpr uint32_t kOffLut12   = 39424;    // 4096 x u16
     static constexpr uint32_t kOffBucket  = 47616;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
@@ -104,11 +110,13 @@ struct Lay19 {
     static constexpr uint32_t kOffSplit   = 53248;    // up to 512 x SplitEnt
     static constexpr uint32_t kLdsBytes   = 61440;
     static constexpr uint32_t kOffGs      = 61440;    // 4096 x u32
-    static constexpr uint32_t kOffCls     = 77824;    // ncls x ClassRec (global memory)
-    static constexpr uint32_t kOffWideRec = 147760;   // ncls x WideRec (global memory)
-    static constexpr uint32_t kOffBinom   = 241008;   // 25 x 25 x u32 (global memory)
-    static constexpr uint32_t kOffInner   = 243520;   // inner-word planes (global memory)
-    static constexpr uint32_t kMaxBlob    = 243520 + 4 * (1u << 24);
+    static constexpr uint32_t kOffCls     = 77824;    // ncls x ClassRec (global memory, like all that follows)
+    static constexpr uint32_t kOffVt8     = 124448;   // ncls x ClassVals, fp8
+    static constexpr uint32_t kOffVti     = 136112;   // ncls x ClassVals, int8
+    static constexpr uint32_t kOffWideRec = 147776;   // ncls x WideRec
+    static constexpr uint32_t kOffBinom   = 241024;   // 25 x 25 x u32
+    static constexpr uint32_t kOffInner   = 243536;   // inner-word planes
+    static constexpr uint32_t kMaxBlob    = 243536 + 4 * (1u << 24);
     static constexpr uint32_t kBucketShift = 43;      // 4096 buckets cover 55 bits
     static constexpr uint64_t kWordMask   = (1ull << 56) - 1;
 };
