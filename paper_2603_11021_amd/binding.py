@@ -72,10 +72,31 @@ def _load():
     return lib
 
 
-def _stream_handle(stream):
+# The calls take 3 to 10 us of GPU time at their smallest, so what Python does around them counts (7.5 -> ~4 us per call):
+# torch is imported once, the current stream is read as a number (torch.cuda.current_stream() builds an object around it) and
+# types are looked up in ready-made tables.
+torch = None
+_raw_stream = _current_device = None
+_X_CODE = _OUT_CODE = None
+
+
+def _bind_torch():
+    global torch, _raw_stream, _current_device, _X_CODE, _OUT_CODE
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    _raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    _X_CODE = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16}
+    _OUT_CODE = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16, torch.float32: LLVQ_F32}
+
+
+def _stream_handle(stream):
+    return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
+
+
+def _rows(x, K):
+    """x as contiguous rows of K values, and their number"""
+    if x.dim() != 2 or x.shape[1] != K or not x.is_contiguous():
+        x = x.reshape(-1, K)
+    return x, x.shape[0]
 
 
 class LLVQ:
@@ -83,6 +104,8 @@ class LLVQ:
 
     def __init__(self, m_max=13, device=0):
         self._lib = _load()
+        if torch is None:
+            _bind_torch()
         h = ctypes.c_void_p()
         rc = self._lib.llvq_create(ctypes.byref(h), m_max, device)
         if rc != 0:
@@ -116,7 +139,6 @@ class LLVQ:
 
     @staticmethod
     def _idx_fmt(idx, fmt=None):
-        import torch
         if fmt == LLVQ_IDX_U24:
             if idx.dtype != torch.uint8:
                 raise LLVQError("24-bit words are passed as a uint8 tensor, 3 bytes per word")
@@ -128,7 +150,6 @@ class LLVQ:
         raise LLVQError("indices must be uint8 (6 bytes per index) or int64/uint64")
 
     def llvq_decode_i8(self, idx, out=None, n_blocks=None, stream=None):
-        import torch
         fmt, n = self._idx_fmt(idx)
         n = n if n_blocks is None else n_blocks
         if out is None:
@@ -138,10 +159,9 @@ class LLVQ:
         return out
 
     def llvq_decode(self, idx, gain, out_dtype=None, out=None, stream=None):
-        import torch
         fmt, n = self._idx_fmt(idx)
         out_dtype = out_dtype or torch.float16
-        code = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16, torch.float32: LLVQ_F32}[out_dtype]
+        code = _OUT_CODE[out_dtype]
         if gain.dtype != torch.float16 or gain.numel() != n:
             raise LLVQError("gain must be float16 with one entry per block")
         if out is None:
@@ -151,13 +171,11 @@ class LLVQ:
         return out
 
     def llvq_matmul(self, x, idx, gain, N, KB, out=None, stream=None, workspace=None):
-        import torch
         fmt, n = self._idx_fmt(idx)
         if n != N * KB or gain.numel() != N * KB or gain.dtype != torch.float16:
             raise LLVQError("idx and gain must hold N*KB blocks; gain float16")
-        code = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16}[x.dtype]
-        x2 = x.reshape(-1, 24 * KB)
-        M = x2.shape[0]
+        code = _X_CODE[x.dtype]
+        x2, M = _rows(x, 24 * KB)
         if out is None:
             out = torch.empty((M, N), dtype=torch.float32, device=x.device)
         if workspace is not None:
@@ -171,13 +189,11 @@ class LLVQ:
 
     def llvq_matmul_multi(self, x, idxs, gains, Ns, KB, outs=None, stream=None):
         """y_i = W_i x for up to four matrices that share x: lists of index tensors, gain tensors and row counts."""
-        import torch
         n_items = len(idxs)
         if not (len(gains) == len(Ns) == n_items) or (outs is not None and len(outs) != n_items):
             raise LLVQError("idxs, gains, Ns and outs must have the same length")
-        code = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16}[x.dtype]
-        x2 = x.reshape(-1, 24 * KB)
-        M = x2.shape[0]
+        code = _X_CODE[x.dtype]
+        x2, M = _rows(x, 24 * KB)
         fmt = None
         for idx, gain, N in zip(idxs, gains, Ns):
             f, n = self._idx_fmt(idx)
@@ -199,7 +215,6 @@ class LLVQ:
 
     # ---- coded words: shape index in the low shape_bits (+ base_index), gain code above them ------------------
     def llvq_decode_i8_coded(self, idx, shape_bits, base_index=0, fmt=None, out=None, stream=None):
-        import torch
         fmt, n = self._idx_fmt(idx, fmt)
         if out is None:
             out = torch.empty((n, 24), dtype=torch.int8, device=idx.device)
@@ -209,7 +224,6 @@ class LLVQ:
 
     @staticmethod
     def _gain_args(gain_lut, gain, n):
-        import torch
         for t, what in ((gain_lut, "gain_lut"), (gain, "gain")):
             if t is not None and t.dtype != torch.float16:
                 raise LLVQError("%s must be float16" % what)
@@ -219,10 +233,9 @@ class LLVQ:
 
     def llvq_decode_coded(self, idx, shape_bits, base_index=0, gain_lut=None, gain=None, fmt=None, out_dtype=None, out=None,
                           stream=None):
-        import torch
         fmt, n = self._idx_fmt(idx, fmt)
         out_dtype = out_dtype or torch.float16
-        code = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16, torch.float32: LLVQ_F32}[out_dtype]
+        code = _OUT_CODE[out_dtype]
         p_lut, p_gain = self._gain_args(gain_lut, gain, n)
         if gain_lut is not None and gain_lut.numel() != 1 << ((24 if fmt == LLVQ_IDX_U24 else 48) - shape_bits):
             raise LLVQError("gain_lut must hold 2^(word bits - shape_bits) entries")
@@ -234,16 +247,14 @@ class LLVQ:
 
     def llvq_matmul_coded(self, x, idx, N, KB, shape_bits, base_index=0, gain_lut=None, gain=None, fmt=None, out=None,
                           stream=None):
-        import torch
         fmt, n = self._idx_fmt(idx, fmt)
         if n != N * KB:
             raise LLVQError("idx must hold N*KB words")
         p_lut, p_gain = self._gain_args(gain_lut, gain, n)
         if gain_lut is not None and gain_lut.numel() != 1 << ((24 if fmt == LLVQ_IDX_U24 else 48) - shape_bits):
             raise LLVQError("gain_lut must hold 2^(word bits - shape_bits) entries")
-        code = {torch.float16: LLVQ_F16, torch.bfloat16: LLVQ_BF16}[x.dtype]
-        x2 = x.reshape(-1, 24 * KB)
-        M = x2.shape[0]
+        code = _X_CODE[x.dtype]
+        x2, M = _rows(x, 24 * KB)
         if out is None:
             out = torch.empty((M, N), dtype=torch.float32, device=x.device)
         self._check(self._lib.llvq_matmul_coded(self._h, x2.data_ptr(), code, M, idx.data_ptr(), fmt, shape_bits, base_index,
@@ -253,7 +264,6 @@ class LLVQ:
 
     def llvq_encode(self, pts, fmt=LLVQ_IDX_U48, out=None, stream=None):
         """pts: int8 [n, 24] -> indices, uint8 [n, 6] (LLVQ_IDX_U48) or int64 [n] (LLVQ_IDX_U64); all ones = not a point"""
-        import torch
         if pts.dtype != torch.int8 or pts.numel() % 24:
             raise LLVQError("points must be int8 with 24 coordinates each")
         n = pts.numel() // 24
@@ -265,7 +275,6 @@ class LLVQ:
 
     def llvq_repack(self, idx, gain, out=None, stream=None):
         """idx (uint8 6 bytes per block, or int64) + gain float16 -> int64 [n]: index | gain bits << 48"""
-        import torch
         fmt, n = self._idx_fmt(idx)
         if gain.dtype != torch.float16 or gain.numel() != n:
             raise LLVQError("gain must hold one float16 per block")
@@ -277,7 +286,6 @@ class LLVQ:
 
     def llvq_quantize(self, w, metric=LLVQ_ANGULAR, fmt=LLVQ_IDX_U48, want_idx=True, stream=None):
         """w: float32 [n, 24] -> (points int8 [n, 24], indices or None, scores float32 [n])"""
-        import torch
         if w.dtype != torch.float32 or w.numel() % 24:
             raise LLVQError("blocks must be float32 with 24 coordinates each")
         n = w.numel() // 24
@@ -295,7 +303,6 @@ class LLVQ:
     def llvq_gptq_quantize(self, W, U, fmt=LLVQ_IDX_U48, gain_levels=None, stream=None):
         """W: float32 [N, 24*KB], overwritten with the quantised layer; U: float32 [K, K] upper factor of H^-1.
         Returns (indices [N, KB(, 6)], gains float16 [N, KB])."""
-        import torch
         N, K = W.shape
         if W.dtype != torch.float32 or U.dtype != torch.float32 or K % 24 or tuple(U.shape) != (K, K) or not W.is_contiguous() or not U.is_contiguous():
             raise LLVQError("W must be contiguous float32 [N, 24*KB] and U float32 [K, K]")
@@ -318,7 +325,6 @@ class LLVQ:
 
     def llvq_gptq_group_scales(self, Wq, W0, H, gain, lam=0.0, stream=None):
         """closed-form group scales in place on Wq and gain; returns the scales s [N, KB] (float32)"""
-        import torch
         N, K = Wq.shape
         if (Wq.dtype != torch.float32 or W0.dtype != torch.float32 or H.dtype != torch.float32 or gain.dtype != torch.float16 or K % 24
                 or tuple(W0.shape) != (N, K) or tuple(H.shape) != (K, K) or tuple(gain.shape) != (N, K // 24)
@@ -342,7 +348,6 @@ class LLVQ:
     def llvq_validate_static(self, idx, out=None, stream=None):
         """Count of out-of-range indices into a one-element int64 device tensor; no synchronisation, no allocation
         inside the library (`out` is allocated here when the caller passes none)."""
-        import torch
         fmt, n = self._idx_fmt(idx)
         if out is None:
             out = torch.empty(1, dtype=torch.int64, device=idx.device)
