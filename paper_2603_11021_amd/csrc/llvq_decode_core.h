@@ -222,13 +222,21 @@ struct Front {
 
 // BIG_GLOBAL: the Golay words and the inner-word planes are read from global memory instead of LDS
 // (GS_LDS: only the inner-word planes are; the kernel has copied the blob up to LAY::kOffInner);
-// REC_GLOBAL: so is the class record (Lay19: and its values)
+// REC_GLOBAL: so is the class record (FullRec)
 template <bool BIG_GLOBAL = false, bool REC_GLOBAL = false, bool GS_LDS = false, class LAY = Lay13>
 LLVQ_HD Front decode_front(const TabPtrsOf<LAY>& T, const ClassHit& hit) {
     Front F;
-    const ClassRec R = REC_GLOBAL ? gtab_at<ClassRec, LAY::kOffCls>(T, hit.c8 * 4u) : tab_at<ClassRec, LAY::kOffCls>(T, hit.c8 * 4u);
-    const ClassVals v8 = REC_GLOBAL && LAY::kWide ? gtab_at<ClassVals, LAY::kOffVt8>(T, hit.c8) : tab_at<ClassVals, LAY::kOffVt8>(T, hit.c8);
-    const ClassVals vi = REC_GLOBAL && LAY::kWide ? gtab_at<ClassVals, LAY::kOffVti>(T, hit.c8) : tab_at<ClassVals, LAY::kOffVti>(T, hit.c8);
+    ClassRec R;
+    ClassVals v8, vi;
+    if constexpr (REC_GLOBAL || LAY::kWide) {
+        const uint32_t off = hit.c8 * 8u;
+        const FullRec full = REC_GLOBAL ? gtab_at<FullRec, LAY::kOffFullRec>(T, off) : tab_at<FullRec, LAY::kOffFullRec>(T, off);
+        R = full.rec; v8 = full.v8; vi = full.vi;
+    } else {
+        R = tab_at<ClassRec, LAY::kOffCls>(T, hit.c8 * 4u);
+        v8 = tab_at<ClassVals, LAY::kOffVt8>(T, hit.c8);
+        vi = tab_at<ClassVals, LAY::kOffVti>(T, hit.c8);
+    }
     const uint32_t f0 = R.f0, f1 = R.f1;
     // r = Ic mod A, then B sign bits, then the permutation rank I''.  All quotients are exact: the operands are
     // integers below 2^48 held in doubles and the reciprocals are nudged upwards.

@@ -246,7 +246,7 @@ struct BatchDeal {
 // words, while class records and inner-word planes are read from global memory
 template <class LAY, bool BIG_GLOBAL>
 __device__ __forceinline__ uint32_t table_bytes_of(const TableLayout& lay) {
-    return LAY::kWide ? Lay19::kOffCls : BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes;
+    return LAY::kWide ? Lay19::kOffFullRec : BIG_GLOBAL ? lay.lds_bytes : lay.blob_bytes;
 }
 
 // ---- llvq_decode_i8 ---------------------------------------------------------------------------------
@@ -449,7 +449,7 @@ __global__ void __launch_bounds__(kThreads) matmul_kernel(const unsigned char* _
         load_raw_near<FMT>(idx0, gain0, min((uint32_t)wave * 64u + (uint32_t)lane, nblk - 1), first_raw);
     }
     // one workgroup per compute unit: the tables are copied once per launch and workgroup
-    const uint32_t table_bytes = LAY::kWide ? Lay19::kOffCls : BIG_GLOBAL ? Lay13::kOffInner : lay.blob_bytes;      // short launches: small tables + Golay words
+    const uint32_t table_bytes = LAY::kWide ? Lay19::kOffFullRec : BIG_GLOBAL ? Lay13::kOffInner : lay.blob_bytes;      // short launches: small tables + Golay words
     float* ysum = reinterpret_cast<float*>(g_lds + table_bytes);      // [kRowsPerPass][kMaxMChunk]
     // the first block number no wave has taken yet: the first two batches of a wave are fixed, after them it takes the
     // next free one, so waves on a SIMD that gets through its batches sooner end up with more of them
@@ -732,7 +732,7 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
     constexpr int kWaves = kThreads / 64;
     constexpr int kPassTiles = kTilePassSlots / TT;                      // row tiles per pass
     constexpr int kTerms = Mma<X2>::kTerms;
-    constexpr uint32_t kTableBytes = LAY::kWide ? Lay19::kOffCls : Lay13::kOffInner;
+    constexpr uint32_t kTableBytes = LAY::kWide ? Lay19::kOffFullRec : Lay13::kOffInner;
     load_tables(blob, kTableBytes);          // the small tables and the Golay words; the inner-word planes stay in global memory
     const auto T = llvq::make_tab_ptrs<LAY>(lds_origin(), blob, lay);
     float* slots = reinterpret_cast<float*>(g_lds + kTableBytes);      // [kWaves][kPassTiles][TT][256]
@@ -929,7 +929,7 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
 // Llama-3-8B-shaped block (seven layers, fp16): M = 64 XX -> XX us, M = 128 XX -> XX us, M = 256 XX -> XX us against the
 // split-K kernel and the strip kernel with two waves per SIMD.
 template <int TT> constexpr int kSliceTiles = TT <= 2 ? 2 : 4;           // 32-row tiles per workgroup
-constexpr uint32_t kSliceTabBytes = Lay13::kOffGs - Lay13::kOffVt8;                        // class records and small tables; Golay words and planes in global memory
+constexpr uint32_t kSliceTabBytes = Lay13::kOffVti;                                        // class records and small tables; Golay words and planes in global memory
 constexpr uint32_t kSliceXOff = (kSliceTabBytes + 511u) & ~511u;
 template <int TT> constexpr uint32_t kSliceXBuf = TT * 3072u;                              // one step of one slice: 32 TT tokens x 96 bytes
 template <int TT> constexpr uint32_t kSliceFlagOff = kSliceXOff + 2u * (16 / kSliceTiles<TT>) * kSliceXBuf<TT>;
@@ -963,8 +963,8 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
     const int col = lane & 31, half = lane >> 5;
     uint32_t* flags = reinterpret_cast<uint32_t*>(g_lds + kSliceFlagOff<TT>);                  // ready[kSlices], done[kSlices]
     if (threadIdx.x < 2 * kSlices) flags[threadIdx.x] = 0;                                     // published by the barrier of load_tables
-    load_tables(blob + Lay13::kOffVt8, kSliceTabBytes);
-    const TabPtrs T = llvq::make_tab_ptrs(lds_origin() - Lay13::kOffVt8, blob, lay);
+    load_tables(blob, kSliceTabBytes);
+    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
     unsigned char* xbuf = g_lds + kSliceXOff + (uint32_t)slice * 2u * kSliceXBuf<TT>;
 
     // steps (block pairs) of a row, cut into one run per slice of every workgroup that shares the row
@@ -1674,7 +1674,7 @@ static int launch_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_id
     // from 64 batches of 64 blocks per compute unit on (four per wave; measured on Llama-3-8B and 70B shapes), copying
     // all tables into LDS pays, and so does dealing the batches to the waves as they finish
     const bool short_launch = (size_t)N * (size_t)KB / 64 < (size_t)ctx->num_cu * 64;
-    const size_t lds = (LAY::kWide ? Lay19::kOffCls : short_launch ? Lay13::kOffInner : ctx->lay.blob_bytes) + (size_t)kRowsPerPass * kMaxMChunk * sizeof(float) + 16;   // row sums + batch counter
+    const size_t lds = (LAY::kWide ? Lay19::kOffFullRec : short_launch ? Lay13::kOffInner : ctx->lay.blob_bytes) + (size_t)kRowsPerPass * kMaxMChunk * sizeof(float) + 16;   // row sums + batch counter
     const int rows_pass = std::max(1, std::min(kRowsPerPass, ((1 << 24) - 1) / KB));       // KB < 2^24 (checked by the caller)
 #define LLVQ_LAUNCH_MATMUL(BG, DYN)                                                                                         \
     do {                                                                                                                    \
@@ -1700,7 +1700,7 @@ static int launch_tile(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx,
     int grid = std::min(ctx->num_cu, n_tiles);
     const int per_wg = (n_tiles + grid - 1) / grid;
     grid = (n_tiles + per_wg - 1) / per_wg;
-    const size_t lds = (LAY::kWide ? Lay19::kOffCls : Lay13::kOffInner) + (size_t)(kThreads / 64) * kTilePassSlots * 256 * sizeof(float);
+    const size_t lds = (LAY::kWide ? Lay19::kOffFullRec : Lay13::kOffInner) + (size_t)(kThreads / 64) * kTilePassSlots * 256 * sizeof(float);
     if (int rc = set_lds<tile_kernel<FMT, X2, TT, MULTI, LAY>>(ctx, lds)) return rc;
     hipLaunchKernelGGL((tile_kernel<FMT, X2, TT, MULTI, LAY>), dim3(grid), dim3(kThreads), lds, st, ctx->d_blob, ctx->lay, d_idx,
                        reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, n_tiles, per_wg, items, d_y);
@@ -2038,7 +2038,7 @@ int wide_finish(llvq_ctx* ctx, const char* what) {
 }
 
 // 78 KB of tables: two workgroups share a compute unit
-constexpr size_t kWideBulkLds = Lay19::kOffCls + 16;           // + the batch counter
+constexpr size_t kWideBulkLds = Lay19::kOffFullRec + 16;           // + the batch counter
 
 template <int FMT>
 int wide_launch_decode_i8(llvq_ctx* ctx, const void* d_idx, size_t n, int8_t* d_out, hipStream_t st) {

@@ -388,14 +388,17 @@ bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const
     std::vector<double> atab = {1.0, 1.0, 759.0, (1.0 / 759.0) * (1.0 + std::ldexp(1.0, -50)),
                                 2576.0, (1.0 / 2576.0) * (1.0 + std::ldexp(1.0, -50)), 4096.0, 1.0 / 4096.0};
     const uint64_t inner_end = LAY::kOffInner + (uint64_t)D.inner.size() * sizeof(uint32_t);
-    const uint32_t cls_end = LAY::kWide ? Lay19::kOffVt8 : Lay13::kOffSpread6;
+    const uint32_t split_end = LAY::kWide ? Lay19::kLdsBytes : Lay13::kOffCls;
+    bool classes_fit;
+    if constexpr (LAY::kWide) classes_fit = ncls * sizeof(FullRec) <= LAY::kOffWideRec - LAY::kOffFullRec;
+    else classes_fit = ncls * sizeof(ClassVals) <= LAY::kLdsBytes - LAY::kOffVti && ncls * sizeof(ClassRec) <= LAY::kOffVt8 - LAY::kOffCls;
     if (D.guess.size() > LAY::kOffAtab - LAY::kOffGuess || cls_off.size() * 8 > LAY::kOffRnorm - LAY::kOffClsOff ||
         (size_t)(m_max + 1) * sizeof(float) > LAY::kOffSplit - LAY::kOffRnorm ||
-        (D.split.size() + 1) * sizeof(SplitEnt) > LAY::kLdsBytes - LAY::kOffSplit || recs.size() * sizeof(ClassRec) > cls_end - LAY::kOffCls ||
-        D.vt8.size() != ncls || ncls * sizeof(ClassVals) > (LAY::kWide ? Lay19::kOffVti - Lay19::kOffVt8 : Lay13::kOffVt8) ||
+        (D.split.size() + 1) * sizeof(SplitEnt) > split_end - LAY::kOffSplit || recs.size() != ncls || D.vt8.size() != ncls || !classes_fit ||
         npoints > (4096ull << LAY::kBucketShift) || inner_end > LAY::kMaxBlob)
         return false;
-    blob.assign((inner_end + 15u) & ~(uint64_t)15u, 0);
+    const uint64_t inner_bytes = (inner_end + 15u) & ~(uint64_t)15u;
+    blob.assign(LAY::kWide ? inner_bytes : LAY::kOffFullRec + ncls * sizeof(FullRec), 0);
     auto put = [&](uint32_t off, const void* src, size_t bytes) { std::memcpy(blob.data() + off, src, bytes); };
     put(LAY::kOffGs, gs.data(), gs.size() * 4);
     put_deposit_tables<LAY>(blob.data());
@@ -409,13 +412,19 @@ bool assemble_blob(const DecoderParts& D, const std::vector<uint32_t>& gs, const
         put(LAY::kOffRnorm + 4 * m, &rn, sizeof rn);
     }
     put(LAY::kOffSplit, D.split.data(), D.split.size() * sizeof(SplitEnt));
-    put(LAY::kOffCls, recs.data(), recs.size() * sizeof(ClassRec));
-    put(LAY::kOffVt8, D.vt8.data(), D.vt8.size() * sizeof(ClassVals));
-    put(LAY::kOffVti, D.vti.data(), D.vti.size() * sizeof(ClassVals));
+    if constexpr (!LAY::kWide) {
+        put(LAY::kOffCls, recs.data(), recs.size() * sizeof(ClassRec));
+        put(LAY::kOffVt8, D.vt8.data(), D.vt8.size() * sizeof(ClassVals));
+        put(LAY::kOffVti, D.vti.data(), D.vti.size() * sizeof(ClassVals));
+    }
+    for (uint32_t ci = 0; ci < ncls; ci++) {
+        const FullRec full = {recs[ci], D.vt8[ci], D.vti[ci]};
+        put(LAY::kOffFullRec + ci * (uint32_t)sizeof full, &full, sizeof full);
+    }
     put(LAY::kOffInner, D.inner.data(), D.inner.size() * 4);
     lay = TableLayout{};
     lay.lds_bytes = LAY::kLdsBytes;
-    lay.blob_bytes = (uint32_t)blob.size();
+    lay.blob_bytes = (uint32_t)inner_bytes;
     lay.ncls = ncls;
     lay.inner_entries = (uint32_t)D.inner.size();
     lay.npoints = npoints;

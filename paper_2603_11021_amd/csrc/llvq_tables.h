@@ -37,6 +37,16 @@ struct ClassVals {
     uint32_t lo, hi;
 };
 
+// The same together, for the kernels that read records from global memory: a record's pieces then lie in one cache line.
+// The vector cache looks up one lane at a time, so lines count: the seven layers of a Llama-3-8B-shaped block at M = 1 take
+// 109.2 us with these, 109.5 with records of 48 bytes, 110.4 with the values in LDS and 110.9 with the values in a table of
+// their own in global memory.
+struct alignas(64) FullRec {
+    ClassRec rec;
+    ClassVals v8, vi;
+};
+static_assert(sizeof(FullRec) == 64, "FullRec layout");
+
 // f0: [0] odd  [1] f1_direct (even class, 0 < w <= 16: F1 planes go through the codeword)
 //     [2] outer_all (outer domain = all 24 positions: odd classes and w = 24)
 //     [3..7] wm1 = max(w-1,0)  [8] forced-sign enable  [9] kappa (parity of negative F1 signs)
@@ -70,22 +80,23 @@ constexpr uint32_t kSpreadPitch = 65;      // dwords per mask row of spread6: en
 constexpr uint32_t kPdepPitch  = 68;       // bytes per mask row of pdep6 (17 dwords, for the same reason)
 struct Lay13 {
     static constexpr bool kWide = false;
-    static constexpr uint32_t kOffVti     = 0;        // ncls x ClassVals, int8, ncls <= 383
-    static constexpr uint32_t kOffVt8     = 3072;     // ncls x ClassVals, fp8
-    static constexpr uint32_t kOffCls     = 6144;     // ncls x ClassRec
-    static constexpr uint32_t kOffSpread6 = 18432;    // 64 x 65 x u32
-    static constexpr uint32_t kOffPdep6   = 35072;    // 64 x 68 x u8
-    static constexpr uint32_t kOffLut12   = 39424;    // 4096 x u16
-    static constexpr uint32_t kOffBucket  = 47616;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
-    static constexpr uint32_t kOffGuess   = 55808;    // up to 48 rows x 64 x u8
-    static constexpr uint32_t kOffAtab    = 58880;    // 4 x {A, 1/A} doubles
-    static constexpr uint32_t kOffClsOff  = 58944;    // (ncls + 4) x u64: offsets, N, and three entries above every index
-    static constexpr uint32_t kOffRnorm   = 62048;    // 16 x float: 1/sqrt(16 m)
-    static constexpr uint32_t kOffSplit   = 62112;    // up to 188 x SplitEnt
-    static constexpr uint32_t kLdsBytes   = 65120;    // end of the tables that every kernel keeps in LDS
-    static constexpr uint32_t kOffGs      = 65120;    // 4096 x u32
-    static constexpr uint32_t kOffInner   = 81504;    // inner-word planes, u32
-    static constexpr uint32_t kMaxBlob    = 81504 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
+    static constexpr uint32_t kOffSpread6 = 0;        // 64 x 65 x u32
+    static constexpr uint32_t kOffPdep6   = 16640;    // 64 x 68 x u8
+    static constexpr uint32_t kOffLut12   = 20992;    // 4096 x u16
+    static constexpr uint32_t kOffBucket  = 29184;    // 4096 x u16: 8 x class id (the byte offset of its entry in cls_off)
+    static constexpr uint32_t kOffGuess   = 37376;    // up to 48 rows x 64 x u8
+    static constexpr uint32_t kOffAtab    = 40448;    // 4 x {A, 1/A} doubles
+    static constexpr uint32_t kOffClsOff  = 40512;    // (ncls + 4) x u64, ncls <= 383: offsets, N, and three entries above every index
+    static constexpr uint32_t kOffRnorm   = 43616;    // 16 x float: 1/sqrt(16 m)
+    static constexpr uint32_t kOffSplit   = 43680;    // up to 188 x SplitEnt
+    static constexpr uint32_t kOffCls     = 46688;    // ncls x ClassRec
+    static constexpr uint32_t kOffVt8     = 58944;    // ncls x ClassVals, fp8
+    static constexpr uint32_t kOffVti     = 62016;    // ncls x ClassVals, int8
+    static constexpr uint32_t kLdsBytes   = 65088;    // end of the tables that every kernel keeps in LDS
+    static constexpr uint32_t kOffGs      = 65088;    // 4096 x u32
+    static constexpr uint32_t kOffInner   = 81472;    // inner-word planes, u32
+    static constexpr uint32_t kMaxBlob    = 81472 + 4 * 65536;   // the inner-word table bases are 16-bit entry numbers
+    static constexpr uint32_t kOffFullRec = (kMaxBlob + 127u) & ~127u;    // ncls x FullRec, in global memory only
     static constexpr uint32_t kBucketShift = 36;      // bucket index = I >> 36 (4096 buckets cover 48 bits)
     static constexpr uint64_t kWordMask   = (1ull << 48) - 1;    // bits of a 64-bit word that hold index and gain code
 };
@@ -110,13 +121,11 @@ struct Lay19 {
     static constexpr uint32_t kOffSplit   = 53248;    // up to 512 x SplitEnt
     static constexpr uint32_t kLdsBytes   = 61440;
     static constexpr uint32_t kOffGs      = 61440;    // 4096 x u32
-    static constexpr uint32_t kOffCls     = 77824;    // ncls x ClassRec (global memory, like all that follows)
-    static constexpr uint32_t kOffVt8     = 124448;   // ncls x ClassVals, fp8
-    static constexpr uint32_t kOffVti     = 136112;   // ncls x ClassVals, int8
-    static constexpr uint32_t kOffWideRec = 147776;   // ncls x WideRec
-    static constexpr uint32_t kOffBinom   = 241024;   // 25 x 25 x u32
-    static constexpr uint32_t kOffInner   = 243536;   // inner-word planes
-    static constexpr uint32_t kMaxBlob    = 243536 + 4 * (1u << 24);
+    static constexpr uint32_t kOffFullRec = 77824;    // ncls x FullRec (global memory, like all that follows)
+    static constexpr uint32_t kOffWideRec = 171072;   // ncls x WideRec
+    static constexpr uint32_t kOffBinom   = 264320;   // 25 x 25 x u32
+    static constexpr uint32_t kOffInner   = 266832;   // inner-word planes
+    static constexpr uint32_t kMaxBlob    = 266832 + 4 * (1u << 24);
     static constexpr uint32_t kBucketShift = 43;      // 4096 buckets cover 55 bits
     static constexpr uint64_t kWordMask   = (1ull << 56) - 1;
 };
@@ -124,7 +133,7 @@ constexpr uint32_t kGuessBuckets = 64;     // buckets of the subset-split guess 
 
 struct TableLayout {
     uint32_t lds_bytes;      // first part of the blob: the tables every kernel keeps in LDS
-    uint32_t blob_bytes;     // the whole blob (kernels that want all tables in LDS copy this many bytes)
+    uint32_t blob_bytes;     // up to the end of the inner-word planes (kernels that want all tables in LDS copy this many bytes)
     uint32_t ncls;
     uint32_t inner_entries;
     uint64_t npoints;        // N(m_max)
