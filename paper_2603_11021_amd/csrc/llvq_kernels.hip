@@ -1185,6 +1185,14 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
 // duty, placement, signs and scaling in the step before the weights are needed.
 constexpr int kPanelRows = 128, kPanelTokens = 512, kPanelWaves = 8;
 constexpr int kPanelMinM = 384;
+// LDS: the tables without the int8 values, two buffers of decoded weights ([term][row tile][k group][lane] x 16 bytes) and the
+// waves' token rows.  For bf16 (two terms per weight) that is 448 bytes short of all there is; with one buffer and a barrier
+// between the products and the decode the seven layers of a Llama-3-8B-shaped block took 1189 us at M = 1024, not 1071.
+constexpr uint32_t kPanelTabBytes = Lay13::kOffVti;
+template <int TERMS> constexpr uint32_t kPanelBBytes = 4u * 3u * 1024u * TERMS;
+constexpr uint32_t kPanelARegion = 6 * 1024 + 4 * 96;            // 64 token rows: six staging instructions of ten rows in 1 KB, one of four
+template <int TERMS> constexpr uint32_t kPanelLds = kPanelTabBytes + 2u * kPanelBBytes<TERMS> + kPanelWaves * kPanelARegion;
+static_assert(kPanelLds<2> <= 160u * 1024u, "panel_kernel: LDS");
 
 // MULTI: the strips are those of up to four matrices that share x, one matrix after the other (`items`).
 template <int FMT, typename X2, bool MULTI = false>
@@ -1208,14 +1216,12 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
         strip -= first_strip;
     }
     constexpr int kTerms = Mma<X2>::kTerms;
-    constexpr int kBBufs = kTerms == 1 ? 2 : 1;                      // two-term weights: one buffer, a second barrier per step
-    constexpr uint32_t kBBytes = 4 * 3 * 1024 * kTerms;              // [term][row tile][k group][lane] x 16 bytes
-    constexpr uint32_t kARegion = 7 * 1024;                          // one wave's 64 token rows: seven staging instructions x 1 KB
-    load_tables<64 * kPanelWaves>(blob, lay.lds_bytes);
+    constexpr uint32_t kBBytes = kPanelBBytes<kTerms>;
+    load_tables<64 * kPanelWaves>(blob, kPanelTabBytes);
     const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
-    unsigned char* bbuf = g_lds + lay.lds_bytes;
+    unsigned char* bbuf = g_lds + kPanelTabBytes;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    unsigned char* abuf = bbuf + kBBufs * kBBytes + (uint32_t)wave * kARegion;
+    unsigned char* abuf = bbuf + 2 * kBBytes + (uint32_t)wave * kPanelARegion;
     const int col = lane & 31, half = lane >> 5;
     const uint32_t spt_all = ((uint32_t)KB + 1) / 2;
     const uint32_t st_first = (uint32_t)(((uint64_t)spt_all * blockIdx.z) / (uint32_t)ksplit);
@@ -1278,7 +1284,7 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
     // 64 x 16 bytes to 1 KB of consecutive LDS addresses.  Lane 6 k + q of instruction i fetches piece q (channels
     // 8 (q % 3) .. + 7 of block 2 st + q / 3) of token 10 i + k, so the 96 bytes of a token row are fetched by six
     // neighbouring lanes (few cache lines per instruction) and land at i * 1024 + k * 96; seven instructions cover the 64
-    // tokens (lanes 60..63 and the tail of the last instruction fetch copies that nobody reads).
+    // tokens (lanes 60..63 fetch copies that nobody reads; the last instruction has four tokens, 24 lanes).
     const int s_tok = lane / 6, s_q = lane - 6 * s_tok;
     // byte offsets of this lane's seven token rows in x (M * KB * 48 < 2^32, checked by the host)
     uint32_t s_row[7];
@@ -1288,9 +1294,11 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
         const uint32_t b = min(2 * st + (uint32_t)(s_q / 3), (uint32_t)KB - 1);      // past the last block: any valid data, its weights are zero
         const uint32_t boff = b * 48u;
 #pragma unroll
-        for (int i = 0; i < 7; i++)
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const unsigned char*>(x) + (s_row[i] + boff)),
-                                             (__attribute__((address_space(3))) void*)(abuf + i * 1024), 16, 0, 0);
+        for (int i = 0; i < 7; i++) {
+            if (i < 6 || lane < 24)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(reinterpret_cast<const unsigned char*>(x) + (s_row[i] + boff)),
+                                                 (__attribute__((address_space(3))) void*)(abuf + i * 1024), 16, 0, 0);
+        }
     };
     // A operands of the staged step in the MFMA's order: token 32 t + col, the lane half's block, channel group j
     uint32_t a_off[2];
@@ -1341,7 +1349,6 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
         constexpr unsigned n = decltype(n_tag)::value;
         __builtin_amdgcn_s_waitcnt((n & 15u) | (7u << 4) | (15u << 8) | ((n >> 4) << 14));
     };
-    constexpr unsigned kFetchLoads = FMT == LLVQ_IDX_U24 ? 4u : 3u;      // loads of fetch_blk
 
     // One step.  kBack: this wave finishes the decode of step st + 1 (its half's turn); otherwise it starts that of
     // step st + 2.  The role alternates from step to step and is fixed per position in the loop below, so that every
@@ -1351,15 +1358,15 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
     auto slot = [&](auto back_tag, uint32_t st) {
         constexpr bool kBack = decltype(back_tag)::value;
         const uint32_t r = st - st_first;
-        const uint32_t bcur = kBBufs == 2 ? (r & 1u) : 0u, bnext = kBBufs == 2 ? ((r + 1) & 1u) : 0u;
+        const uint32_t bcur = r & 1u, bnext = (r + 1) & 1u;
         // the A operands of step st are in registers (read before the barrier that ended the last step), so the
         // activation rows of step st + 1 can be requested into the same region right away
         // (the decoding half asks after its decode: all eight waves asking at once right after the barrier queue at the
         // vector memory pipe, 56 KB per step, and every one of them waits for the issue of its seven loads)
         const uint32_t st_stage = min(st + 1, st_last);
-        if (!(kBBufs == 2 && kBack)) stage_dma(st_stage);
+        if (!kBack) stage_dma(st_stage);
         // second part of step st + 1 before the products: the other wave of this SIMD multiplies meanwhile
-        if (kBBufs == 2 && kBack) {
+        if (kBack) {
             back_to_lds(F, U, ok, gb, bnext);
             fetch_blk(min(st + 3, st_last), blk);
             stage_dma(st_stage);
@@ -1398,18 +1405,10 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
                 }
             }
         }
-        if (kBBufs == 1) {
-            __syncthreads();                                         // every wave has read the weights of step st
-            if (kBack) {
-                back_to_lds(F, U, ok, gb, 0);
-                fetch_blk(min(st + 3, st_last), blk);
-            }
-        }
         if (!kBack) F = front_of(blk, ok, gb, U);                    // first part of step st + 2 (its word was requested a step ago)
         // the rows of step st + 1 have landed in LDS once the loads requested after them are the only ones outstanding:
         // the three table reads that front_of leaves in flight, or the words requested behind the rows
         if (!kBack) wait_loads_but(std::integral_constant<unsigned, 3>{});
-        else if (kBBufs == 1) wait_loads_but(std::integral_constant<unsigned, kFetchLoads>{});
         else wait_loads_but(std::integral_constant<unsigned, 0>{});
         read_a();
         __syncthreads();
@@ -1842,7 +1841,7 @@ static int launch_panel(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx
     if (ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
     const dim3 grid(strips, passes, ksplit);
     constexpr int kTerms = Mma<X2>::kTerms;
-    const size_t lds = ctx->lay.lds_bytes + (size_t)(kTerms == 1 ? 2 : 1) * (4 * 3 * 1024 * kTerms) + (size_t)kPanelWaves * 7 * 1024;
+    const size_t lds = kPanelLds<kTerms>;
     if (int rc = set_lds<panel_kernel<FMT, X2, MULTI>>(ctx, lds)) return rc;
     hipLaunchKernelGGL((panel_kernel<FMT, X2, MULTI>), grid, dim3(64 * kPanelWaves), lds, st, ctx->d_blob, ctx->lay, d_idx,
                        reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, (int)ksplit, items, d_y);
