@@ -1728,18 +1728,21 @@ static int launch_encode(llvq_ctx* ctx, const int8_t* d_x, size_t n, void* d_idx
 }
 
 // nearest-direction search of n blocks whose rows start ldw floats apart
-static int launch_search(llvq_ctx* ctx, int metric, const float* d_w, size_t ldw, size_t n, int8_t* d_points, float* d_score, hipStream_t st) {
+// step: each vector goes through a step of the block-wise loop as well (metric: angular, d_w: step->W)
+static int launch_search(llvq_ctx* ctx, int metric, const float* d_w, size_t ldw, size_t n, int8_t* d_points, float* d_score, hipStream_t st,
+                         const RetractStep* step = nullptr) {
     // two workgroups of four waves per compute unit (two waves per SIMD: the bounds of 8192 pairs fill the registers)
     const int grid = (int)std::min<size_t>((n + kSearchWaves - 1) / kSearchWaves, (size_t)2 * ctx->num_cu);
-    const size_t lds = (kSearchTabDwords + kSearchWaves * kSearchScratch) * sizeof(uint32_t);
-#define LLVQ_LAUNCH_SEARCH(METRIC)                                                                                                          \
+    const size_t lds = (kSearchTabDwords + kSearchWaves * kSearchScratch + (step ? 24 * 24 : 0)) * sizeof(uint32_t);
+#define LLVQ_LAUNCH_SEARCH(METRIC, RETRACT)                                                                                                 \
     do {                                                                                                                                    \
-        if (int rc = set_lds<search_kernel<METRIC>>(ctx, lds)) return rc;                                                                   \
-        hipLaunchKernelGGL(search_kernel<METRIC>, dim3(grid), dim3(64 * kSearchWaves), lds, st, ctx->d_search, ctx->search_lay,             \
-                           (uint32_t)ctx->m_max, ctx->d_tile_a, ctx->d_tile_scale, d_w, ldw, n, d_points, d_score);                         \
+        if (int rc = set_lds<search_kernel<METRIC, RETRACT>>(ctx, lds)) return rc;                                                          \
+        hipLaunchKernelGGL((search_kernel<METRIC, RETRACT>), dim3(grid), dim3(64 * kSearchWaves), lds, st, ctx->d_search, ctx->search_lay,  \
+                           (uint32_t)ctx->m_max, ctx->d_tile_a, ctx->d_tile_scale, d_w, ldw, n, d_points, d_score, step ? *step : RetractStep{}); \
     } while (0)
-    if (metric == LLVQ_ANGULAR) LLVQ_LAUNCH_SEARCH(LLVQ_ANGULAR);
-    else LLVQ_LAUNCH_SEARCH(LLVQ_EUCLIDEAN);
+    if (step) LLVQ_LAUNCH_SEARCH(LLVQ_ANGULAR, true);
+    else if (metric == LLVQ_ANGULAR) LLVQ_LAUNCH_SEARCH(LLVQ_ANGULAR, false);
+    else LLVQ_LAUNCH_SEARCH(LLVQ_EUCLIDEAN, false);
 #undef LLVQ_LAUNCH_SEARCH
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "search launch");
@@ -2326,25 +2329,19 @@ int llvq_gptq_quantize_levels(llvq_ctx* ctx, float* d_W, int N, int KB, size_t l
     const float one = 1.0f, minus_one = -1.0f;
     for (int t = 0; t < KB; t++) {
         float* Wq = d_W + (size_t)24 * t;
-        // directions of this block column, their indices (strided into the [N][KB] array), gain reset and error
-        if (int rc = launch_search(ctx, LLVQ_ANGULAR, Wq, ldw, (size_t)N, d_pts, nullptr, st)) return rc;
+        const size_t r0 = (size_t)24 * (t + 1);
+        // directions of this block column, gain reset, E U_QQ^-1; the indices (strided into the [N][KB] array)
+        const RetractStep step = {Wq, d_U + (size_t)24 * t * K + (size_t)24 * t, K, r0 < K ? d_E : nullptr, reinterpret_cast<uint16_t*>(d_gain) + t, (size_t)KB,
+                                  reinterpret_cast<const uint16_t*>(d_gain_levels), n_levels};
+        if (int rc = launch_search(ctx, LLVQ_ANGULAR, Wq, ldw, (size_t)N, d_pts, nullptr, st, &step)) return rc;
         void* idx_t = reinterpret_cast<unsigned char*>(d_idx) + isz * (size_t)t;
         const int rc = fmt == LLVQ_IDX_U48 ? launch_encode<LLVQ_IDX_U48>(ctx, d_pts, (size_t)N, idx_t, st, (size_t)KB)
                                            : launch_encode<LLVQ_IDX_U64>(ctx, d_pts, (size_t)N, idx_t, st, (size_t)KB);
         if (rc) return rc;
-        hipLaunchKernelGGL(retract_kernel, dim3((N + 255) / 256), dim3(256), 0, st, Wq, ldw, d_pts, N, d_E,
-                           reinterpret_cast<uint16_t*>(d_gain) + t, (size_t)KB, reinterpret_cast<const uint16_t*>(d_gain_levels), n_levels);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(ctx, e, "gptq step launch");
-        const size_t r0 = (size_t)24 * (t + 1);
         if (r0 >= K) break;
-        // W[:, R] -= (E U_QQ^-1) U_QR.  Row-major arrays seen column-major: E^T (24 x N), U^T (lower triangular)
-        const float* Uqq = d_U + (size_t)24 * t * K + (size_t)24 * t;
-        rocblas_status bs = rocblas_strsm(ctx->blas, rocblas_side_left, rocblas_fill_lower, rocblas_operation_none,
-                                          rocblas_diagonal_non_unit, 24, N, &one, Uqq, (rocblas_int)K, d_E, 24);
-        if (bs == rocblas_status_success)
-            bs = rocblas_sgemm(ctx->blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)(K - r0), N, 24, &minus_one,
-                               d_U + (size_t)24 * t * K + r0, (rocblas_int)K, d_E, 24, &one, d_W + r0, (rocblas_int)ldw);
+        // W[:, R] -= (E U_QQ^-1) U_QR.  Row-major arrays seen column-major
+        const rocblas_status bs = rocblas_sgemm(ctx->blas, rocblas_operation_none, rocblas_operation_none, (rocblas_int)(K - r0), N, 24, &minus_one,
+                                                d_U + (size_t)24 * t * K + r0, (rocblas_int)K, d_E, 24, &one, d_W + r0, (rocblas_int)ldw);
         if (bs != rocblas_status_success) { ctx->set_error(std::string("rocblas: ") + rocblas_status_to_string(bs)); return LLVQ_EHIP; }
     }
     return LLVQ_OK;

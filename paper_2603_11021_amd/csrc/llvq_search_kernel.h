@@ -453,64 +453,94 @@ __device__ __forceinline__ int search_block(const llvq::SearchRec* __restrict__ 
     return lane < 24u ? x : 0;
 }
 
-template <int METRIC>
+// One step of the block-wise loop of paper App. B (Alg. 1), per row: the block v = W[row][0..23] that has been given its nearest
+// direction x is replaced by g * x / ||x|| with g = ||v|| rounded to fp16 (the norm-preserving "gain reset" of paper
+// Sec. 3.3), and E U_QQ^-1 for the error E = v - g x / ||x|| is kept for the propagation.
+// levels != nullptr: the optional scalar gain quantiser of App. B Alg. 1 -- g is the nearest of n_levels fp16
+// reconstruction levels (ascending; ties go to the lower level) instead of the rounded norm.
+struct RetractStep {
+    float* W;                     // the block column, rows ldw apart
+    const float* U;               // its diagonal block of the factor, rows ldu apart
+    size_t ldu;
+    float* E;                     // [rows][24]; nullptr: the last block column, nothing to propagate to
+    uint16_t* gain;               // of the block column, gain_stride apart
+    size_t gain_stride;
+    const uint16_t* levels;
+    int n_levels;
+};
+
+// v and x: coordinate of lane i < 24 (other lanes: 0); U: the diagonal block in LDS, [24][24].  Written as part of
+// search_kernel: a lane's coordinates are in registers there, and two launches of the loop (11.8 us of arithmetic and dispatch
+// per block column of 4096 rows, of 95 us in all) go.
+__device__ __forceinline__ void retract_row(const RetractStep& step, size_t row, size_t ldw, float v, int xi, const float* U) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const float x = (float)xi;
+    float n2 = 0.0f, x2 = 0.0f;
+#pragma unroll
+    for (uint32_t i = 0; i < 24u; i++) {
+        const float vi = lane_value(v, i), xv = lane_value(x, i);
+        n2 = fmaf(vi, vi, n2);
+        x2 = fmaf(xv, xv, x2);
+    }
+    const float norm = sqrtf(n2);
+    __half gh = __float2half_rn(norm);
+    if (step.levels) {
+        // the nearest level of every 64th, then the nearest of the lanes' (the lowest of equals)
+        float best = INFINITY;
+        uint32_t k_best = 0xFFFFFFFFu;
+        for (uint32_t k = lane; k < (uint32_t)step.n_levels; k += 64u) {
+            const float d = fabsf(norm - __half2float(__ushort_as_half(step.levels[k])));
+            if (d < best) { best = d; k_best = k; }
+        }
+        const float d_min = -wave_max(-best);
+        if (d_min < INFINITY) {
+            uint32_t k = best == d_min ? k_best : 0xFFFFFFFFu;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) k = min(k, (uint32_t)__shfl_xor((int)k, off));
+            gh = __ushort_as_half(step.levels[k]);
+        }
+    }
+    const float q = __half2float(gh) / sqrtf(x2) * x;
+    if (lane < 24u) step.W[row * ldw + lane] = q;
+    if (lane == 0) step.gain[row * step.gain_stride] = __half_as_ushort(gh);
+    if (!step.E) return;
+    // e U_QQ = E: column i is final once the columns before it are taken out
+    float e = v - q;
+#pragma unroll
+    for (uint32_t i = 0; i < 24u; i++) {
+        const float u = U[i * 24u + min(lane, 23u)];
+        const float ei = lane_value(e, i) / lane_value(u, i);
+        e = lane == i ? ei : lane > i ? fmaf(-ei, u, e) : e;
+    }
+    if (lane < 24u) step.E[row * 24 + lane] = e;
+}
+
+// RETRACT: the vectors are the rows of step.W (w_in is not used), and every one goes through a step of the block-wise loop
+template <int METRIC, bool RETRACT>
 __global__ void __launch_bounds__(64 * kSearchWaves, 2) search_kernel(const llvq::SearchRec* __restrict__ recs, llvq::SearchLayout lay, uint32_t m_max,
                                                                      const uint4* __restrict__ tile_a, const float* __restrict__ tile_scale,
                                                                      const float* __restrict__ w_in, size_t ldw, size_t n, int8_t* __restrict__ pts,
-                                                                     float* __restrict__ score_out) {
+                                                                     float* __restrict__ score_out, RetractStep step) {
     uint32_t* lds = reinterpret_cast<uint32_t*>(g_lds);
     const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const SearchTabs T = load_search_tabs<METRIC>(lds, lay, tile_a, tile_scale);
     const SearchScratch scr = search_scratch(lds + kSearchTabDwords + wave * kSearchScratch);
+    float* U = reinterpret_cast<float*>(lds + kSearchTabDwords + kSearchWaves * kSearchScratch);
     for (uint32_t i = lane; i < 384u; i += 64u) scr.delta[i] = 0u;   // k = 26..31 stay zero
+    if constexpr (RETRACT) {
+        for (uint32_t i = threadIdx.x; i < 24u * 24u; i += blockDim.x) U[i] = step.U[(size_t)(i / 24u) * step.ldu + i % 24u];
+    }
     __syncthreads();
     const SearchSigns S = search_signs();
     for (size_t v = (size_t)blockIdx.x * kSearchWaves + wave; v < n; v += (size_t)gridDim.x * kSearchWaves) {
-        const float wi = lane < 24u ? w_in[ldw * v + lane] : 0.0f;
+        const float wi = lane < 24u ? (RETRACT ? step.W : w_in)[ldw * v + lane] : 0.0f;
         float score;
         uint32_t rec;
         const int x = search_block<METRIC>(recs, lay, m_max, T, S, scr, wi, score, rec);
         if (lane < 24u) pts[24 * v + lane] = (int8_t)x;
-        if (lane == 0 && score_out) score_out[v] = score;
+        if constexpr (RETRACT) retract_row(step, v, ldw, wi, x, U);
+        else if (lane == 0 && score_out) score_out[v] = score;
     }
-}
-
-// One step of the block-wise loop of paper App. B (Alg. 1): for every row the block v = W[row][0..23] has been
-// given its nearest direction x (pts); the block is replaced by g * x / ||x|| with g = ||v|| rounded to fp16 (the
-// norm-preserving "gain reset" of paper Sec. 3.3), and the error E = v - g x/||x|| is kept for the propagation.
-// levels != nullptr: the optional scalar gain quantiser of App. B Alg. 1 -- g is the nearest of n_levels fp16
-// reconstruction levels (ascending; ties go to the lower level) instead of the rounded norm.
-__global__ void retract_kernel(float* __restrict__ W, size_t ldw, const int8_t* __restrict__ pts, int N,
-                               float* __restrict__ E, uint16_t* __restrict__ gain, size_t gain_stride,
-                               const uint16_t* __restrict__ levels, int n_levels) {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= N) return;
-    float v[24], x[24], n2 = 0.0f, x2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 24; i++) {
-        v[i] = W[(size_t)row * ldw + i];
-        x[i] = (float)pts[(size_t)row * 24 + i];
-        n2 = fmaf(v[i], v[i], n2);
-        x2 = fmaf(x[i], x[i], x2);
-    }
-    const float norm = sqrtf(n2);
-    __half gh = __float2half_rn(norm);
-    if (levels) {
-        float best = INFINITY;
-        for (int k = 0; k < n_levels; k++) {
-            const __half lv = __ushort_as_half(levels[k]);
-            const float d = fabsf(norm - __half2float(lv));
-            if (d < best) { best = d; gh = lv; }
-        }
-    }
-    const float scale = __half2float(gh) / sqrtf(x2);
-#pragma unroll
-    for (int i = 0; i < 24; i++) {
-        const float q = scale * x[i];
-        W[(size_t)row * ldw + i] = q;
-        E[(size_t)row * 24 + i] = v[i] - q;
-    }
-    gain[(size_t)row * gain_stride] = __half_as_ushort(gh);
 }
 
 }  // namespace
