@@ -1,0 +1,60 @@
+"""llvq_matmul and llvq_matmul_multi at 33 <= M < 384: slices of K that share activation tiles and are added in LDS.  Sizes at the
+edges of its token tiles (32 per tile, up to four per pass), row tiles (64 and 128 rows per workgroup) and slices (block pairs
+dealt to four or eight slices of one or more workgroups: fewer pairs than slices, an odd block count, a row of one block)."""
+import numpy as np
+import pytest
+
+from paper_2603_11021_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2603_11021_amd import LLVQ
+    return LLVQ(13, 0)
+
+
+def _dev(a):
+    import torch
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _bound(xd):
+    # fp16 weights carry 2^-11 per weight (a single block, M * N draws: below 2^-11 * 4); bf16 weights enter as two terms (2^-16)
+    return 2e-3 if xd == "f16" else 1e-4
+
+
+def _activations(x, xd):
+    import torch
+    return _dev(x).to(torch.float16 if xd == "f16" else torch.bfloat16)
+
+
+@pytest.mark.parametrize("xd", ["f16", "bf16"])
+@pytest.mark.parametrize("N,KB,M", [(1, 2, 33), (31, 1, 64), (33, 3, 64), (64, 2, 65), (65, 7, 96), (127, 8, 97), (129, 16, 128), (128, 17, 129),
+                                    (63, 33, 192), (130, 5, 193), (97, 9, 256), (96, 10, 383), (40, 171, 160), (257, 40, 34)])
+def test_slices_match_the_oracle(gpu, oracle13, N, KB, M, xd):
+    idx, gain, x = synth.layer(8, 5000 + N + 7 * KB + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    import torch
+    y = torch.full((M, N), float("nan"), device="cuda:0")                 # every element has to be written
+    gpu.llvq_matmul(_activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1)), N, KB, out=y)
+    ref = oracle13.matmul(x, idx, gain)
+    err = np.abs(y.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()
+    assert err <= _bound(xd), err
+
+
+@pytest.mark.parametrize("Ns,KB,M,xd", [((64, 1, 130, 65), 6, 33, "f16"), ((129, 128), 11, 100, "bf16"), ((5, 300, 33), 2, 383, "bf16")])
+def test_slices_of_several_matrices(gpu, oracle13, Ns, KB, M, xd):
+    import torch
+    parts = [synth.layer(8, 6000 + i + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16") for i, N in enumerate(Ns)]
+    x = parts[0][2]
+    outs = [torch.full((M, N), float("nan"), device="cuda:0") for N in Ns]
+    gpu.llvq_matmul_multi(_activations(x, xd), [_dev(synth.pack_u48(p[0]).reshape(-1)) for p in parts], [_dev(p[1].reshape(-1)) for p in parts], list(Ns), KB,
+                          outs=outs)
+    for p, y in zip(parts, outs):
+        ref = oracle13.matmul(x, p[0], p[1])
+        err = np.abs(y.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()
+        assert err <= _bound(xd), err
