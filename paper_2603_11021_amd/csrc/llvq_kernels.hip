@@ -1184,7 +1184,7 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
 // The decode of a step is spread over two steps of its wave: class search and digits while the wave's half is off
 // duty, placement, signs and scaling in the step before the weights are needed.
 constexpr int kPanelRows = 128, kPanelTokens = 512, kPanelWaves = 8;
-constexpr int kPanelMinM = 384;
+constexpr int kPanelMinM = 384, kPanelLongMinM = 257;             // see panel_fits
 // LDS: the tables without the int8 values, two buffers of decoded weights ([term][row tile][k group][lane] x 16 bytes) and the
 // waves' token rows.  For bf16 (two terms per weight) that is 448 bytes short of all there is; with one buffer and a barrier
 // between the products and the decode the seven layers of a Llama-3-8B-shaped block took 1189 us at M = 1024, not 1071.
@@ -1855,9 +1855,13 @@ static int launch_panel(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx
 // whether a product with this many strips of 128 rows takes the panel kernel: from kPanelMinM tokens on, when there are
 // panels for at least a sixteenth of the chip (the rest comes from splitting the rows' block pairs, at least 16 steps
 // per part; measured on Llama-3-8B shapes: 4096 rows at M = 512 take 72 us against 92 us in the strip kernel, 1024 rows
-// are level at M = 1024 and slower below); activation offsets inside the kernel are 32-bit byte offsets
+// are level at M = 1024 and slower below); activation offsets inside the kernel are 32-bit byte offsets.  From
+// kPanelLongMinM tokens on, where slice_kernel needs a third pass, only if every compute unit gets 32 steps or more
+// (M = 280, fp16 and bf16 against slice_kernel: 4096 x 14352 110 / 144 us against 125 / 147; 4096 x 4104 54 / 68 against 50 / 55;
+// 14336 x 1008 47 / 63 against 48 / 55; seven layers of a Llama-3-8B-shaped block at M = 320 443 / 584 against 564 / 678)
 static bool panel_fits(const llvq_ctx* ctx, int M, uint64_t strips, int KB) {
-    return M >= kPanelMinM && (uint64_t)M * (uint64_t)KB * 48u < (1ull << 32) &&
+    const bool many_steps = strips * (((uint64_t)KB + 1) / 2) >= (uint64_t)ctx->num_cu * 32u;
+    return M >= (many_steps ? kPanelLongMinM : kPanelMinM) && (uint64_t)M * (uint64_t)KB * 48u < (1ull << 32) &&
            strips * (uint64_t)((M + kPanelTokens - 1) / kPanelTokens) * 16u >= (uint64_t)ctx->num_cu;
 }
 
@@ -1984,15 +1988,17 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
     // prefill: the 128-row strips of all matrices in one launch when at least one of them has panels for less than half
     // of the chip (small matrices such as k and v then run at the rate of the large ones; matrices that fill the chip
     // on their own gain nothing from sharing a launch and lose to the uneven last round)
-    bool small_item = false;
-    for (int i = 0; i < n_items; i++)
+    bool small_item = false, all_panels = true;          // all_panels: each of the matrices takes the panel kernel on its own
+    for (int i = 0; i < n_items; i++) {
+        all_panels = all_panels && panel_fits(ctx, M, (uint64_t)((N[i] + kPanelRows - 1) / kPanelRows), KB);
         small_item = small_item || (uint64_t)((N[i] + kPanelRows - 1) / kPanelRows) * (uint64_t)((M + kPanelTokens - 1) / kPanelTokens) * 2u < (uint64_t)ctx->num_cu;
+    }
     if (n_items > 1 && small_item && panel_fits(ctx, M, (uint64_t)strips, KB)) {
         if (x_dtype == LLVQ_F16)
             return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
         return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
-    if (n_items == 1 || KB == 1 || panel_fits(ctx, M, 1u << 20, KB)) {
+    if (n_items == 1 || KB == 1 || all_panels || (M >= kPanelMinM && panel_fits(ctx, M, 1u << 20, KB))) {
         // one matrix, single-block rows (see launch_any_matmul), or matrices that take the panel kernel each on its own: one
         // product after the other
         for (int i = 0; i < n_items; i++)

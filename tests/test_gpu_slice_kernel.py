@@ -46,6 +46,20 @@ def test_slices_match_the_oracle(gpu, oracle13, N, KB, M, xd):
     assert err <= _bound(xd), err
 
 
+@pytest.mark.parametrize("N,KB,M,xd", [(12801, 164, 257, "bf16"), (12801, 164, 320, "f16"), (4000, 512, 383, "bf16"), (12801, 164, 256, "f16")])
+def test_long_layers_on_either_side_of_a_third_pass(gpu, oracle13, N, KB, M, xd):
+    """257 <= M < 384 on layers with many steps: the panel kernel with up to half of its waves' tokens past M"""
+    import torch
+    idx, gain, x = synth.layer(8, 7000 + N + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    y = torch.full((M, N), float("nan"), device="cuda:0")
+    gpu.llvq_matmul(_activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1)), N, KB, out=y)
+    assert not torch.isnan(y).any()
+    rows = np.concatenate([np.arange(8), np.arange(N - 8, N), np.random.default_rng(N + M).choice(N, 24, replace=False)])
+    ref = oracle13.matmul(x, idx[rows], gain[rows])
+    err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+    assert err <= _bound(xd), err
+
+
 @pytest.mark.parametrize("Ns,KB,M,xd", [((64, 1, 130, 65), 6, 33, "f16"), ((129, 128), 11, 100, "bf16"), ((5, 300, 33), 2, 383, "bf16")])
 def test_slices_of_several_matrices(gpu, oracle13, Ns, KB, M, xd):
     import torch
