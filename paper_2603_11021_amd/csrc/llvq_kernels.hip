@@ -21,6 +21,7 @@
 #include "../../include/llvq.h"
 #include "llvq_decode_core.h"
 #include "llvq_encode_core.h"
+#include "llvq_slices.h"
 #include "llvq_tables.h"
 #include "llvq_wide.h"
 
@@ -1011,18 +1012,12 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
     // 2 h + 1, and swapping the upper lanes of the first with the lower lanes of the second leaves every lane the word of its
     // block in either step.  The vector cache looks up one lane at a time: one load of 12 bytes and one of two gains cost it a
     // third of what three narrow loads per step did.
-    const size_t blk0 = (size_t)row0 * (size_t)KB;
-    const unsigned char* idx0 = reinterpret_cast<const unsigned char*>(idx) + blk0 * kWordBytes<FMT>;
-    const unsigned char* gain0 = cd.gain_array() ? reinterpret_cast<const unsigned char*>(gain + blk0) : idx0;
-    const uint32_t kl0 = (uint32_t)(min(wrow, N - 1) - row0) * (uint32_t)KB;           // at most 127 rows of fewer than 2^24 blocks
-    const size_t left = (size_t)(N - row0) * (size_t)KB;                               // blocks from the strip's first to the matrix's last
-    const uint32_t kl_last = (uint32_t)min(left, (size_t)0x80000000u) - 1u;
+    const llvq::SliceWords sw = llvq::slice_words(row0, wrow, N, KB);
+    const unsigned char* idx0 = reinterpret_cast<const unsigned char*>(idx) + sw.first * kWordBytes<FMT>;
+    const unsigned char* gain0 = cd.gain_array() ? reinterpret_cast<const unsigned char*>(gain + sw.first) : idx0;
     struct Two { uint32_t q[4], g; bool late; };
     auto fetch_two = [&](uint32_t st, bool real, Two& r) {
-        // the last word of the matrix is read as the second of a pair (a matrix of one block is not given to this kernel)
-        const uint32_t k = kl0 + min(2 * (st + (uint32_t)half), (uint32_t)KB - 1);
-        r.late = k >= kl_last;
-        const uint32_t kk = real ? r.late ? k - 1 : k : 0;
+        const uint32_t kk = llvq::slice_pair(sw, st, (uint32_t)half, (uint32_t)KB, real, r.late);
         const unsigned char* p = idx0 + (size_t)kk * kWordBytes<FMT>;
         if constexpr (FMT == LLVQ_IDX_U64) {
             typedef uint32_t u32x4_a8 __attribute__((ext_vector_type(4), aligned(8)));

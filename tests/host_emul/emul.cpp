@@ -6,6 +6,7 @@
 
 #include "../../paper_2603_11021_amd/csrc/llvq_decode_core.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_encode_core.h"
+#include "../../paper_2603_11021_amd/csrc/llvq_slices.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_tables.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_wide.h"
 
@@ -86,6 +87,35 @@ uint64_t emul_wide_tab_decode_i8(const uint64_t* idx, uint64_t n, int8_t* out) {
         std::memcpy(out + 24 * k, o, 24);
     }
     return bad;
+}
+
+// ---- the words slice_kernel reads ---------------------------------------------------------------------------
+// Walks every lane of every strip of `strip_rows` rows through the pairs it fetches (all steps of a row, or the first and the
+// last 64 of a long one) and returns how many of them do not lie inside the N x KB words or do not hold the lane's block where
+// `late` says it is.
+uint64_t emul_slice_pairs_wrong(int N, int KB, int strip_rows) {
+    uint64_t wrong = 0;
+    const int64_t words = (int64_t)N * KB;
+    const int steps = (KB + 1) / 2;
+    for (int row0 = 0; row0 < N; row0 += strip_rows)
+        for (int r = 0; r < strip_rows; r++) {
+            const llvq::SliceWords sw = llvq::slice_words(row0, row0 + r, N, KB);
+            const int row = row0 + r < N ? row0 + r : N - 1;
+            for (int st = 0; st < steps; st = (st == 63 && steps > 128) ? steps - 64 : st + 1)
+                for (int half = 0; half < 2; half++)
+                    for (int real = 0; real < 2; real++) {
+                        bool late = false;
+                        const uint32_t kk = llvq::slice_pair(sw, (uint32_t)st, (uint32_t)half, (uint32_t)KB, real != 0, late);
+                        const int64_t pair = (int64_t)sw.first + (int64_t)(uint64_t)kk;      // kk is an unsigned offset in the kernel too
+                        bool ok = pair >= 0 && pair + 1 < words;
+                        if (real) {
+                            const int b = 2 * (st + half) < KB ? 2 * (st + half) : KB - 1;
+                            ok = ok && pair + (late ? 1 : 0) == (int64_t)row * KB + b;
+                        }
+                        wrong += !ok;
+                    }
+        }
+    return wrong;
 }
 
 }  // extern "C"

@@ -4,7 +4,7 @@ dealt to four or eight slices of one or more workgroups: fewer pairs than slices
 import numpy as np
 import pytest
 
-from paper_2603_11021_amd import synth
+from paper_2603_11021_amd import LLVQ_IDX_U24, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -71,4 +71,27 @@ def test_slices_of_several_matrices(gpu, oracle13, Ns, KB, M, xd):
     for p, y in zip(parts, outs):
         ref = oracle13.matmul(x, p[0], p[1])
         err = np.abs(y.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()
+        assert err <= _bound(xd), err
+
+
+@pytest.mark.parametrize("M,xd", [(33, "f16"), (100, "bf16")])
+@pytest.mark.parametrize("N", [65, 129, 193])
+def test_last_strip_of_a_single_block(gpu, oracle13, N, M, xd):
+    """One block per row and one row in the last strip: its word is read as the second of a pair, in every word format"""
+    import torch
+    idx, gain, x = synth.layer(8, 8000 + N + M, N, 24, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    d_x, d_gain = _activations(x, xd), _dev(gain.reshape(-1))
+    ref = oracle13.matmul(x, idx, gain)
+    base = gpu.llvq_shell_offset(3)
+    words3 = idx % np.uint64(gpu.llvq_shell_offset(4) - base)                 # 24-bit words address shell 3
+    ref3 = oracle13.matmul(x, words3 + np.uint64(base), gain)
+
+    def out():
+        return torch.full((M, N), float("nan"), device="cuda:0")
+
+    d48, d64, d24 = _dev(synth.pack_u48(idx).reshape(-1)), _dev(idx.view(np.int64).reshape(-1)), _dev(synth.pack_u24(words3).reshape(-1))
+    for y, want in ((gpu.llvq_matmul(d_x, d48, d_gain, N, 1, out=out()), ref), (gpu.llvq_matmul(d_x, d64, d_gain, N, 1, out=out()), ref),
+                    (gpu.llvq_matmul_coded(d_x, d24, N, 1, 24, base, gain=d_gain, fmt=LLVQ_IDX_U24, out=out()), ref3),
+                    (gpu.llvq_matmul_multi(d_x, [d48, d48], [d_gain, d_gain], [N, N], 1, outs=[out(), out()])[1], ref)):
+        err = np.abs(y.cpu().numpy().astype(np.float64) - want).max() / np.abs(want).max()
         assert err <= _bound(xd), err
