@@ -929,7 +929,7 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
 // things these do before they wait themselves, so every wait ends.
 // Llama-3-8B-shaped block (seven layers): M = 64 242 -> 197 us (bf16), M = 250 520 -> 352 us (fp16), M = 128 203 us, against the
 // split-K kernel (M <= 64) and the strip kernel with two waves per SIMD.
-template <int TT> constexpr int kSliceTiles = TT <= 2 ? 2 : 4;           // 32-row tiles per workgroup
+template <int TT> constexpr int kSliceTiles = llvq::slice_tiles(TT);      // 32-row tiles per workgroup
 constexpr uint32_t kSliceTabBytes = Lay13::kOffVti;                                        // class records and small tables; Golay words and planes in global memory
 constexpr uint32_t kSliceXOff = (kSliceTabBytes + 511u) & ~511u;
 template <int TT> constexpr uint32_t kSliceXBuf = TT * 3072u;                              // one step of one slice: 32 TT tokens x 96 bytes
@@ -1785,45 +1785,30 @@ static void clear_y(const MatItems* items, int n_items, int M, int N, float* d_y
     }
 }
 
-// How many workgroups share the block pairs of a row in slice_kernel.  Estimated time in us: rounds of workgroups x (steps of
-// a slice x the time of a step + tables and final sum), and, when the rows are split, 335 atomics per ns and the clearing
-// of y (all measured).
-static int slice_ksplit(const llvq_ctx* ctx, int TT, int slices, uint64_t wgs, int KB, int M, uint64_t rows) {
-    const uint64_t spt = ((uint64_t)KB + 1) / 2;
-    const double step = TT == 2 ? 2.7 : TT == 3 ? 3.1 : 3.6;
-    double best = 0.0;
-    int ks_best = 1;
-    for (uint64_t ks = 1; ks <= 64 && (ks == 1 || ks * slices <= spt); ks++) {
-        const uint64_t rounds = (wgs * ks + ctx->num_cu - 1) / ctx->num_cu;
-        const double t = (double)rounds * ((double)((spt + ks * slices - 1) / (ks * slices)) * step + 6.0) +
-                         (ks > 1 ? (double)ks * (double)M * (double)rows / 335e3 + 3.0 : 0.0);
-        if (ks == 1 || t < best) { best = t; ks_best = (int)ks; }
-    }
-    return ks_best;
-}
-
 template <int FMT, typename X2, int TT, bool MULTI>
-static int launch_slice_cfg(llvq_ctx* ctx, const void* d_x, int M, int passes, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
-                            MatItems items, int n_items) {
-    constexpr int kRows = 32 * kSliceTiles<TT>;
-    const int strips = MULTI ? set_strips(items, kRows) : (N + kRows - 1) / kRows;
-    const int ksplit = slice_ksplit(ctx, TT, 16 / kSliceTiles<TT>, (uint64_t)strips * passes, KB, M, (uint64_t)N);
-    if (ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
+static int launch_slice_cfg(llvq_ctx* ctx, const llvq::SlicePlan& plan, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB,
+                            float* d_y, hipStream_t st, MatItems items, int n_items) {
+    const int strips = MULTI ? set_strips(items, plan.strip_rows) : (N + plan.strip_rows - 1) / plan.strip_rows;
+    if (plan.ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
     if (int rc = set_lds<slice_kernel<FMT, X2, TT, MULTI>>(ctx, kSliceLds<TT>)) return rc;
-    hipLaunchKernelGGL((slice_kernel<FMT, X2, TT, MULTI>), dim3((unsigned)strips, (unsigned)passes, (unsigned)ksplit), dim3(kThreads), kSliceLds<TT>, st,
-                       ctx->d_blob, ctx->lay, d_idx, reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, ksplit, items, d_y);
+    hipLaunchKernelGGL((slice_kernel<FMT, X2, TT, MULTI>), dim3((unsigned)strips, (unsigned)plan.passes, (unsigned)plan.ksplit), dim3(kThreads), kSliceLds<TT>, st,
+                       ctx->d_blob, ctx->lay, d_idx, reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, plan.ksplit, items, d_y);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "slice matmul launch");
 }
 
-// passes of at most 128 tokens, as even as token tiles of 32 allow
+// MULTI: N is the number of rows of all matrices of `items` together
 template <int FMT, typename X2, bool MULTI = false>
 static int launch_slice(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
                         const MatItems& items = MatItems{}, int n_items = 1) {
-    const int tiles = (M + 31) / 32, passes = (tiles + 3) / 4, per_pass = (tiles + passes - 1) / passes;
-    if (per_pass <= 2) return launch_slice_cfg<FMT, X2, 2, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
-    if (per_pass == 3) return launch_slice_cfg<FMT, X2, 3, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
-    return launch_slice_cfg<FMT, X2, 4, MULTI>(ctx, d_x, M, passes, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+    int rows[kMaxItems] = {N};
+    if (MULTI) {
+        for (int i = 0; i < n_items; i++) rows[i] = items.row_end[i] - (i ? items.row_end[i - 1] : 0);
+    }
+    const llvq::SlicePlan plan = llvq::slice_plan(ctx->num_cu, M, KB, rows, n_items);
+    if (plan.token_tiles == 2) return launch_slice_cfg<FMT, X2, 2, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+    if (plan.token_tiles == 3) return launch_slice_cfg<FMT, X2, 3, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+    return launch_slice_cfg<FMT, X2, 4, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
 }
 
 // MULTI: N is not used; the strips are those of `items`

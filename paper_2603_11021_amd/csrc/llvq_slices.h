@@ -1,9 +1,57 @@
-// Where slice_kernel reads its words: plain integer arithmetic, one source for the kernel and for the host test that walks it
-// over whole matrices.
+// Integer arithmetic of slice_kernel that host tests walk over whole ranges of sizes: how a product is cut into workgroups, and
+// where the kernel reads its words.
 #pragma once
 #include "llvq_decode_core.h"
 
 namespace llvq {
+
+// Products whose partial sums llvq.h promises to add in the same order from call to call (M > 64): those with more strips of 256
+// rows x 256 tokens (128 x 512 from M = 384 on) than half the compute units.  slice_kernel needs no atomics there.
+inline bool fixed_order(int num_cu, int M, int N) {
+    if (M <= 64) return false;
+    const int64_t rows = M < 384 ? 256 : 128, tokens = M < 384 ? 256 : 512;
+    return ((N + rows - 1) / rows) * ((M + tokens - 1) / tokens) * 2 > num_cu;
+}
+
+// 32-row tiles per workgroup and slices of K per workgroup for passes of TT token tiles
+constexpr int slice_tiles(int TT) { return TT <= 2 ? 2 : 4; }
+
+struct SlicePlan {
+    int token_tiles;     // tiles of 32 tokens per pass: 2, 3 or 4
+    int passes;
+    int strip_rows;
+    int ksplit;          // workgroups that share the block pairs of a row
+};
+
+// n_items matrices of N[i] rows and KB blocks per row in one launch.  Passes of at most 128 tokens, as even as token tiles
+// allow.  The split: the smallest estimated time in us, rounds of workgroups x (steps of a slice x the time of a step + tables
+// and final sum), and, when the rows are split, 335 atomics per ns and the clearing of y (all measured).
+inline SlicePlan slice_plan(int num_cu, int M, int KB, const int* N, int n_items) {
+    SlicePlan p;
+    const int tiles = (M + 31) / 32;
+    p.passes = (tiles + 3) / 4;
+    const int per_pass = (tiles + p.passes - 1) / p.passes;
+    p.token_tiles = per_pass <= 2 ? 2 : per_pass;
+    p.strip_rows = 32 * slice_tiles(p.token_tiles);
+    const uint64_t slices = (uint64_t)(16 / slice_tiles(p.token_tiles)), spt = ((uint64_t)KB + 1) / 2;
+    uint64_t wgs = 0, rows = 0;
+    bool split = true;
+    for (int i = 0; i < n_items; i++) {
+        wgs += (uint64_t)((N[i] + p.strip_rows - 1) / p.strip_rows) * (uint64_t)p.passes;
+        rows += (uint64_t)N[i];
+        split = split && !fixed_order(num_cu, M, N[i]);
+    }
+    const double step = p.token_tiles == 2 ? 2.7 : p.token_tiles == 3 ? 3.1 : 3.6;
+    double best = 0.0;
+    p.ksplit = 1;
+    for (uint64_t ks = 1; ks <= 64 && (ks == 1 || (split && ks * slices <= spt)); ks++) {
+        const uint64_t rounds = (wgs * ks + num_cu - 1) / num_cu;
+        const double t = (double)rounds * ((double)((spt + ks * slices - 1) / (ks * slices)) * step + 6.0) +
+                         (ks > 1 ? (double)ks * (double)M * (double)rows / 335e3 + 3.0 : 0.0);
+        if (ks == 1 || t < best) { best = t; p.ksplit = (int)ks; }
+    }
+    return p;
+}
 
 // The words of a row tile, as 32-bit block offsets from block `first` of the matrix (wave-uniform).  Words are read in pairs, so
 // where the strip holds a single block (the last row of a matrix with one block per row) `first` is the block before the

@@ -95,3 +95,22 @@ def test_last_strip_of_a_single_block(gpu, oracle13, N, M, xd):
                     (gpu.llvq_matmul_multi(d_x, [d48, d48], [d_gain, d_gain], [N, N], 1, outs=[out(), out()])[1], ref)):
         err = np.abs(y.cpu().numpy().astype(np.float64) - want).max() / np.abs(want).max()
         assert err <= _bound(xd), err
+
+
+@pytest.mark.parametrize("M,xd", [(65, "bf16"), (256, "f16")])
+def test_many_rows_give_the_same_bits(gpu, oracle13, M, xd):
+    """More strips of 256 rows x 256 tokens than half the compute units: K is not split, also beside a small matrix"""
+    import torch
+    N, KB = 33024, 40
+    idx, gain, x = synth.layer(8, 9000 + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    d_x, d_idx, d_gain = _activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1))
+    y = gpu.llvq_matmul(d_x, d_idx, d_gain, N, KB)
+    for _ in range(3):
+        assert torch.equal(gpu.llvq_matmul(d_x, d_idx, d_gain, N, KB), y)
+    n = 100                                                                   # the first rows as a matrix of their own
+    both = gpu.llvq_matmul_multi(d_x, [d_idx[:6 * KB * n], d_idx], [d_gain[:KB * n], d_gain], [n, N], KB)
+    assert torch.equal(both[1], y) and torch.equal(both[0], y[:, :n])
+    rows = np.concatenate([np.arange(4), np.arange(N - 4, N), np.random.default_rng(M).choice(N, 24, replace=False)])
+    ref = oracle13.matmul(x, idx[rows], gain[rows])
+    err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+    assert err <= _bound(xd), err

@@ -1,4 +1,4 @@
-"""CPU-only: where slice_kernel reads its words, walked lane by lane over whole matrices."""
+"""CPU-only: how slice_kernel cuts a product, and where it reads its words, walked lane by lane over whole matrices."""
 import ctypes
 
 import pytest
@@ -26,3 +26,39 @@ def test_word_pairs_lie_inside_the_matrix(pairs_wrong, strip_rows):
 def test_word_pairs_of_large_matrices(pairs_wrong, N, KB, strip_rows):
     """Up to 2^32 blocks: offsets of a strip near 2^31, more blocks left than 32 bits hold"""
     assert pairs_wrong(N, KB, strip_rows) == 0
+
+
+@pytest.fixture(scope="module")
+def plan(emul):  # noqa: F811
+    def f(M, KB, *Ns, num_cu=256):
+        out = (ctypes.c_int * 4)()
+        emul.lib.emul_slice_plan(num_cu, M, KB, (ctypes.c_int * len(Ns))(*Ns), len(Ns), out)
+        return tuple(out)
+    return f
+
+
+def test_plan_covers_the_tokens(plan):
+    for M in range(33, 1025):
+        tiles, passes, strip_rows, ksplit = plan(M, 171, 4096)
+        assert tiles in (2, 3, 4) and strip_rows == (64 if tiles == 2 else 128)
+        assert 32 * tiles * (passes - 1) < M <= 32 * tiles * passes and ksplit >= 1
+
+
+def _promised(M, N, num_cu=256):
+    """llvq.h: more strips of 256 rows x 256 tokens (128 x 512 from M = 384 on) than half the compute units"""
+    rows, tokens = (256, 256) if M < 384 else (128, 512)
+    return M > 64 and -(-N // rows) * -(-M // tokens) * 2 > num_cu
+
+
+def test_k_is_not_split_where_reproducible_sums_are_promised(plan):
+    Ns = (8192, 8193, 16129, 16384, 16385, 32513, 32768, 32769, 33024, 40000, 65536, 65537, 128256)
+    seen = 0
+    for N in Ns:
+        for M in (65, 96, 97, 128, 129, 160, 250, 256, 257, 320, 383, 384, 513, 1024):
+            for KB in (1, 2, 16, 42, 171, 342, 598, 1195):
+                if _promised(M, N):
+                    seen += 1
+                    assert plan(M, KB, N)[3] == 1, (N, M, KB)
+                    assert plan(M, KB, 1024, N)[3] == 1, (N, M, KB)        # beside a small matrix as well
+    assert seen > 400
+    assert plan(64, 171, 40000)[0] == 2 and plan(128, 171, 1024)[3] > 1      # small products still share their rows
