@@ -1164,6 +1164,143 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
     }
 }
 
+// ---- llvq_matmul, 65 <= M < 384 on large products: a block is decoded once per 256 tokens ---------------------------
+// A workgroup of eight waves owns 256 weight rows (wave w: rows 32 w .. 32 w + 31) x a pass of 256 tokens and walks block pairs of
+// the rows: 128 accumulator registers and two waves per SIMD, so a step (decode of 256 rows x 2 blocks, products with 256
+// tokens) is bound by the chains of dependent table reads, 2.4 us with fp16 and 3.1 us with bf16 weights.  slice_kernel keeps four
+// waves on a SIMD and decodes every block once per 128 tokens (see strip_faster for where either is the faster).  Per step the activation tile (256 tokens x 48 channels) is staged once and read by all waves as A operands; the
+// decoded blocks are B operands straight from the decoder's registers.  The Golay words and inner-word planes are read from
+// global memory, which leaves room for two activation buffers.  65536 x 4104 at M = 256: 239 us (fp16), 308 us (bf16).
+constexpr int kStripWaves = llvq::kStripRows / 32, kStripTiles = llvq::kStripTokens / 32, kStripThreads = 64 * kStripWaves;
+constexpr uint32_t kStripPitch = 112;                  // bytes per token in the staged tile: 96 of data, padded so that rows stay 16-byte
+                                                       // aligned (128-bit LDS accesses) and eight consecutive tokens cover all banks
+constexpr uint32_t kStripABuf = llvq::kStripTokens * kStripPitch, kStripLds = Lay13::kOffVti + 2u * kStripABuf;
+static_assert(kStripThreads == 2 * llvq::kStripTokens, "a thread stages half of a token's step");
+
+template <int FMT, typename X2>
+__global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
+                                                                const void* __restrict__ idx, const uint16_t* __restrict__ gain,
+                                                                const uint32_t* __restrict__ x, int M, int N, int KB, Code cd,
+                                                                int ksplit, float* __restrict__ y) {
+    constexpr int kTerms = Mma<X2>::kTerms;
+    load_tables<kStripThreads>(blob, Lay13::kOffVti);
+    const TabPtrs T = llvq::make_tab_ptrs(lds_origin(), blob, lay);
+    unsigned char* abuf = g_lds + Lay13::kOffVti;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 31, half = lane >> 5;
+    // steps (block pairs) of a row; the workgroups of blockIdx.z share them
+    const uint32_t spt = ((uint32_t)KB + 1) / 2;
+    const uint32_t st_first = (uint32_t)(((uint64_t)spt * blockIdx.z) / (uint32_t)ksplit);
+    const uint32_t st_end = (uint32_t)(((uint64_t)spt * (blockIdx.z + 1)) / (uint32_t)ksplit);
+    const int m0 = (int)blockIdx.y * llvq::kStripTokens;
+    const int wrow = (int)blockIdx.x * llvq::kStripRows + wave * 32 + col;
+
+    // staging: token threadIdx / 2 (past M: a copy of the last one), block threadIdx % 2 of the pair
+    const uint32_t s_part = threadIdx.x & 1u;
+    const uint32_t* s_src = x + (size_t)min(M - 1, m0 + (int)(threadIdx.x >> 1)) * ((size_t)KB * 12);
+    unsigned char* s_dst = abuf + (threadIdx.x >> 1) * kStripPitch + s_part * 48u;
+    auto stage_load = [&](uint32_t st, uint4 (&v)[3]) {
+        const uint32_t b = min(2 * st + s_part, (uint32_t)KB - 1);       // past the last block: any valid data, its weights are zero
+        const uint4* p = reinterpret_cast<const uint4*>(s_src + (size_t)b * 12);
+        v[0] = p[0]; v[1] = p[1]; v[2] = p[2];
+    };
+    auto stage_store = [&](uint32_t buf, const uint4 (&v)[3]) {
+        uint4* d = reinterpret_cast<uint4*>(s_dst + buf * kStripABuf);
+        d[0] = v[0]; d[1] = v[1]; d[2] = v[2];
+    };
+
+    float16_t acc[kStripTiles];
+#pragma unroll
+    for (int t = 0; t < kStripTiles; t++) {
+#pragma unroll
+        for (int v = 0; v < 16; v++) acc[t][v] = 0.0f;
+    }
+    // The word of the next step is requested first, then this step's block is placed, then the next step's class search and
+    // digits run (their reads from global memory are in flight during the products), then the products, then the next
+    // activation tile goes to LDS.
+    struct Blk { RawBlock raw; bool live; };
+    auto fetch_blk = [&](uint32_t st, Blk& q) {
+        const uint32_t b = 2 * st + (uint32_t)half;
+        q.live = wrow < N && b < (uint32_t)KB;
+        const size_t k = (size_t)min(wrow, N - 1) * KB + min(b, (uint32_t)KB - 1);
+        load_raw<FMT>(idx, gain, cd.gain_array(), k, q.raw);
+    };
+    auto front_of = [&](const Blk& q, bool& ok, uint16_t& gb) {
+        uint64_t I;
+        finish_block<FMT>(q.raw, cd, I, gb);
+        ok = q.live && I < T.npoints;
+        return llvq::decode_front<true>(T, llvq::find_class(T, ok ? I : 0));
+    };
+    {
+        uint4 v[3];
+        stage_load(st_first, v);
+        stage_store(st_first & 1u, v);
+    }
+    Blk cur_blk, nxt_blk;
+    fetch_blk(st_first, cur_blk);
+    bool ok_cur = false, ok_nxt = false;
+    uint16_t g_cur = 0, g_nxt = 0;
+    llvq::Front F = front_of(cur_blk, ok_cur, g_cur), Fn;
+    __syncthreads();
+    for (uint32_t st = st_first; st < st_end; st++) {
+        const uint32_t st_next = st + 1 < st_end ? st + 1 : st;          // past the end the last step is requested again
+        uint4 nextv[3];
+        stage_load(st_next, nextv);
+        fetch_blk(st_next, nxt_blk);
+        uint32_t w[4];
+        const llvq::BlockInfo bi = llvq::decode_back(T, F, w);
+        const float scale = ok_cur ? __half2float(__ushort_as_half(g_cur)) * bi.rnorm : 0.0f;
+        uint32_t wt[kTerms][12];
+#pragma unroll
+        for (int c = 0; c < 4; c++) {
+            uint32_t fe, fo, o[kTerms];
+            chunk_fp8(w[c], bi.vt8_lo, bi.vt8_hi, fe, fo);
+            Mma<X2>::weights(fe, false, scale, o);
+#pragma unroll
+            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 0] = o[r];
+            Mma<X2>::weights(fo, false, scale, o);
+#pragma unroll
+            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 1] = o[r];
+            Mma<X2>::weights(fe, true, scale, o);
+#pragma unroll
+            for (int r = 0; r < kTerms; r++) wt[r][3 * c + 2] = o[r];
+        }
+        Fn = front_of(nxt_blk, ok_nxt, g_nxt);
+        // A operands: token 32 t + col, the lane half's block (48 bytes), channel group j.  Channel groups outermost: consecutive
+        // products go to different accumulators and do not wait for each other.
+        const unsigned char* arow = abuf + (st & 1u) * kStripABuf + (uint32_t)col * kStripPitch + (uint32_t)half * 48u;
+#pragma unroll
+        for (int j = 0; j < 3; j++) {
+#pragma unroll
+            for (int t = 0; t < kStripTiles; t++) {
+                const u32x4 a = *reinterpret_cast<const u32x4*>(arow + (uint32_t)t * 32u * kStripPitch + (uint32_t)j * 16u);
+#pragma unroll
+                for (int r = 0; r < kTerms; r++)
+                    acc[t] = Mma<X2>::mma(a, u32x4{wt[r][4 * j], wt[r][4 * j + 1], wt[r][4 * j + 2], wt[r][4 * j + 3]}, acc[t]);
+            }
+        }
+        stage_store((st + 1) & 1u, nextv);
+        F = Fn;
+        ok_cur = ok_nxt;
+        g_cur = g_nxt;
+        __syncthreads();
+    }
+    // y[token][wrow]: register v of tile t belongs to token m0 + 32 t + 8 (v / 4) + 4 half + v % 4
+    if (wrow < N) {
+#pragma unroll
+        for (int t = 0; t < kStripTiles; t++) {
+#pragma unroll
+            for (int v = 0; v < 16; v++) {
+                const int tok = m0 + 32 * t + 8 * (v / 4) + 4 * half + (v % 4);
+                if (tok < M) {
+                    if (ksplit == 1) y[(size_t)tok * N + wrow] = acc[t][v];
+                    else atomicAdd(y + (size_t)tok * N + wrow, acc[t][v]);
+                }
+            }
+        }
+    }
+}
+
 // ---- llvq_matmul, prefill kernel for M >= kPanelMinM: decoded weights shared through LDS ------------------------
 // The index decode costs the vector ALUs and the LDS gather pipe as much per block as 500 tokens cost the matrix cores,
 // so a block should be decoded once per as many tokens as the accumulators can hold.  A workgroup of eight waves owns a
@@ -1805,10 +1942,21 @@ static int launch_slice(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx
     if (MULTI) {
         for (int i = 0; i < n_items; i++) rows[i] = items.row_end[i] - (i ? items.row_end[i - 1] : 0);
     }
-    const llvq::SlicePlan plan = llvq::slice_plan(ctx->num_cu, M, KB, rows, n_items);
+    const llvq::SlicePlan plan = llvq::slice_plan(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, rows, n_items);
     if (plan.token_tiles == 2) return launch_slice_cfg<FMT, X2, 2, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
     if (plan.token_tiles == 3) return launch_slice_cfg<FMT, X2, 3, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
     return launch_slice_cfg<FMT, X2, 4, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
+}
+
+template <int FMT, typename X2>
+static int launch_strip(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st) {
+    const llvq::StripPlan plan = llvq::strip_plan(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, N);
+    if (plan.ksplit > 1) clear_y(nullptr, 1, M, N, d_y, st);
+    if (int rc = set_lds<strip_kernel<FMT, X2>>(ctx, kStripLds)) return rc;
+    hipLaunchKernelGGL((strip_kernel<FMT, X2>), dim3((unsigned)plan.strips, (unsigned)plan.passes, (unsigned)plan.ksplit), dim3(kStripThreads), kStripLds, st, ctx->d_blob, ctx->lay, d_idx,
+                       reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, plan.ksplit, d_y);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "strip matmul launch");
 }
 
 // MULTI: N is not used; the strips are those of `items`
@@ -1853,6 +2001,7 @@ static int launch_any_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* 
         return launch_panel<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= 16) return launch_tile<FMT, X2, 1>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= kTileMaxM) return launch_tile<FMT, X2, 2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+    if (llvq::strip_faster(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, N)) return launch_strip<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     return launch_slice<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
 }
 
@@ -1978,9 +2127,10 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
             return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
         return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
-    if (n_items == 1 || KB == 1 || all_panels || (M >= kPanelMinM && panel_fits(ctx, M, 1u << 20, KB))) {
-        // one matrix, single-block rows (see launch_any_matmul), or matrices that take the panel kernel each on its own: one
-        // product after the other
+    if (n_items == 1 || KB == 1 || all_panels || (M >= kPanelMinM && panel_fits(ctx, M, 1u << 20, KB)) ||
+        llvq::strips_apart(ctx->num_cu, M, KB, x_dtype == LLVQ_BF16, N, n_items)) {
+        // one matrix, single-block rows (see launch_any_matmul), or matrices that take the panel kernel or the strip kernel each on
+        // its own: one product after the other
         for (int i = 0; i < n_items; i++)
             if (int rc = matmul_impl(ctx, d_x, x_dtype, M, d_idx[i], fmt, d_gain[i], cd, N[i], KB, d_y[i], stream)) return rc;
         return LLVQ_OK;

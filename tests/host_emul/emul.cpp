@@ -118,10 +118,13 @@ uint64_t emul_slice_pairs_wrong(int N, int KB, int strip_rows) {
     return wrong;
 }
 
-// the plan of a product of n_items matrices on a device of num_cu compute units: token tiles, passes, rows per strip, split of K
-void emul_slice_plan(int num_cu, int M, int KB, const int* N, int n_items, int* out) {
-    const llvq::SlicePlan p = llvq::slice_plan(num_cu, M, KB, N, n_items);
+// the plan of a product of n_items matrices on a device of num_cu compute units: token tiles, passes, rows per strip and split of K of
+// slice_kernel; split of K of strip_kernel and whether it is taken, for the first matrix
+void emul_slice_plan(int num_cu, int M, int KB, int two_terms, const int* N, int n_items, int* out) {
+    const llvq::SlicePlan p = llvq::slice_plan(num_cu, M, KB, two_terms != 0, N, n_items);
     out[0] = p.token_tiles; out[1] = p.passes; out[2] = p.strip_rows; out[3] = p.ksplit;
+    out[4] = llvq::strip_plan(num_cu, M, KB, two_terms != 0, N[0]).ksplit;
+    out[5] = llvq::strip_faster(num_cu, M, KB, two_terms != 0, N[0]);
 }
 
 }  // extern "C"

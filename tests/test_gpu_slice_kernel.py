@@ -18,6 +18,9 @@ def gpu():
     return LLVQ(13, 0)
 
 
+STRIP_SIZES = [(65601, 3, 129, "bf16"), (65537, 1, 257, "f16"), (40001, 5, 383, "f16"), (65300, 9, 256, "bf16"), (8003, 598, 129, "f16"), (11001, 301, 250, "bf16")]
+
+
 def _dev(a):
     import torch
     return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
@@ -104,13 +107,59 @@ def test_many_rows_give_the_same_bits(gpu, oracle13, M, xd):
     N, KB = 33024, 40
     idx, gain, x = synth.layer(8, 9000 + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
     d_x, d_idx, d_gain = _activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1))
-    y = gpu.llvq_matmul(d_x, d_idx, d_gain, N, KB)
-    for _ in range(3):
-        assert torch.equal(gpu.llvq_matmul(d_x, d_idx, d_gain, N, KB), y)
     n = 100                                                                   # the first rows as a matrix of their own
-    both = gpu.llvq_matmul_multi(d_x, [d_idx[:6 * KB * n], d_idx], [d_gain[:KB * n], d_gain], [n, N], KB)
-    assert torch.equal(both[1], y) and torch.equal(both[0], y[:, :n])
+
+    def single():
+        return gpu.llvq_matmul(d_x, d_idx, d_gain, N, KB)
+
+    def multi():
+        return gpu.llvq_matmul_multi(d_x, [d_idx[:6 * KB * n], d_idx], [d_gain[:KB * n], d_gain], [n, N], KB)[1]
+
     rows = np.concatenate([np.arange(4), np.arange(N - 4, N), np.random.default_rng(M).choice(N, 24, replace=False)])
     ref = oracle13.matmul(x, idx[rows], gain[rows])
-    err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
-    assert err <= _bound(xd), err
+    for product in (single, multi):
+        y = product()
+        for _ in range(3):
+            assert torch.equal(product(), y)
+        err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+        assert err <= _bound(xd), err
+
+
+# sizes that strip_faster gives to the strip kernel (tests/test_host_slices.py)
+@pytest.mark.parametrize("N,KB,M,xd", STRIP_SIZES)
+def test_strips_match_the_oracle(gpu, oracle13, N, KB, M, xd):
+    """256 rows x 256 tokens: one and two passes, partial strips and passes, odd block counts, single blocks, K split and whole"""
+    import torch
+    idx, gain, x = synth.layer(8, 9500 + N + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    d_x, d_gain = _activations(x, xd), _dev(gain.reshape(-1))
+    rows = np.unique(np.concatenate([np.arange(8), np.arange(N - 8, N), np.random.default_rng(N + M).choice(N, 40, replace=False)]))
+    d_rows = _dev(rows)
+    base = gpu.llvq_shell_offset(3)
+    words3 = idx % np.uint64(gpu.llvq_shell_offset(4) - base)                 # 24-bit words address shell 3
+    refs = [oracle13.matmul(x, idx[rows], gain[rows]), oracle13.matmul(x, words3[rows] + np.uint64(base), gain[rows])]
+
+    def out():
+        return torch.full((M, N), float("nan"), device="cuda:0")              # every element has to be written
+
+    for y, ref in ((gpu.llvq_matmul(d_x, _dev(synth.pack_u48(idx).reshape(-1)), d_gain, N, KB, out=out()), refs[0]),
+                   (gpu.llvq_matmul(d_x, _dev(idx.view(np.int64).reshape(-1)), d_gain, N, KB, out=out()), refs[0]),
+                   (gpu.llvq_matmul_coded(d_x, _dev(synth.pack_u24(words3).reshape(-1)), N, KB, 24, base, gain=d_gain, fmt=LLVQ_IDX_U24, out=out()), refs[1])):
+        assert not torch.isnan(y).any()
+        err = np.abs(y[:, d_rows].cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max()
+        assert err <= _bound(xd), err
+
+
+def test_strips_of_several_matrices_one_after_the_other(gpu, oracle13):
+    import torch
+    Ns, KB, M = (65001, 700, 65001), 21, 250
+    parts = [synth.layer(8, 9700 + i, N, 24 * KB, M) for i, N in enumerate(Ns)]
+    x = parts[0][2]
+    d_x, d_idx, d_gain = _activations(x, "f16"), [_dev(synth.pack_u48(p[0]).reshape(-1)) for p in parts], [_dev(p[1].reshape(-1)) for p in parts]
+    outs = [torch.full((M, N), float("nan"), device="cuda:0") for N in Ns]
+    gpu.llvq_matmul_multi(d_x, d_idx, d_gain, list(Ns), KB, outs=outs)
+    for (idx, gain, _), y, N in zip(parts, outs, Ns):
+        rows = np.unique(np.concatenate([np.arange(4), np.arange(N - 4, N), np.random.default_rng(N).choice(N, 24, replace=False)]))
+        ref = oracle13.matmul(x, idx[rows], gain[rows])
+        assert not torch.isnan(y).any()
+        err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+        assert err <= _bound("f16"), err
