@@ -21,7 +21,7 @@
 #include "../../include/llvq.h"
 #include "llvq_decode_core.h"
 #include "llvq_encode_core.h"
-#include "llvq_slices.h"
+#include "llvq_plan.h"
 #include "llvq_tables.h"
 #include "llvq_wide.h"
 
@@ -1164,18 +1164,18 @@ __global__ void __launch_bounds__(kThreads) slice_kernel(const unsigned char* __
     }
 }
 
-// ---- llvq_matmul, 65 <= M < 384 on large products: a block is decoded once per 256 tokens ---------------------------
-// A workgroup of eight waves owns 256 weight rows (wave w: rows 32 w .. 32 w + 31) x a pass of 256 tokens and walks block pairs of
+// ---- llvq_matmul, 65 <= M <= 256 on large products: a block is decoded once for all tokens ------------------------
+// A workgroup of eight waves owns 256 weight rows (wave w: rows 32 w .. 32 w + 31) x up to 256 tokens and walks block pairs of
 // the rows: 128 accumulator registers and two waves per SIMD, so a step (decode of 256 rows x 2 blocks, products with 256
 // tokens) is bound by the chains of dependent table reads, 2.4 us with fp16 and 3.1 us with bf16 weights.  slice_kernel keeps four
-// waves on a SIMD and decodes every block once per 128 tokens (see strip_faster for where either is the faster).  Per step the activation tile (256 tokens x 48 channels) is staged once and read by all waves as A operands; the
+// waves on a SIMD and decodes every block once per 128 tokens (see best_route for where either is the faster).  Per step the activation tile (256 tokens x 48 channels) is staged once and read by all waves as A operands; the
 // decoded blocks are B operands straight from the decoder's registers.  The Golay words and inner-word planes are read from
 // global memory, which leaves room for two activation buffers.  65536 x 4104 at M = 256: 239 us (fp16), 308 us (bf16).
-constexpr int kStripWaves = llvq::kStripRows / 32, kStripTiles = llvq::kStripTokens / 32, kStripThreads = 64 * kStripWaves;
+constexpr int kStripWaves = llvq::kStripRows / 32, kStripTiles = llvq::kStripMaxM / 32, kStripThreads = 64 * kStripWaves;
 constexpr uint32_t kStripPitch = 112;                  // bytes per token in the staged tile: 96 of data, padded so that rows stay 16-byte
                                                        // aligned (128-bit LDS accesses) and eight consecutive tokens cover all banks
-constexpr uint32_t kStripABuf = llvq::kStripTokens * kStripPitch, kStripLds = Lay13::kOffVti + 2u * kStripABuf;
-static_assert(kStripThreads == 2 * llvq::kStripTokens, "a thread stages half of a token's step");
+constexpr uint32_t kStripABuf = llvq::kStripMaxM * kStripPitch, kStripLds = Lay13::kOffVti + 2u * kStripABuf;
+static_assert(kStripThreads == 2 * llvq::kStripMaxM, "a thread stages half of a token's step");
 
 template <int FMT, typename X2>
 __global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned char* __restrict__ blob, TableLayout lay,
@@ -1188,16 +1188,15 @@ __global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned cha
     unsigned char* abuf = g_lds + Lay13::kOffVti;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, half = lane >> 5;
-    // steps (block pairs) of a row; the workgroups of blockIdx.z share them
+    // steps (block pairs) of a row; the workgroups of blockIdx.y share them
     const uint32_t spt = ((uint32_t)KB + 1) / 2;
-    const uint32_t st_first = (uint32_t)(((uint64_t)spt * blockIdx.z) / (uint32_t)ksplit);
-    const uint32_t st_end = (uint32_t)(((uint64_t)spt * (blockIdx.z + 1)) / (uint32_t)ksplit);
-    const int m0 = (int)blockIdx.y * llvq::kStripTokens;
+    const uint32_t st_first = (uint32_t)(((uint64_t)spt * blockIdx.y) / (uint32_t)ksplit);
+    const uint32_t st_end = (uint32_t)(((uint64_t)spt * (blockIdx.y + 1)) / (uint32_t)ksplit);
     const int wrow = (int)blockIdx.x * llvq::kStripRows + wave * 32 + col;
 
     // staging: token threadIdx / 2 (past M: a copy of the last one), block threadIdx % 2 of the pair
     const uint32_t s_part = threadIdx.x & 1u;
-    const uint32_t* s_src = x + (size_t)min(M - 1, m0 + (int)(threadIdx.x >> 1)) * ((size_t)KB * 12);
+    const uint32_t* s_src = x + (size_t)min(M - 1, (int)(threadIdx.x >> 1)) * ((size_t)KB * 12);
     unsigned char* s_dst = abuf + (threadIdx.x >> 1) * kStripPitch + s_part * 48u;
     auto stage_load = [&](uint32_t st, uint4 (&v)[3]) {
         const uint32_t b = min(2 * st + s_part, (uint32_t)KB - 1);       // past the last block: any valid data, its weights are zero
@@ -1285,13 +1284,13 @@ __global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned cha
         g_cur = g_nxt;
         __syncthreads();
     }
-    // y[token][wrow]: register v of tile t belongs to token m0 + 32 t + 8 (v / 4) + 4 half + v % 4
+    // y[token][wrow]: register v of tile t belongs to token 32 t + 8 (v / 4) + 4 half + v % 4
     if (wrow < N) {
 #pragma unroll
         for (int t = 0; t < kStripTiles; t++) {
 #pragma unroll
             for (int v = 0; v < 16; v++) {
-                const int tok = m0 + 32 * t + 8 * (v / 4) + 4 * half + (v % 4);
+                const int tok = 32 * t + 8 * (v / 4) + 4 * half + (v % 4);
                 if (tok < M) {
                     if (ksplit == 1) y[(size_t)tok * N + wrow] = acc[t][v];
                     else atomicAdd(y + (size_t)tok * N + wrow, acc[t][v]);
@@ -1301,7 +1300,7 @@ __global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned cha
     }
 }
 
-// ---- llvq_matmul, prefill kernel for M >= kPanelMinM: decoded weights shared through LDS ------------------------
+// ---- llvq_matmul, prefill kernel for M >= llvq::kPanelMinM: decoded weights shared through LDS ------------------------
 // The index decode costs the vector ALUs and the LDS gather pipe as much per block as 500 tokens cost the matrix cores,
 // so a block should be decoded once per as many tokens as the accumulators can hold.  A workgroup of eight waves owns a
 // panel of 128 weight rows x 512 tokens: wave w keeps ALL 128 rows x tokens 64 w .. 64 w + 63 (eight 32 x 32 tiles, 128
@@ -1315,8 +1314,7 @@ __global__ void __launch_bounds__(kStripThreads) strip_kernel(const unsigned cha
 // (30 KB with the two terms of a bf16 weight).
 // The decode of a step is spread over two steps of its wave: class search and digits while the wave's half is off
 // duty, placement, signs and scaling in the step before the weights are needed.
-constexpr int kPanelRows = 128, kPanelTokens = 512, kPanelWaves = 8;
-constexpr int kPanelMinM = 384, kPanelLongMinM = 257;             // see panel_fits
+constexpr int kPanelWaves = llvq::kPanelTokens / 64;
 // LDS: the tables without the int8 values, two buffers of decoded weights ([term][row tile][k group][lane] x 16 bytes) and the
 // waves' token rows.  For bf16 (two terms per weight) that is 448 bytes short of all there is; with one buffer and a barrier
 // between the products and the decode the seven layers of a Llama-3-8B-shaped block took 1189 us at M = 1024, not 1071.
@@ -1358,8 +1356,8 @@ __global__ void __launch_bounds__(64 * kPanelWaves) panel_kernel(const unsigned 
     const uint32_t spt_all = ((uint32_t)KB + 1) / 2;
     const uint32_t st_first = (uint32_t)(((uint64_t)spt_all * blockIdx.z) / (uint32_t)ksplit);
     const uint32_t st_end = (uint32_t)(((uint64_t)spt_all * (blockIdx.z + 1)) / (uint32_t)ksplit);
-    const int row0 = strip * kPanelRows;
-    const int m0 = (int)blockIdx.y * kPanelTokens + wave * 64;        // first token of this wave
+    const int row0 = strip * llvq::kPanelRows;
+    const int m0 = (int)blockIdx.y * llvq::kPanelTokens + wave * 64;        // first token of this wave
     const uint32_t xpitch = (uint32_t)KB * 12u;                       // dwords per activation row
 
     // decoding role: row tile (wave % 4), steps of parity (wave / 4) counted from st_first
@@ -1909,6 +1907,11 @@ static int set_strips(MatItems& items, int rows) {
     return end;
 }
 
+// rows of each matrix of `items`
+static void items_rows(const MatItems& items, int n_items, int (&rows)[kMaxItems]) {
+    for (int i = 0; i < n_items; i++) rows[i] = items.row_end[i] - (i ? items.row_end[i - 1] : 0);
+}
+
 // clears y before a launch that adds to it: one matrix, or all matrices of `items`
 static void clear_y(const MatItems* items, int n_items, int M, int N, float* d_y, hipStream_t st) {
     if (items) {
@@ -1939,9 +1942,7 @@ template <int FMT, typename X2, bool MULTI = false>
 static int launch_slice(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
                         const MatItems& items = MatItems{}, int n_items = 1) {
     int rows[kMaxItems] = {N};
-    if (MULTI) {
-        for (int i = 0; i < n_items; i++) rows[i] = items.row_end[i] - (i ? items.row_end[i - 1] : 0);
-    }
+    if (MULTI) items_rows(items, n_items, rows);
     const llvq::SlicePlan plan = llvq::slice_plan(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, rows, n_items);
     if (plan.token_tiles == 2) return launch_slice_cfg<FMT, X2, 2, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
     if (plan.token_tiles == 3) return launch_slice_cfg<FMT, X2, 3, MULTI>(ctx, plan, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st, items, n_items);
@@ -1953,56 +1954,44 @@ static int launch_strip(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx
     const llvq::StripPlan plan = llvq::strip_plan(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, N);
     if (plan.ksplit > 1) clear_y(nullptr, 1, M, N, d_y, st);
     if (int rc = set_lds<strip_kernel<FMT, X2>>(ctx, kStripLds)) return rc;
-    hipLaunchKernelGGL((strip_kernel<FMT, X2>), dim3((unsigned)plan.strips, (unsigned)plan.passes, (unsigned)plan.ksplit), dim3(kStripThreads), kStripLds, st, ctx->d_blob, ctx->lay, d_idx,
+    hipLaunchKernelGGL((strip_kernel<FMT, X2>), dim3((unsigned)plan.strips, (unsigned)plan.ksplit), dim3(kStripThreads), kStripLds, st, ctx->d_blob, ctx->lay, d_idx,
                        reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, plan.ksplit, d_y);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "strip matmul launch");
 }
 
-// MULTI: N is not used; the strips are those of `items`
+// MULTI: N is the number of rows of all matrices of `items` together
 template <int FMT, typename X2, bool MULTI = false>
 static int launch_panel(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st,
                         MatItems items = MatItems{}, int n_items = 1) {
-    const unsigned strips = MULTI ? (unsigned)set_strips(items, kPanelRows) : (unsigned)((N + kPanelRows - 1) / kPanelRows);
-    const unsigned passes = (unsigned)((M + kPanelTokens - 1) / kPanelTokens);
-    // enough workgroups for the chip: split the block pairs of a row among up to ksplit workgroups (at least 16 steps each)
-    const unsigned spt = ((unsigned)KB + 1) / 2;
-    unsigned ksplit = (unsigned)ctx->num_cu / (strips * passes);
-    ksplit = std::max(1u, std::min(ksplit, std::max(1u, spt / 16)));
-    if (ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
-    const dim3 grid(strips, passes, ksplit);
+    int rows[kMaxItems] = {N};
+    if (MULTI) {
+        items_rows(items, n_items, rows);
+        set_strips(items, llvq::kPanelRows);
+    }
+    const llvq::PanelPlan plan = llvq::panel_plan(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, rows, n_items);
+    if (plan.ksplit > 1) clear_y(MULTI ? &items : nullptr, n_items, M, N, d_y, st);
+    const dim3 grid((unsigned)plan.strips, (unsigned)plan.passes, (unsigned)plan.ksplit);
     constexpr int kTerms = Mma<X2>::kTerms;
     const size_t lds = kPanelLds<kTerms>;
     if (int rc = set_lds<panel_kernel<FMT, X2, MULTI>>(ctx, lds)) return rc;
     hipLaunchKernelGGL((panel_kernel<FMT, X2, MULTI>), grid, dim3(64 * kPanelWaves), lds, st, ctx->d_blob, ctx->lay, d_idx,
-                       reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, (int)ksplit, items, d_y);
+                       reinterpret_cast<const uint16_t*>(d_gain), reinterpret_cast<const uint32_t*>(d_x), M, N, KB, cd, plan.ksplit, items, d_y);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? LLVQ_OK : hip_fail(ctx, e, "panel matmul launch");
-}
-
-// whether a product with this many strips of 128 rows takes the panel kernel: from kPanelMinM tokens on, when there are
-// panels for at least a sixteenth of the chip (the rest comes from splitting the rows' block pairs, at least 16 steps
-// per part; measured on Llama-3-8B shapes: 4096 rows at M = 512 take 72 us against 92 us in the strip kernel, 1024 rows
-// are level at M = 1024 and slower below); activation offsets inside the kernel are 32-bit byte offsets.  From
-// kPanelLongMinM tokens on, where slice_kernel needs a third pass, only if every compute unit gets 32 steps or more
-// (M = 280, fp16 and bf16 against slice_kernel: 4096 x 14352 110 / 144 us against 125 / 147; 4096 x 4104 54 / 68 against 50 / 55;
-// 14336 x 1008 47 / 63 against 48 / 55; seven layers of a Llama-3-8B-shaped block at M = 320 443 / 584 against 564 / 678)
-static bool panel_fits(const llvq_ctx* ctx, int M, uint64_t strips, int KB) {
-    const bool many_steps = strips * (((uint64_t)KB + 1) / 2) >= (uint64_t)ctx->num_cu * 32u;
-    return M >= (many_steps ? kPanelLongMinM : kPanelMinM) && (uint64_t)M * (uint64_t)KB * 48u < (1ull << 32) &&
-           strips * (uint64_t)((M + kPanelTokens - 1) / kPanelTokens) * 16u >= (uint64_t)ctx->num_cu;
 }
 
 template <int FMT, typename X2>
 static int launch_any_matmul(llvq_ctx* ctx, const void* d_x, int M, const void* d_idx, const void* d_gain, const Code& cd, int N, int KB, float* d_y, hipStream_t st) {
     // (slice_kernel reads words in pairs: a matrix of a single block takes the lane-per-block kernel at every M)
     if (M < kMfmaMinM || (size_t)N * KB < 2) return launch_matmul<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
-    if (panel_fits(ctx, M, (uint64_t)((N + kPanelRows - 1) / kPanelRows), KB))
-        return launch_panel<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= 16) return launch_tile<FMT, X2, 1>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
     if (M <= kTileMaxM) return launch_tile<FMT, X2, 2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
-    if (llvq::strip_faster(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, N)) return launch_strip<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
-    return launch_slice<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+    switch (llvq::best_route(ctx->num_cu, M, KB, Mma<X2>::kTerms == 2, N).route) {
+        case llvq::kRoutePanel: return launch_panel<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+        case llvq::kRouteStrip: return launch_strip<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+        default: return launch_slice<FMT, X2>(ctx, d_x, M, d_idx, d_gain, cd, N, KB, d_y, st);
+    }
 }
 
 // evaluates EXPR with the constant F set to the storage format `fmt` (which check_idx has accepted)
@@ -2103,10 +2092,10 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
         if (tiles * (size_t)((KB + 1) / 2) >= (1ull << 32) || (size_t)M * (size_t)KB * 12 >= (1ull << 32)) return LLVQ_EINVAL;
     }
     MatItems items;
-    int rows = 0, tiles16 = 0, strips = 0;
+    int rows = 0, tiles16 = 0;
     for (int i = 0; i < kMaxItems; i++) {
         const int k = i < n_items ? i : n_items - 1;
-        if (i < n_items) { rows += N[i]; tiles16 += (N[i] + kTileRows - 1) / kTileRows; strips += (N[i] + kPanelRows - 1) / kPanelRows; }
+        if (i < n_items) { rows += N[i]; tiles16 += (N[i] + kTileRows - 1) / kTileRows; }
         items.tile16_end[i] = tiles16;
         items.idx[i] = d_idx[k];
         items.gain[i] = reinterpret_cast<const uint16_t*>(d_gain[k]);
@@ -2114,26 +2103,17 @@ int matmul_multi_impl(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_
         items.row_end[i] = rows;
     }
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    // prefill: the 128-row strips of all matrices in one launch when at least one of them has panels for less than half
-    // of the chip (small matrices such as k and v then run at the rate of the large ones; matrices that fill the chip
-    // on their own gain nothing from sharing a launch and lose to the uneven last round)
-    bool small_item = false, all_panels = true;          // all_panels: each of the matrices takes the panel kernel on its own
-    for (int i = 0; i < n_items; i++) {
-        all_panels = all_panels && panel_fits(ctx, M, (uint64_t)((N[i] + kPanelRows - 1) / kPanelRows), KB);
-        small_item = small_item || (uint64_t)((N[i] + kPanelRows - 1) / kPanelRows) * (uint64_t)((M + kPanelTokens - 1) / kPanelTokens) * 2u < (uint64_t)ctx->num_cu;
-    }
-    if (n_items > 1 && small_item && panel_fits(ctx, M, (uint64_t)strips, KB)) {
-        if (x_dtype == LLVQ_F16)
-            return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
-        return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
-    }
-    if (n_items == 1 || KB == 1 || all_panels || (M >= kPanelMinM && panel_fits(ctx, M, 1u << 20, KB)) ||
-        llvq::strips_apart(ctx->num_cu, M, KB, x_dtype == LLVQ_BF16, N, n_items)) {
-        // one matrix, single-block rows (see launch_any_matmul), or matrices that take the panel kernel or the strip kernel each on
-        // its own: one product after the other
+    const llvq::MultiRoute route = M > kTileMaxM ? llvq::multi_route(ctx->num_cu, M, KB, x_dtype == LLVQ_BF16, N, n_items) : llvq::kMultiSlice;
+    if (n_items == 1 || KB == 1 || route == llvq::kMultiApart) {
+        // (single-block rows: see launch_any_matmul)
         for (int i = 0; i < n_items; i++)
             if (int rc = matmul_impl(ctx, d_x, x_dtype, M, d_idx[i], fmt, d_gain[i], cd, N[i], KB, d_y[i], stream)) return rc;
         return LLVQ_OK;
+    }
+    if (route == llvq::kMultiPanel) {
+        if (x_dtype == LLVQ_F16)
+            return LLVQ_BY_FMT(fmt, (launch_panel<F, half2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
+        return LLVQ_BY_FMT(fmt, (launch_panel<F, bf16x2_t, true>(ctx, d_x, M, d_idx[0], d_gain[0], cd, rows, KB, d_y[0], st, items, n_items)));
     }
     if (M >= kMfmaMinM && M <= kTileMaxM) {
         // row tiles of all matrices in one launch, each tile reduced inside its workgroup

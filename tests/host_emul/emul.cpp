@@ -6,7 +6,7 @@
 
 #include "../../paper_2603_11021_amd/csrc/llvq_decode_core.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_encode_core.h"
-#include "../../paper_2603_11021_amd/csrc/llvq_slices.h"
+#include "../../paper_2603_11021_amd/csrc/llvq_plan.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_tables.h"
 #include "../../paper_2603_11021_amd/csrc/llvq_wide.h"
 
@@ -118,13 +118,17 @@ uint64_t emul_slice_pairs_wrong(int N, int KB, int strip_rows) {
     return wrong;
 }
 
-// the plan of a product of n_items matrices on a device of num_cu compute units: token tiles, passes, rows per strip and split of K of
-// slice_kernel; split of K of strip_kernel and whether it is taken, for the first matrix
-void emul_slice_plan(int num_cu, int M, int KB, int two_terms, const int* N, int n_items, int* out) {
-    const llvq::SlicePlan p = llvq::slice_plan(num_cu, M, KB, two_terms != 0, N, n_items);
+// How n_items matrices are multiplied on a device of num_cu compute units: token tiles, passes, rows per strip and split of K of one
+// launch of slice_kernel; split of K of strip_kernel (first matrix) and of one launch of panel_kernel; the route of the first
+// matrix alone (0 slice, 1 strip, 2 panel) and of all (0 slice, 1 panel, 2 one after the other).
+void emul_plan(int num_cu, int M, int KB, int two_terms, const int* N, int n_items, int* out) {
+    const bool two = two_terms != 0;
+    const llvq::SlicePlan p = llvq::slice_plan(num_cu, M, KB, two, N, n_items);
     out[0] = p.token_tiles; out[1] = p.passes; out[2] = p.strip_rows; out[3] = p.ksplit;
-    out[4] = llvq::strip_plan(num_cu, M, KB, two_terms != 0, N[0]).ksplit;
-    out[5] = llvq::strip_faster(num_cu, M, KB, two_terms != 0, N[0]);
+    out[4] = llvq::strip_plan(num_cu, M, KB, two, N[0]).ksplit;
+    out[5] = llvq::panel_plan(num_cu, M, KB, two, N, n_items).ksplit;
+    out[6] = llvq::best_route(num_cu, M, KB, two, N[0]).route;
+    out[7] = llvq::multi_route(num_cu, M, KB, two, N, n_items);
 }
 
 }  // extern "C"

@@ -18,7 +18,13 @@ def gpu():
     return LLVQ(13, 0)
 
 
-STRIP_SIZES = [(65601, 3, 129, "bf16"), (65537, 1, 257, "f16"), (40001, 5, 383, "f16"), (65300, 9, 256, "bf16"), (8003, 598, 129, "f16"), (11001, 301, 250, "bf16")]
+# sizes that the choice of kernels gives to slice_kernel, panel_kernel, panel_kernel with several matrices in one launch, and
+# strip_kernel (checked in tests/test_host_slices.py)
+SLICE_SIZES = [(1, 2, 33), (31, 1, 64), (33, 3, 64), (64, 2, 65), (65, 7, 96), (127, 8, 97), (129, 16, 128), (128, 17, 129), (63, 33, 192), (130, 5, 193),
+               (97, 9, 256), (96, 10, 383), (40, 171, 160), (257, 40, 34), (300, 40, 1024), (1100, 33, 1000), (2051, 21, 513), (65, 1, 385)]
+PANEL_SIZES = [(14000, 171, 513, "f16"), (28600, 60, 257, "bf16"), (8200, 33, 385, "bf16")]
+MULTI_PANEL_SIZES = [((4100, 1000, 130, 3000), 81, 400, "bf16"), ((5000, 7000), 9, 513, "f16"), ((2050, 1), 342, 1024, "f16")]
+STRIP_SIZES = [(65601, 3, 129, "bf16"), (65537, 1, 255, "f16"), (40001, 5, 161, "f16"), (65300, 9, 256, "bf16"), (8003, 598, 129, "f16"), (11001, 301, 250, "bf16")]
 
 
 def _dev(a):
@@ -37,8 +43,7 @@ def _activations(x, xd):
 
 
 @pytest.mark.parametrize("xd", ["f16", "bf16"])
-@pytest.mark.parametrize("N,KB,M", [(1, 2, 33), (31, 1, 64), (33, 3, 64), (64, 2, 65), (65, 7, 96), (127, 8, 97), (129, 16, 128), (128, 17, 129),
-                                    (63, 33, 192), (130, 5, 193), (97, 9, 256), (96, 10, 383), (40, 171, 160), (257, 40, 34)])
+@pytest.mark.parametrize("N,KB,M", SLICE_SIZES)
 def test_slices_match_the_oracle(gpu, oracle13, N, KB, M, xd):
     idx, gain, x = synth.layer(8, 5000 + N + 7 * KB + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
     import torch
@@ -125,10 +130,9 @@ def test_many_rows_give_the_same_bits(gpu, oracle13, M, xd):
         assert err <= _bound(xd), err
 
 
-# sizes that strip_faster gives to the strip kernel (tests/test_host_slices.py)
 @pytest.mark.parametrize("N,KB,M,xd", STRIP_SIZES)
 def test_strips_match_the_oracle(gpu, oracle13, N, KB, M, xd):
-    """256 rows x 256 tokens: one and two passes, partial strips and passes, odd block counts, single blocks, K split and whole"""
+    """256 rows x up to 256 tokens: partial strips, partial and whole token tiles, odd block counts, single blocks, K split and whole"""
     import torch
     idx, gain, x = synth.layer(8, 9500 + N + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
     d_x, d_gain = _activations(x, xd), _dev(gain.reshape(-1))
@@ -163,3 +167,34 @@ def test_strips_of_several_matrices_one_after_the_other(gpu, oracle13):
         assert not torch.isnan(y).any()
         err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
         assert err <= _bound("f16"), err
+
+
+@pytest.mark.parametrize("N,KB,M,xd", PANEL_SIZES)
+def test_panels_match_the_oracle(gpu, oracle13, N, KB, M, xd):
+    """one token in the last pass or in the last wave's share, partial panels, K split and whole"""
+    import torch
+    idx, gain, x = synth.layer(8, 9900 + N + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+    y = torch.full((M, N), float("nan"), device="cuda:0")
+    gpu.llvq_matmul(_activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1)), N, KB, out=y)
+    assert not torch.isnan(y).any()
+    rows = np.unique(np.concatenate([np.arange(4), np.arange(N - 4, N), np.random.default_rng(N + M).choice(N, 32, replace=False)]))
+    ref = oracle13.matmul(x, idx[rows], gain[rows])
+    err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+    assert err <= _bound(xd), err
+
+
+@pytest.mark.parametrize("Ns,KB,M,xd", MULTI_PANEL_SIZES)
+def test_panels_of_several_matrices(gpu, oracle13, Ns, KB, M, xd):
+    """ragged row counts, so that every matrix ends in a partial panel; K split and whole"""
+    import torch
+    parts = [synth.layer(8, 9800 + i + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16") for i, N in enumerate(Ns)]
+    x = parts[0][2]
+    outs = [torch.full((M, N), float("nan"), device="cuda:0") for N in Ns]
+    gpu.llvq_matmul_multi(_activations(x, xd), [_dev(synth.pack_u48(p[0]).reshape(-1)) for p in parts], [_dev(p[1].reshape(-1)) for p in parts], list(Ns), KB,
+                          outs=outs)
+    for (idx, gain, _), y, N in zip(parts, outs, Ns):
+        rows = np.unique(np.concatenate([[0, N - 1], np.random.default_rng(N).choice(N, min(N, 40), replace=False)]))
+        ref = oracle13.matmul(x, idx[rows], gain[rows])
+        assert not torch.isnan(y).any()
+        err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
+        assert err <= _bound(xd), err

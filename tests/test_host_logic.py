@@ -17,7 +17,7 @@ EMUL = os.path.join(ROOT, "tests", "host_emul", "libemul.so")
 def emul():
     srcs = [os.path.join(ROOT, "tests", "host_emul", "emul.cpp")] + [
         os.path.join(ROOT, "paper_2603_11021_amd", "csrc", f)
-        for f in ("llvq_tables.cpp", "llvq_tables.h", "llvq_decode_core.h", "llvq_encode_core.h", "llvq_slices.h", "llvq_wide.h")]
+        for f in ("llvq_tables.cpp", "llvq_tables.h", "llvq_decode_core.h", "llvq_encode_core.h", "llvq_plan.h", "llvq_wide.h")]
     if not os.path.exists(EMUL) or os.path.getmtime(EMUL) < max(os.path.getmtime(f) for f in srcs):
         subprocess.check_call(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-o", EMUL,
                                os.path.join(ROOT, "tests", "host_emul", "emul.cpp"),
