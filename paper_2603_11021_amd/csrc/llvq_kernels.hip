@@ -921,14 +921,13 @@ __global__ void __launch_bounds__(kThreads) tile_kernel(const unsigned char* __r
 // them with all tokens of the pass (16 TT accumulator registers), the slices take turns at the block pairs, and the
 // kRowTiles waves of a slice share its activation tile in LDS.  At the end the slices are added through LDS, so one
 // workgroup writes (or, with the rows' block pairs split over workgroups, adds to y) 32 kRowTiles x 32 TT values once.
-// 128 registers per lane keep four waves on a SIMD, which the decode's chains of dependent table reads need (two waves
-// with 256 tokens each, as here before, ran at a third of the rate).
+// 128 registers per lane keep four waves on a SIMD, which hide the decode's chains of dependent table reads.
 // The slices do not wait for each other: no barrier in the loop, but two counters per slice in LDS.  `ready` counts staged token
 // tiles, `done` counts finished steps; a wave stages token tile `tile` of the next step (direct global-to-LDS loads) once
 // all waves of its slice are past the step before this one.  A wave waits only for waves of its own workgroup and for
 // things these do before they wait themselves, so every wait ends.
-// Llama-3-8B-shaped block (seven layers): M = 64 242 -> 197 us (bf16), M = 250 520 -> 352 us (fp16), M = 128 203 us, against the
-// split-K kernel (M <= 64) and the strip kernel with two waves per SIMD.
+// Llama-3-8B-shaped block (seven layers): M = 64 242 -> 193 us (bf16), against a kernel that staged per wave and added every
+// partial sum to y; M = 250 520 -> 352 us (fp16), against strip_kernel; M = 128 203 us.
 template <int TT> constexpr int kSliceTiles = llvq::slice_tiles(TT);      // 32-row tiles per workgroup
 constexpr uint32_t kSliceTabBytes = Lay13::kOffVti;                                        // class records and small tables; Golay words and planes in global memory
 constexpr uint32_t kSliceXOff = (kSliceTabBytes + 511u) & ~511u;
