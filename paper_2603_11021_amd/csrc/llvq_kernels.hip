@@ -1677,7 +1677,6 @@ struct llvq_ctx {
     unsigned char* d_enc_blob = nullptr;
     llvq::SearchLayout search_lay{};
     llvq::SearchRec* d_search = nullptr;    // nearest-point search records
-    uint32_t* d_words = nullptr;            // the 4096 Golay words in (weight, message) order
     uint4* d_tile_a = nullptr;              // matrix-core operands of the class tiles
     float* d_tile_scale = nullptr;          // per-class factor and offset in accumulator order
     unsigned long long* d_counter = nullptr;
@@ -2255,10 +2254,9 @@ int llvq_create(llvq_ctx** out, int m_max, int device) {
         (void)hipFree(ctx->d_blob); (void)hipFree(ctx->d_counter); delete ctx; return LLVQ_EHIP;
     }
     ctx->search_lay = tabs.search_lay;
-    const size_t sbytes = tabs.search_recs.size() * sizeof(llvq::SearchRec), wbytes = tabs.golay_sorted.size() * sizeof(uint32_t);
-    if ((e = hipMalloc(&ctx->d_search, sbytes)) != hipSuccess || (e = hipMalloc(&ctx->d_words, wbytes)) != hipSuccess ||
-        (e = hipMemcpy(ctx->d_search, tabs.search_recs.data(), sbytes, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemcpy(ctx->d_words, tabs.golay_sorted.data(), wbytes, hipMemcpyHostToDevice)) != hipSuccess) {
+    const size_t sbytes = tabs.search_recs.size() * sizeof(llvq::SearchRec);
+    if ((e = hipMalloc(&ctx->d_search, sbytes)) != hipSuccess ||
+        (e = hipMemcpy(ctx->d_search, tabs.search_recs.data(), sbytes, hipMemcpyHostToDevice)) != hipSuccess) {
         llvq_destroy(ctx);
         return LLVQ_EHIP;
     }
@@ -2280,7 +2278,6 @@ void llvq_destroy(llvq_ctx* ctx) {
     if (ctx->d_counter) (void)hipFree(ctx->d_counter);
     if (ctx->d_enc_blob) (void)hipFree(ctx->d_enc_blob);
     if (ctx->d_search) (void)hipFree(ctx->d_search);
-    if (ctx->d_words) (void)hipFree(ctx->d_words);
     if (ctx->d_tile_a) (void)hipFree(ctx->d_tile_a);
     if (ctx->d_tile_scale) (void)hipFree(ctx->d_tile_scale);
     if (ctx->blas) (void)rocblas_destroy_handle(ctx->blas);

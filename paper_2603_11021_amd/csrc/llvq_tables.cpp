@@ -439,25 +439,21 @@ bool build_wide_tables(int m_max, WideTables& out) {
     int woff[25];
     uint64_t total = 0;
     for (int m = 0; m < 24; m++) out.shell_off[m] = 0;
-    if (!enumerate_leaders(m_max, out.gs, woff, cls, out.shell_off, total)) return false;
+    std::vector<uint32_t> gs;          // 4096 Golay words in (weight, message) order
+    if (!enumerate_leaders(m_max, gs, woff, cls, out.shell_off, total)) return false;
     for (int m = m_max + 1; m < 24; m++) out.shell_off[m] = total;
     if (total >= (1ull << 56)) return false;
-    out.lay.ncls = (uint32_t)cls.size();
-    out.lay.m_max = (uint32_t)m_max;
-    out.lay.npoints = total;
-    out.binom.assign(25 * 25, 0);
+    std::vector<uint32_t> binom(25 * 25, 0);
     for (int n = 0; n <= 24; n++)
         for (int k = 0; k <= 24; k++) {
             if (g_binom[n][k] > 0xFFFFFFFFull) return false;
-            out.binom[n * 25 + k] = (uint32_t)g_binom[n][k];
+            binom[n * 25 + k] = (uint32_t)g_binom[n][k];
         }
-    out.recs.assign(cls.size(), WideRec{});
-    out.cls_off.assign(cls.size() + 1, total);
+    std::vector<WideRec> wide(cls.size());
     for (size_t ci = 0; ci < cls.size(); ci++) {
         const Leader& L = cls[ci];
         const ClassShape S = shape_of(L);
         WideRec R{};
-        out.cls_off[ci] = L.offset;
         if (S.mv.size() > (size_t)kWideMaxMinor || S.dv.size() > (size_t)kWideMaxDirect) return false;
         const uint64_t Pin = multinomial(S.mc), P1 = S.f1direct ? multinomial(S.dc) : 1;
         if (g_binom[S.n][S.q] * Pin * P1 != L.P1 * L.P0 || P1 > 0xFFFFFFFFull) return false;     // consistency with the class cardinality
@@ -473,7 +469,7 @@ bool build_wide_tables(int m_max, WideTables& out) {
         R.outside = signed_value(S.outside);
         for (size_t i = 0; i < S.mv.size(); i++) { R.mv[i] = signed_value(S.mv[i]); R.mc[i] = (uint8_t)S.mc[i]; }
         for (size_t i = 0; i < S.dv.size(); i++) { R.dv[i] = (int8_t)S.dv[i]; R.dc[i] = (uint8_t)S.dc[i]; }
-        out.recs[ci] = R;
+        wide[ci] = R;
     }
     // The tables of the table-driven decoder.  The direct F1 words' planes come first, the largest last: their entry
     // numbers have 16 bits, and 80,551 planes fit because only the first entry of a table has to be named.
@@ -498,12 +494,12 @@ bool build_wide_tables(int m_max, WideTables& out) {
     for (size_t ci = 0; ci < cls.size(); ci++) {
         const Leader& L = cls[ci];
         const ClassShape S = shape_of(L);
-        if (L.size >= (1ull << 52) || out.recs[ci].Pin * out.recs[ci].P1 >= (1u << 22) || out.recs[ci].P1 > 0xFFFF) return false;
+        if (L.size >= (1ull << 52) || wide[ci].Pin * wide[ci].P1 >= (1u << 22) || wide[ci].P1 > 0xFFFF) return false;
         int64_t tb0 = D.inner_table(S.mc, outer_symbol(S));
         const bool steps = tb0 < 0;
         if (steps) {
             if (S.f1direct || S.mv.size() > 7) return false;
-            most_steps = std::max(most_steps, out.recs[ci].Pin);
+            most_steps = std::max(most_steps, wide[ci].Pin);
             tb0 = 0;
         }
         DecoderParts::SplitInfo si;
@@ -514,10 +510,10 @@ bool build_wide_tables(int m_max, WideTables& out) {
         recs[ci] = R;
     }
     if (most_steps > D.inner.size() || D.guess.size() / kGuessBuckets > 64) return false;      // the decoder reads (and drops) entry rin of a step class
-    if (!assemble_blob<Lay19>(D, out.gs, recs, cls, total, m_max, out.tab, out.blob)) return false;
-    if (out.recs.size() * sizeof(WideRec) > Lay19::kOffBinom - Lay19::kOffWideRec || out.binom.size() * 4 > Lay19::kOffInner - Lay19::kOffBinom) return false;
-    std::memcpy(out.blob.data() + Lay19::kOffWideRec, out.recs.data(), out.recs.size() * sizeof(WideRec));
-    std::memcpy(out.blob.data() + Lay19::kOffBinom, out.binom.data(), out.binom.size() * 4);
+    if (!assemble_blob<Lay19>(D, gs, recs, cls, total, m_max, out.tab, out.blob)) return false;
+    if (wide.size() * sizeof(WideRec) > Lay19::kOffBinom - Lay19::kOffWideRec || binom.size() * 4 > Lay19::kOffInner - Lay19::kOffBinom) return false;
+    std::memcpy(out.blob.data() + Lay19::kOffWideRec, wide.data(), wide.size() * sizeof(WideRec));
+    std::memcpy(out.blob.data() + Lay19::kOffBinom, binom.data(), binom.size() * 4);
     return true;
 }
 
@@ -774,7 +770,6 @@ bool build_tables(int m_max, Tables& out) {
         }
     }
     out.search_lay = sl;
-    out.golay_sorted = gs;
     return true;
 }
 

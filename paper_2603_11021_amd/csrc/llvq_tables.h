@@ -233,7 +233,6 @@ struct Tables {
     std::vector<SearchRec> search_recs;
     std::vector<uint16_t> search_tile_a;      // n_tiles x 2 x 64 x 8 bf16
     std::vector<float> search_tile_scale;     // n_tiles x kSearchTileScaleFloats
-    std::vector<uint32_t> golay_sorted;   // the 4096 words in (weight, message) order
 };
 
 // Builds every table for Lambda_24(m_max), 2 <= m_max <= 13.  Returns false on an internal inconsistency.

@@ -1,9 +1,8 @@
-// The larger unions of shells, Lambda_24(m_max) with 14 <= m_max <= 19 (paper Table 1, row m = 19: 23,546,209,100,646,960
-// points, 55-bit indices; App. A steps 1-4), decoded step by step with plain 64-bit integer arithmetic, subsets unranked
-// against a table of binomial coefficients.  The kernels decode these unions with the tables of llvq_decode_core.h
-// (layout Lay19); what those tables cannot describe, the few classes with subsets of more than 16 slots or more than four
-// minority values (3 in a million indices), is placed by wide_place below.  wide_decode is the whole procedure in one
-// call, without any of the tables; a test harness runs it on the host.
+// Step-by-step placement of App. A step 4 for the larger unions of shells, Lambda_24(m_max) with 14 <= m_max <= 19 (paper Table 1,
+// row m = 19: 23,546,209,100,646,960 points, 55-bit indices): plain integer arithmetic, subsets unranked against a table of binomial
+// coefficients.  The kernels decode these unions with the tables of llvq_decode_core.h (layout Lay19); wide_place is for what
+// those tables cannot describe, the few classes with subsets of more than 16 slots or more than four minority values (3 in
+// a million indices).
 #pragma once
 #include <cstdint>
 #include <vector>
@@ -41,22 +40,6 @@ struct alignas(16) WideRec {
     uint8_t  pad[13];
 };
 static_assert(sizeof(WideRec) == 64, "WideRec layout");
-
-struct WideLayout {
-    uint32_t ncls;
-    uint32_t m_max;
-    uint64_t npoints;
-};
-
-// device / host views of the tables
-struct WidePtrs {
-    const WideRec*  recs;      // ncls records
-    const uint64_t* cls_off;   // ncls + 1 cumulative class offsets (the last one is N)
-    const uint32_t* gs;        // 4096 Golay words ordered by (weight, message)
-    const uint32_t* binom;     // 25 x 25 binomial coefficients C(n, k) at [n * 25 + k]
-    uint32_t ncls;
-    uint64_t npoints;
-};
 
 LLVQ_WHD uint32_t wide_popc(uint32_t v) { return (uint32_t)__builtin_popcount(v); }
 
@@ -134,48 +117,11 @@ LLVQ_WHD uint32_t wide_place(const uint32_t* binom, const WideRec& R, uint32_t c
     return wide_deposit(s1, c) | wide_deposit(s >> wm1, U);
 }
 
-// Decodes index I < npoints into 24 int8 coordinates (six dwords, position order); returns the shell.
-LLVQ_WHD uint32_t wide_decode(const WidePtrs& T, uint64_t I, uint32_t (&out)[6], float& rnorm) {
-    // App. A steps 1-2: the class whose range of indices holds I
-    uint32_t lo = 0, hi = T.ncls;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (I >= T.cls_off[mid]) lo = mid; else hi = mid;
-    }
-    const WideRec R = T.recs[lo];
-    // step 3: r = Ic mod A, then B sign bits, then I'' = (d * Pin + rin) * P1 + rho1
-    uint64_t t = I - T.cls_off[lo];
-    const uint32_t r = (uint32_t)(t % R.A);
-    t /= R.A;
-    const uint32_t s = (uint32_t)(t & ((1ull << R.B) - 1ull));
-    t >>= R.B;
-    const uint32_t rho1 = (uint32_t)(t % R.P1);
-    t /= R.P1;
-    const uint64_t rin = t % R.Pin;
-    const uint32_t d = (uint32_t)(t / R.Pin);
-    // step 4: Golay word, placement, signs
-    int8_t x[24] = {};
-    const uint32_t neg = wide_place(T.binom, R, T.gs[R.goff + r], s, d, rin, rho1, [&](uint32_t occ, int, int v) {
-        for (int p = 0; p < 24; p++) if ((occ >> p) & 1u) x[p] = (int8_t)v;
-    });
-    for (int p = 0; p < 24; p++) if ((neg >> p) & 1u) x[p] = (int8_t)-x[p];
-    for (int k = 0; k < 6; k++)
-        out[k] = (uint32_t)(uint8_t)x[4 * k] | ((uint32_t)(uint8_t)x[4 * k + 1] << 8) | ((uint32_t)(uint8_t)x[4 * k + 2] << 16) |
-                 ((uint32_t)(uint8_t)x[4 * k + 3] << 24);
-    rnorm = R.rnorm;
-    return R.m;
-}
-
-// host-side tables of the wide decoder
+// host-side tables of a wide context
 struct WideTables {
-    WideLayout lay;
-    TableLayout tab;                   // the tables of llvq_decode_core.h in layout Lay19
-    std::vector<unsigned char> blob;
+    TableLayout tab;
+    std::vector<unsigned char> blob;   // the tables of llvq_decode_core.h in layout Lay19, the WideRecs and the binomial coefficients
     uint64_t shell_off[24];            // index of the first point of shell m (N(m-1)); entries above m_max hold N(m_max)
-    std::vector<WideRec> recs;
-    std::vector<uint64_t> cls_off;     // ncls + 1 entries
-    std::vector<uint32_t> gs;          // 4096 Golay words in (weight, message) order
-    std::vector<uint32_t> binom;       // 25 x 25
 };
 
 // Builds the tables for Lambda_24(m_max), 2 <= m_max <= 19.  Returns false on an internal inconsistency.

@@ -13,6 +13,47 @@
 static llvq::Tables g_tabs;
 static bool g_ok = false;
 
+// The whole of App. A for these unions in one call, step by step and without the decoder's tables: its class records, offsets, Golay
+// words and binomial coefficients are those of the blob that llvq_create copies to the device.
+struct WidePtrs {
+    const llvq::WideRec* recs;
+    const uint64_t* cls_off;   // first index of every class, then N
+    const uint32_t* gs;        // 4096 Golay words ordered by (weight, message)
+    const uint32_t* binom;     // 25 x 25 binomial coefficients C(n, k) at [n * 25 + k]
+    uint32_t ncls;
+    uint64_t npoints;
+};
+
+// index I < npoints -> 24 int8 coordinates (six dwords, position order)
+static void wide_decode(const WidePtrs& T, uint64_t I, uint32_t (&out)[6]) {
+    // App. A steps 1-2: the class whose range of indices holds I
+    uint32_t lo = 0, hi = T.ncls;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (I >= T.cls_off[mid]) lo = mid; else hi = mid;
+    }
+    const llvq::WideRec R = T.recs[lo];
+    // step 3: r = Ic mod A, then B sign bits, then I'' = (d * Pin + rin) * P1 + rho1
+    uint64_t t = I - T.cls_off[lo];
+    const uint32_t r = (uint32_t)(t % R.A);
+    t /= R.A;
+    const uint32_t s = (uint32_t)(t & ((1ull << R.B) - 1ull));
+    t >>= R.B;
+    const uint32_t rho1 = (uint32_t)(t % R.P1);
+    t /= R.P1;
+    const uint64_t rin = t % R.Pin;
+    const uint32_t d = (uint32_t)(t / R.Pin);
+    // step 4: Golay word, placement, signs
+    int8_t x[24] = {};
+    const uint32_t neg = llvq::wide_place(T.binom, R, T.gs[R.goff + r], s, d, rin, rho1, [&](uint32_t occ, int, int v) {
+        for (int p = 0; p < 24; p++) if ((occ >> p) & 1u) x[p] = (int8_t)v;
+    });
+    for (int p = 0; p < 24; p++) if ((neg >> p) & 1u) x[p] = (int8_t)-x[p];
+    for (int k = 0; k < 6; k++)
+        out[k] = (uint32_t)(uint8_t)x[4 * k] | ((uint32_t)(uint8_t)x[4 * k + 1] << 8) | ((uint32_t)(uint8_t)x[4 * k + 2] << 16) |
+                 ((uint32_t)(uint8_t)x[4 * k + 3] << 24);
+}
+
 extern "C" {
 
 int emul_init(int m_max) {
@@ -58,18 +99,21 @@ uint64_t emul_encode(const int8_t* pts, uint64_t n, uint64_t* idx) {
 static llvq::WideTables g_wide;
 
 int emul_wide_init(int m_max) { return llvq::build_wide_tables(m_max, g_wide) ? 0 : -1; }
-uint32_t emul_wide_num_classes() { return g_wide.lay.ncls; }
-uint64_t emul_wide_num_points() { return g_wide.lay.npoints; }
+uint32_t emul_wide_num_classes() { return g_wide.tab.ncls; }
+uint64_t emul_wide_num_points() { return g_wide.tab.npoints; }
 uint64_t emul_wide_shell_offset(int m) { return (m >= 0 && m < 24) ? g_wide.shell_off[m] : 0; }
 
 uint64_t emul_wide_decode_i8(const uint64_t* idx, uint64_t n, int8_t* out) {
-    llvq::WidePtrs T = {g_wide.recs.data(), g_wide.cls_off.data(), g_wide.gs.data(), g_wide.binom.data(), g_wide.lay.ncls, g_wide.lay.npoints};
+    using llvq::Lay19;
+    const unsigned char* blob = g_wide.blob.data();
+    const WidePtrs T = {reinterpret_cast<const llvq::WideRec*>(blob + Lay19::kOffWideRec), reinterpret_cast<const uint64_t*>(blob + Lay19::kOffClsOff),
+                        reinterpret_cast<const uint32_t*>(blob + Lay19::kOffGs), reinterpret_cast<const uint32_t*>(blob + Lay19::kOffBinom),
+                        g_wide.tab.ncls, g_wide.tab.npoints};
     uint64_t bad = 0;
     for (uint64_t k = 0; k < n; k++) {
         if (idx[k] >= T.npoints) { bad++; std::memset(out + 24 * k, 0, 24); continue; }
         uint32_t o[6];
-        float rnorm;
-        llvq::wide_decode(T, idx[k], o, rnorm);
+        wide_decode(T, idx[k], o);
         std::memcpy(out + 24 * k, o, 24);
     }
     return bad;
