@@ -1,4 +1,5 @@
 """ctypes binding with the same names as the C ABI (include/llvq.h).  Argument marshalling only."""
+import contextlib
 import ctypes
 import os
 import subprocess
@@ -92,10 +93,11 @@ def _stream_handle(stream):
     return _raw_stream(_current_device()) if stream is None else stream.cuda_stream
 
 
-def _rows(x, K):
-    """x as contiguous rows of K values, and their number"""
+def _rows(x, K, stream):
+    """x as contiguous rows of K values, and their number; a copy is made on the stream that will read it"""
     if x.dim() != 2 or x.shape[1] != K or not x.is_contiguous():
-        x = x.reshape(-1, K)
+        with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
+            x = x.reshape(-1, K).contiguous()
     return x, x.shape[0]
 
 
@@ -175,7 +177,7 @@ class LLVQ:
         if n != N * KB or gain.numel() != N * KB or gain.dtype != torch.float16:
             raise LLVQError("idx and gain must hold N*KB blocks; gain float16")
         code = _X_CODE[x.dtype]
-        x2, M = _rows(x, 24 * KB)
+        x2, M = _rows(x, 24 * KB, stream)
         if out is None:
             out = torch.empty((M, N), dtype=torch.float32, device=x.device)
         if workspace is not None:
@@ -193,7 +195,7 @@ class LLVQ:
         if not (len(gains) == len(Ns) == n_items) or (outs is not None and len(outs) != n_items):
             raise LLVQError("idxs, gains, Ns and outs must have the same length")
         code = _X_CODE[x.dtype]
-        x2, M = _rows(x, 24 * KB)
+        x2, M = _rows(x, 24 * KB, stream)
         fmt = None
         for idx, gain, N in zip(idxs, gains, Ns):
             f, n = self._idx_fmt(idx)
@@ -254,7 +256,7 @@ class LLVQ:
         if gain_lut is not None and gain_lut.numel() != 1 << ((24 if fmt == LLVQ_IDX_U24 else 48) - shape_bits):
             raise LLVQError("gain_lut must hold 2^(word bits - shape_bits) entries")
         code = _X_CODE[x.dtype]
-        x2, M = _rows(x, 24 * KB)
+        x2, M = _rows(x, 24 * KB, stream)
         if out is None:
             out = torch.empty((M, N), dtype=torch.float32, device=x.device)
         self._check(self._lib.llvq_matmul_coded(self._h, x2.data_ptr(), code, M, idx.data_ptr(), fmt, shape_bits, base_index,
