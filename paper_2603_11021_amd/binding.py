@@ -101,6 +101,13 @@ def _rows(x, K, stream):
     return x, x.shape[0]
 
 
+def _workspace(nbytes, device, stream):
+    """Scratch of one call, from the memory of the stream it runs on: freed when the call returns, and not handed out again before
+    that stream is done with it."""
+    with contextlib.nullcontext() if stream is None else torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
 class LLVQ:
     """A context for Lambda_24(m_max) on one device.  Tensors are torch CUDA (ROCm) tensors owned by the caller."""
 
@@ -312,7 +319,7 @@ class LLVQ:
         idx = (torch.empty((N, KB, 6), dtype=torch.uint8, device=W.device) if fmt == LLVQ_IDX_U48
                else torch.empty((N, KB), dtype=torch.int64, device=W.device))
         gain = torch.empty((N, KB), dtype=torch.float16, device=W.device)
-        ws = torch.empty(int(self._lib.llvq_gptq_workspace_bytes(N)), dtype=torch.uint8, device=W.device)
+        ws = _workspace(int(self._lib.llvq_gptq_workspace_bytes(N)), W.device, stream)
         if gain_levels is not None:
             if gain_levels.dtype != torch.float16 or not gain_levels.is_contiguous():
                 raise LLVQError("gain_levels must be a contiguous float16 tensor (ascending levels)")
@@ -334,7 +341,7 @@ class LLVQ:
             raise LLVQError("Wq, W0 contiguous float32 [N, 24*KB], H float32 [K, K], gain float16 [N, KB]")
         KB = K // 24
         s = torch.empty((N, KB), dtype=torch.float32, device=Wq.device)
-        ws = torch.empty(int(self._lib.llvq_gptq_group_scales_workspace_bytes(N, KB)), dtype=torch.uint8, device=Wq.device)
+        ws = _workspace(int(self._lib.llvq_gptq_group_scales_workspace_bytes(N, KB)), Wq.device, stream)
         self._check(self._lib.llvq_gptq_group_scales(self._h, Wq.data_ptr(), W0.data_ptr(), N, KB, K, H.data_ptr(), float(lam),
                                                      gain.data_ptr(), s.data_ptr(), ws.data_ptr(), ws.numel(), _stream_handle(stream)),
                     "llvq_gptq_group_scales")

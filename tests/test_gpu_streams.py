@@ -39,3 +39,44 @@ def test_activations_that_are_not_contiguous(gpu, oracle13, M):
         gpu.llvq_matmul(wide[:, 8:], d_idx, d_gain, N, KB, out=y, stream=stream)
         torch.cuda.synchronize()
         assert np.abs(y.cpu().numpy().astype(np.float64) - ref).max() / np.abs(ref).max() <= 2e-3
+
+
+def test_scratch_of_another_stream_is_not_handed_out_while_it_runs(gpu):
+    import torch
+    from paper_2603_11021_amd import binding
+    n = 3 << 20
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    side = torch.cuda.Stream()
+    ws = binding._workspace(n, "cuda:0", side)
+    where = ws.data_ptr()
+    del ws
+    assert torch.empty(n, dtype=torch.uint8, device="cuda:0").data_ptr() != where       # the current stream's memory
+    ws = binding._workspace(n, "cuda:0", None)
+    where = ws.data_ptr()
+    del ws
+    assert torch.empty(n, dtype=torch.uint8, device="cuda:0").data_ptr() == where       # kept for the next call of a stream
+
+
+def test_gptq_on_another_stream(gpu):
+    """the block-wise loop and the group scales on a stream of the caller's: the results of the current stream"""
+    import torch
+    N, K = 64, 24 * 6
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    W = torch.randn((N, K), device="cuda:0", generator=g)
+    z = torch.randn((2 * K, K), device="cuda:0", generator=g)
+    H = (z.t() @ z / (2 * K) + 0.05 * torch.eye(K, device="cuda:0")).double().cpu().numpy()
+    G = np.linalg.inv(H)
+    U = _dev(np.linalg.cholesky((G + G.T) / 2).T.astype(np.float32))
+    d_H = _dev(H.astype(np.float32))
+    results = []
+    for stream in (None, torch.cuda.Stream()):
+        Wq = W.clone()
+        torch.cuda.synchronize()
+        idx, gain = gpu.llvq_gptq_quantize(Wq, U, stream=stream)
+        s = gpu.llvq_gptq_group_scales(Wq, W, d_H, gain, lam=1e-3, stream=stream)
+        torch.cuda.synchronize()
+        results.append((idx, gain, s, Wq))
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
