@@ -70,9 +70,10 @@ enum {
  * m_max <= 13 (indices below 2^48; 13 is the paper's 2 bits per weight) gets the full library.  14 <= m_max <= 19 (paper
  * Table 1, row m = 19: 23,546,209,100,646,960 points, 55-bit indices) gets the dequantiser only: llvq_decode_i8,
  * llvq_decode, llvq_matmul with M <= 16 (LLVQ_ENOTIMPL above), llvq_matmul_ws (same as llvq_matmul), llvq_validate,
- * llvq_validate_static, llvq_num_points, llvq_num_classes and llvq_shell_offset, through a slower decoder that keeps
- * its tables in global memory; every other call returns LLVQ_ENOTIMPL.  In these contexts a LLVQ_IDX_U64 word carries
- * the index in its low 56 bits (upper 8 bits ignored), and llvq_matmul combines partial sums with fp32 atomic adds.
+ * llvq_validate_static, llvq_num_points, llvq_num_classes and llvq_shell_offset, through the same kernels with larger
+ * tables; every other call returns LLVQ_ENOTIMPL.  In these contexts a LLVQ_IDX_U64 word carries the index in its low
+ * 56 bits (upper 8 bits ignored), and llvq_matmul with 3 <= M <= 16 keeps weights and activations in fp32 (fp32 matrix
+ * instructions); sums are added in the order said there.
  * Builds the constant tables (Golay words, class records, ranking tables) on the host and copies
  * them to the device.  The tables are immutable afterwards; llvq_decode*, llvq_matmul, llvq_matmul_multi, llvq_matmul_coded, llvq_encode,
  * llvq_repack, llvq_quantize and llvq_shell_offset may be called on one context from several threads.  llvq_matmul_ws,
@@ -118,10 +119,12 @@ int llvq_decode(llvq_ctx* ctx, const void* d_idx, int fmt, const void* d_gain, s
  *   type (fp16: one value, relative rounding error 2^-11; bf16: two values, the rounding and the rounding of what it
  *   leaves, together 2^-17) and contracted on the matrix cores with fp32 accumulation.
  *   3 <= M <= 32: a tile of 16 rows is reduced over K inside one workgroup in a fixed order: no clearing, no atomic
- *   adds, the same bits from call to call.  33 <= M <= 64: partial sums of different K ranges are combined with fp32
- *   atomic adds after y was cleared, so the last bits of y can differ between calls.  M > 64: strips of 256 rows x
- *   256 tokens, from M = 384 on panels of 128 rows x 512 tokens; when they number more than half the compute units
- *   K is not split and y is reproducible, otherwise as for 33 <= M <= 64.
+ *   adds, the same bits from call to call.  M >= 33: one of three kernels, with tiles of 64 or 128 rows x up to 128 tokens,
+ *   256 rows x 256 tokens (65 <= M <= 256) or 128 rows x 512 tokens (M >= 257), whichever is estimated to be the fastest for
+ *   the size.  Where a product has too few tiles for the device, several workgroups share the K range of a row, y is
+ *   cleared first and their sums are combined with fp32 atomic adds, so the last bits of y can differ between calls.  That
+ *   is never done, and y is the same from call to call, for M > 64 when strips of 256 rows x 256 tokens (128 rows x
+ *   512 tokens from M = 384 on), partial ones counted, number more than half the compute units.
  *   Requires N*KB < 2^32, KB < 2^24 and M*N < 2^32 (LLVQ_EINVAL otherwise).                            */
 int llvq_matmul(llvq_ctx* ctx, const void* d_x, int x_dtype, int M,
                 const void* d_idx, int fmt, const void* d_gain, int N, int KB,
@@ -131,10 +134,11 @@ int llvq_matmul(llvq_ctx* ctx, const void* d_x, int x_dtype, int M,
  * format: the q/k/v or the gate/up matrices of a transformer block (the fused product of paper App. C, several
  * weight matrices per launch).  d_idx, d_gain, N and d_y are HOST arrays of n_items entries (device pointers and row
  * counts, read during the call); every matrix and every output is laid out as for llvq_matmul (y_i is [M][N_i]).  For
- * M <= 64 all products run in ONE launch (for 33 <= M <= 64 after one launch that clears all outputs), which pays the
- * per-launch start-up once.  For M >= 384 the 128-row strips of all matrices share one launch of the prefill kernel
- * when at least one matrix alone would leave more than half of the compute units idle (k and v next to q; gate and up
- * below 1024 tokens); otherwise, and for 64 < M < 384, the call is the same as n_items calls of llvq_matmul.  Requires
+ * M <= 32 all products run in ONE launch, which pays the per-launch start-up once.  For M >= 33 they run in one launch
+ * (after one that clears all outputs, where K is shared) or one after the other, whichever is estimated to be faster:
+ * together where a matrix alone would leave compute units idle (k and v next to q), apart where large matrices do better in
+ * another kernel.  A matrix gets the same bits from call to call wherever llvq_matmul promises them; against single calls
+ * the order of the sums, and so the last bits, can differ.  Requires
  * (N_0 + .. + N_last)*KB < 2^32; arguments and errors otherwise as for llvq_matmul (LLVQ_EINVAL also for n_items
  * outside 1..4).                                                                                              */
 int llvq_matmul_multi(llvq_ctx* ctx, const void* d_x, int x_dtype, int M, int n_items,
@@ -214,7 +218,7 @@ int llvq_quantize(llvq_ctx* ctx, const float* d_w, size_t n_blocks, int metric, 
  *           input second-moment matrix H (the caller's, e.g. damped); only the upper triangle is read
  *   d_idx : [N][KB] indices in format `fmt` (LLVQ_IDX_U48 or LLVQ_IDX_U64), written;  d_gain: [N][KB] fp16, written
  *   d_ws  : device workspace of at least llvq_gptq_workspace_bytes(N) bytes, 16-byte aligned
- * The dense steps (a 24 x 24 triangular solve and an N x 24 x |R| product per block) are library BLAS calls.
+ * The trailing product of a step (N x 24 x |R|) is a library BLAS call, everything else of it runs in kernels of this library.
  * K not a multiple of 24: pad W with zero columns and U with an identity block.                         */
 size_t llvq_gptq_workspace_bytes(int N);
 int llvq_gptq_quantize(llvq_ctx* ctx, float* d_W, int N, int KB, size_t ldw, const float* d_U,
@@ -239,8 +243,8 @@ int llvq_gptq_quantize_levels(llvq_ctx* ctx, float* d_W, int N, int KB, size_t l
  *           rescaled by exactly the ratio of the two fp16 gains, so that it stays what llvq_decode reconstructs
  *   d_s   : [N][KB] fp32, written: the scales (NULL: not wanted);  lambda >= 0
  *   d_ws  : workspace of at least llvq_gptq_group_scales_workspace_bytes(N, KB) bytes, 16-byte aligned
- * Arithmetic in fp32 (dense products by library BLAS calls, one Cholesky factorisation per row in a kernel of this
- * library); a row whose system is not positive definite in fp32 is left unchanged (s = 1).                      */
+ * Arithmetic in fp32 (products, and one Cholesky factorisation per row, in kernels of this library); a row whose system is
+ * not positive definite in fp32 is left unchanged (s = 1).                                                     */
 size_t llvq_gptq_group_scales_workspace_bytes(int N, int KB);
 int llvq_gptq_group_scales(llvq_ctx* ctx, float* d_Wq, const float* d_W0, int N, int KB, size_t ldw,
                            const float* d_H, float lambda, void* d_gain, float* d_s,

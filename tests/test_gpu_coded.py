@@ -184,7 +184,7 @@ def test_packed_words_carry_index_and_gain(gpu, oracle13, src_fmt):
     y = gpu.llvq_matmul_coded(_dev(x16).half(), packed, N, KB, 48).cpu().numpy()      # matrix-core kernel
     assert _rel(y, oracle13.matmul(x16, idx, gain)) <= TOL
     x300 = synth.activations(synth.rng_for(6, 6102), 100, K, "bf16")
-    y = gpu.llvq_matmul_coded(_dev(x300).to(torch.bfloat16), packed, N, KB, 48).cpu().numpy()   # strip kernel
+    y = gpu.llvq_matmul_coded(_dev(x300).to(torch.bfloat16), packed, N, KB, 48).cpu().numpy()   # activations shared by slices of K
     assert _rel(y, oracle13.matmul(x300, idx, gain)) <= TOL
 
 

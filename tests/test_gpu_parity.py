@@ -229,7 +229,7 @@ def _round_to(a, kind):
 
 @pytest.mark.parametrize("name,M,xd", [("q", 64, "f16"), ("q", 64, "bf16"), ("k", 256, "bf16"), ("q", 1024, "bf16"),
                                        ("down", 64, "bf16"), ("gate", 100, "f16"),
-                                       # enough workgroups for the strip kernel (activations shared through LDS)
+                                       # enough panels of 128 rows x 512 tokens (decoded weights shared through LDS)
                                        ("gate", 1024, "bf16"), ("gate", 520, "f16"), ("down", 700, "bf16")])
 def test_prefill_mfma_llama3_8b_shapes(gpu, oracle13, name, M, xd):
     """Config 4: the matrix-core path.  fp16: weights enter the MFMA scaled and rounded to fp16, so two errors are
@@ -260,7 +260,7 @@ def test_prefill_mfma_llama3_8b_shapes(gpu, oracle13, name, M, xd):
 @pytest.mark.parametrize("N,K,M", [(33, 48, 3), (31, 24, 40), (100, 72, 65), (257, 24 * 7, 130), (64, 24 * 9, 300)])
 @pytest.mark.parametrize("xd", ["f16", "bf16"])
 def test_mfma_ragged_shapes(gpu, oracle13, N, K, M, xd):
-    """every matrix-core kernel (row tiles, split-K tiles, strips) on short ragged rows, both activation types, against
+    """matrix-core kernels (row tiles, slices of K) on short ragged rows, both activation types, against
     the EXACT oracle: bf16 weights enter as two bf16 terms, so rows this short (1-9 blocks) need no averaging"""
     err = _matmul_case(gpu, oracle13, 8, N + K + M, N, K, M, x_dtype=np.float16 if xd == "f16" else "bf16")
     if xd == "bf16":
@@ -296,7 +296,7 @@ def test_batched_decode_row_tiles(gpu, oracle13, N, K, M):
 
 @pytest.mark.parametrize("N,K,M", [(13000, 72, 1024), (26001, 24, 300), (6700, 24 * 5 - 3, 1000)])
 def test_strip_prefill_ragged_shapes(gpu, oracle13, N, K, M):
-    """shapes that take the strip kernel with ragged strips (N not a multiple of 256), ragged passes, an odd block count"""
+    """many rows and few columns at M >= 257: ragged last panels and token groups, one to five blocks per row"""
     _matmul_case(gpu, oracle13, 8, N + K + M, N, K, M, sample_rows=200)
 
 
@@ -305,7 +305,8 @@ def test_strip_prefill_ragged_shapes(gpu, oracle13, N, K, M):
 def test_panel_prefill_ragged_shapes(gpu, oracle13, N, K, M, xd):
     """M >= 384 with enough rows: panels of 128 rows x 512 tokens whose waves split the tokens and share the decoded
     weights through LDS.  Ragged last panel (rows and tokens), token groups past M, an odd block count, one or two steps
-    only, rows split along K with the parts added into a cleared y (the last two shapes); both activation types"""
+    only, rows split along K with the parts added into a cleared y (the last shape); both activation types.  The fifth shape
+    is estimated level and goes to slices of K."""
     err = _matmul_case(gpu, oracle13, 8, 500 + N + K + M, N, K, M, x_dtype=np.float16 if xd == "f16" else "bf16", sample_rows=160)
     if xd == "bf16":
         assert err <= 1e-4, err
@@ -485,7 +486,7 @@ def test_matmul_long_launch_several_passes(gpu, oracle13, N, K, M):
 
 @pytest.mark.parametrize("M", [5, 70])
 def test_matmul_output_not_16_byte_aligned(gpu, oracle13, M):
-    """the split-K paths clear y first (16-byte stores over the aligned middle, single floats at the ends): an output
+    """kernels whose workgroups share the K range of a row clear y first (16-byte stores over the aligned middle, single floats at the ends): an output
     that starts one float into an allocation is cleared exactly, and its neighbours stay untouched"""
     import torch
     N, K = 77, 600
@@ -523,9 +524,9 @@ def test_matmul_multi_small(gpu, oracle13, Ns, K, M):
 @pytest.mark.parametrize("Ns,K,M,xd", [((4096, 1024, 1024), 4096, 1024, "f16"), ((4100, 1000, 130, 3000), 24 * 37, 400, "bf16"),
                                         ((5000, 7000), 24 * 9, 513, "f16")])
 def test_matmul_multi_prefill_panels(gpu, oracle13, Ns, K, M, xd):
-    """several matrices that share x at M >= 384: the 128-row strips of all of them in one launch of the panel kernel
-    (q/k/v of a Llama-3-8B-shaped block; ragged row counts so that every matrix ends in a partial strip; both
-    activation types); sampled rows of every output against the oracle"""
+    """several matrices that share x at M >= 384 in one launch, of the panel kernel (q/k/v of a Llama-3-8B-shaped block, the last
+    shape) or of slices of K (the second one); ragged row counts so that every matrix ends in a partial strip; both
+    activation types; sampled rows of every output against the oracle"""
     import torch
     rng = synth.rng_for(3, 7400 + M + len(Ns))
     KB = synth.blocks_per_row(K)

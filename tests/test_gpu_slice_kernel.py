@@ -1,6 +1,7 @@
-"""llvq_matmul and llvq_matmul_multi at 33 <= M < 384: slices of K that share activation tiles and are added in LDS.  Sizes at the
-edges of its token tiles (32 per tile, up to four per pass), row tiles (64 and 128 rows per workgroup) and slices (block pairs
-dealt to four or eight slices of one or more workgroups: fewer pairs than slices, an odd block count, a row of one block)."""
+"""llvq_matmul and llvq_matmul_multi at M >= 33, kernel by kernel.  Slices of K that share activation tiles and are added in LDS, at
+the edges of token tiles (32 per tile, up to four per pass), row tiles (64 and 128 rows per workgroup) and slices (block pairs
+dealt to four or eight slices of one or more workgroups: fewer pairs than slices, an odd block count, a row of one block); strips
+of 256 rows x 256 tokens; panels of 128 rows x 512 tokens."""
 import numpy as np
 import pytest
 
