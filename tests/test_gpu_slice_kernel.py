@@ -199,3 +199,46 @@ def test_panels_of_several_matrices(gpu, oracle13, Ns, KB, M, xd):
         assert not torch.isnan(y).any()
         err = np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max()
         assert err <= _bound(xd), err
+
+
+def test_products_that_clear_y_can_be_captured_in_a_graph(gpu, oracle13):
+    """K split in each of the three kernels (y is cleared, then added to) and several matrices in one launch: every replay, with eager
+    work and synchronisations in between, reproduces the eager result up to the order of the fp32 atomic adds"""
+    import torch
+    cases = []
+    for N, KB, M, xd in ((40, 171, 160, "f16"), (11001, 301, 250, "bf16"), (4100, 131, 1000, "bf16")):
+        idx, gain, x = synth.layer(8, 9950 + M, N, 24 * KB, M, x_dtype=np.float16 if xd == "f16" else "bf16")
+        rows = np.unique(np.concatenate([[0, N - 1], np.random.default_rng(M).choice(N, min(N, 24), replace=False)]))
+        cases.append((_activations(x, xd), _dev(synth.pack_u48(idx).reshape(-1)), _dev(gain.reshape(-1)), N, KB,
+                      torch.empty((M, N), dtype=torch.float32, device="cuda:0"), rows, oracle13.matmul(x, idx[rows], gain[rows])))
+    x, idx, gain, N, KB = cases[0][:5]
+    several = [torch.empty((x.shape[0], n), dtype=torch.float32, device="cuda:0") for n in (N, 17)]
+
+    def run():
+        for x_, idx_, gain_, N_, KB_, y, _, _ in cases:
+            gpu.llvq_matmul(x_, idx_, gain_, N_, KB_, out=y)
+        gpu.llvq_matmul_multi(x, [idx, idx[:6 * KB * 17]], [gain, gain[:KB * 17]], [N, 17], KB, outs=several)
+
+    run()
+    torch.cuda.synchronize()
+    ys = [c[5] for c in cases] + several
+    eager = [y.clone() for y in ys]
+    for (_, _, _, _, _, y, rows, ref) in cases:
+        assert np.abs(y.cpu().numpy().astype(np.float64)[:, rows] - ref).max() / np.abs(ref).max() <= 2e-3
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        run()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for rep in range(4):
+        for y in ys:
+            y.fill_(float(rep))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for y, want in zip(ys, eager):
+            # up to 16 partial sums of fp32 in another order
+            assert float((y - want).abs().max()) <= 16 * 2.0 ** -23 * float(want.abs().max())
